@@ -326,7 +326,7 @@ typedef struct {
 
 /* One contraction launch of a profiling window, in launch order. */
 typedef struct {
-    int32_t kernel;   /* 1 VALU tile kernel (k_cgemm), 2 MFMA kernel
+    int32_t kernel;   /* 1 wave-sliced kernel (k_cgemm_wave), 2 tile kernel
                          (k_cgemm_mfma), 3 BF16x3 kernel (k_cgemm_bf16x3)     */
     int32_t prec;     /* 0 FP64 operands, 1 FP32 operands                     */
     int32_t heff;     /* 1 when the launch applies H_eff / K_eff              */

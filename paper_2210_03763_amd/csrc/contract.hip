@@ -1,6 +1,7 @@
-// Complex contraction (GEMM) kernels of the TDVP library for gfx950: a tiled
-// VALU fallback, the MFMA kernel and the split-K reduction, with the host-side
-// dispatch cgemm().
+// Complex contraction (GEMM) kernels of the TDVP library for gfx950: the
+// LDS-tiled MFMA kernel, the wave-sliced kernel of short launches, the
+// BF16-split kernel and the split-K reduction, with the host-side dispatch
+// cgemm().
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -13,149 +14,6 @@
 namespace ttn {
 
 namespace {
-
-constexpr int GEMM_THREADS = 256;
-
-template <typename R, int BM, int BN, int BK>
-__global__ __launch_bounds__(GEMM_THREADS) void k_cgemm(Gemm<R> g, int tilesM, int tilesN,
-                                                        int splits, int kchunk, R* partial,
-                                                        int a_mfast, int b_nfast) {
-    if (g.skip && *g.skip) return;
-    constexpr int TM = BM / 16, TN = BN / 16;
-    __shared__ R As[2][BK][BM + 1];
-    __shared__ R Bs[2][BK][BN + 1];
-    int64_t bid = blockIdx.x;
-    const int tm = bid % tilesM;
-    bid /= tilesM;
-    const int tn = bid % tilesN;
-    bid /= tilesN;
-    const int sp = bid % splits;
-    bid /= splits;
-    const int b = (int)bid;
-    const int b1 = b % g.B1, b2 = b / g.B1;
-    const R* A = g.A + b1 * g.sab1 + b2 * g.sab2;
-    const R* B = g.B + b1 * g.sbb1 + b2 * g.sbb2;
-    const int m0 = tm * BM, n0 = tn * BN;
-    const int K = g.Kin * g.Kout;
-    const int kb = sp * kchunk;
-    const int ke = min(K, kb + kchunk);
-    const int tid = threadIdx.x;
-    const int tx = tid % 16, ty = tid / 16;
-    R acc_re[TM][TN], acc_im[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            acc_re[i][j] = 0;
-            acc_im[i][j] = 0;
-        }
-    const R sa = g.conjA ? R(-1) : R(1);
-    const R sb = g.conjB ? R(-1) : R(1);
-    for (int k0 = kb; k0 < ke; k0 += BK) {
-        for (int e = tid; e < BM * BK; e += GEMM_THREADS) {
-            int mm, kk;
-            if (a_mfast) {
-                mm = e % BM;
-                kk = e / BM;
-            } else {
-                kk = e % BK;
-                mm = e / BK;
-            }
-            const int m = m0 + mm, k = k0 + kk;
-            R re = 0, im = 0;
-            if (m < g.M && k < ke) {
-                const int kin = k % g.Kin, kout = k / g.Kin;
-                const int64_t off = (int64_t)m * g.sam + (int64_t)kin * g.sak + (int64_t)kout * g.sako;
-                re = A[off];
-                im = sa * A[off + g.a_plane];
-            }
-            As[0][kk][mm] = re;
-            As[1][kk][mm] = im;
-        }
-        for (int e = tid; e < BN * BK; e += GEMM_THREADS) {
-            int nn, kk;
-            if (b_nfast) {
-                nn = e % BN;
-                kk = e / BN;
-            } else {
-                kk = e % BK;
-                nn = e / BK;
-            }
-            const int n = n0 + nn, k = k0 + kk;
-            R re = 0, im = 0;
-            if (n < g.N && k < ke) {
-                const int kin = k % g.Kin, kout = k / g.Kin;
-                const int64_t off = (int64_t)n * g.sbn + (int64_t)kin * g.sbk + (int64_t)kout * g.sbko;
-                re = B[off];
-                im = sb * B[off + g.b_plane];
-            }
-            Bs[0][kk][nn] = re;
-            Bs[1][kk][nn] = im;
-        }
-        __syncthreads();
-#pragma unroll 4
-        for (int kk = 0; kk < BK; ++kk) {
-            R ar[TM], ai[TM], br[TN], bi[TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                ar[i] = As[0][kk][tx + 16 * i];
-                ai[i] = As[1][kk][tx + 16 * i];
-            }
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                br[j] = Bs[0][kk][ty + 16 * j];
-                bi[j] = Bs[1][kk][ty + 16 * j];
-            }
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    acc_re[i][j] = fma(ar[i], br[j], acc_re[i][j]);
-                    acc_re[i][j] = fma(-ai[i], bi[j], acc_re[i][j]);
-                    acc_im[i][j] = fma(ar[i], bi[j], acc_im[i][j]);
-                    acc_im[i][j] = fma(ai[i], br[j], acc_im[i][j]);
-                }
-        }
-        __syncthreads();
-    }
-    if (splits == 1) {
-        R* C = g.C + b1 * g.scb1 + b2 * g.scb2;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int m = m0 + tx + 16 * i;
-            if (m >= g.M) continue;
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int n = n0 + ty + 16 * j;
-                if (n >= g.N) continue;
-                const int64_t off = (int64_t)m * g.scm + (int64_t)n * g.scn;
-                R re = g.alpha * acc_re[i][j], im = g.alpha * acc_im[i][j];
-                if (g.beta) {
-                    re += C[off];
-                    im += C[off + g.c_plane];
-                }
-                C[off] = re;
-                C[off + g.c_plane] = im;
-            }
-        }
-    } else {
-        const int64_t MN = (int64_t)g.M * g.N;
-        const int nbatch = g.B1 * g.B2;
-        R* P = partial + ((int64_t)sp * nbatch + b) * 2 * MN;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int m = m0 + tx + 16 * i;
-            if (m >= g.M) continue;
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int n = n0 + ty + 16 * j;
-                if (n >= g.N) continue;
-                P[m + (int64_t)g.M * n] = acc_re[i][j];
-                P[MN + m + (int64_t)g.M * n] = acc_im[i][j];
-            }
-        }
-    }
-}
 
 // Sum of the split-K partials into C (alpha, beta applied).  G threads share
 // an element (G a power of two dividing 256): thread group q sums splits q,
@@ -317,7 +175,11 @@ struct MfmaT<double> {
     static constexpr int PAD = 8;
 };
 
-template <typename R, int BM, int BN, int WGM, int WGN, int MINB, int BK, bool AK, bool BKF>
+// RAG: any inner extent and any strides.  The contraction index is walked
+// flattened over (k_in, k_out), each element stepping its own address, loads
+// past K give zero, and the complex product takes four real products (no
+// Re + Im sums), as accurate as a plain FMA loop.
+template <typename R, int BM, int BN, int WGM, int WGN, int MINB, int BK, bool AK, bool BKF, bool RAG = false>
 __global__ __launch_bounds__(64 * WGM * WGN, MINB) void k_cgemm_mfma(Gemm<R> g, int tilesM, int tilesN,
                                                                     int splits, int kchunk, R* partial) {
     if (g.skip && *g.skip) return;
@@ -360,15 +222,27 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void k_cgemm_mfma(Gemm<R> g, 
     const R sa = g.conjA ? R(-1) : R(1), sb = g.conjB ? R(-1) : R(1);
     const int mlim = g.M - m0, nlim = g.N - n0;
 
+    // rows past the edge read row 0: masked to zero, or (RAG) left in outputs
+    // that are not stored
     int offA[QA], offB[QB];
     R mA[QA], mB[QB];
+    // RAG: address of every element's k, its inner index, and the step from the
+    // end of one outer index to the next
+    const R *ptrA[QA], *ptrB[QB];
+    int kinA[QA], kinB[QB];
+    const int64_t wrapA = g.sako - g.Kin * g.sak, wrapB = g.sbko - g.Kin * g.sbk;
 #pragma unroll
     for (int q = 0; q < QA; ++q) {
         const int e = tid + NT * q;
         const int mm = AK ? e / BK : e % BM, kk = AK ? e % BK : e / BM;
         const bool ok = mm < mlim;
         mA[q] = ok ? R(1) : R(0);
-        offA[q] = (ok ? mm : 0) * (int)g.sam + kk * (int)g.sak;
+        if constexpr (RAG) {
+            const int kout = (kb + kk) / g.Kin;
+            kinA[q] = (kb + kk) - kout * g.Kin;
+            ptrA[q] = A + (ok ? mm : 0) * g.sam + kinA[q] * g.sak + kout * g.sako;
+        } else
+            offA[q] = (ok ? mm : 0) * (int)g.sam + kk * (int)g.sak;
     }
 #pragma unroll
     for (int q = 0; q < QB; ++q) {
@@ -376,10 +250,42 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void k_cgemm_mfma(Gemm<R> g, 
         const int nn = BKF ? e / BK : e % BN, kk = BKF ? e % BK : e / BN;
         const bool ok = nn < nlim;
         mB[q] = ok ? R(1) : R(0);
-        offB[q] = (ok ? nn : 0) * (int)g.sbn + kk * (int)g.sbk;
+        if constexpr (RAG) {
+            const int kout = (kb + kk) / g.Kin;
+            kinB[q] = (kb + kk) - kout * g.Kin;
+            ptrB[q] = B + (ok ? nn : 0) * g.sbn + kinB[q] * g.sbk + kout * g.sbko;
+        } else
+            offB[q] = (ok ? nn : 0) * (int)g.sbn + kk * (int)g.sbk;
     }
     R pa[2][QA], pb[2][QB];
     auto fetch = [&](int k0) {
+        if constexpr (RAG) {
+            // tiles are fetched in k order; only the last one can pass ke
+            const bool full = k0 + BK <= ke;
+#pragma unroll
+            for (int q = 0; q < QA; ++q) {
+                const int e = tid + NT * q;
+                const bool ok = full || k0 + (AK ? e % BK : e / BM) < ke;
+                const R* src = ok ? ptrA[q] : A;
+                const R re = src[0], im = src[g.a_plane];
+                pa[0][q] = ok ? re : R(0);
+                pa[1][q] = ok ? sa * im : R(0);
+                ptrA[q] += BK * g.sak;
+                for (kinA[q] += BK; kinA[q] >= g.Kin; kinA[q] -= g.Kin) ptrA[q] += wrapA;
+            }
+#pragma unroll
+            for (int q = 0; q < QB; ++q) {
+                const int e = tid + NT * q;
+                const bool ok = full || k0 + (BKF ? e % BK : e / BN) < ke;
+                const R* src = ok ? ptrB[q] : B;
+                const R re = src[0], im = src[g.b_plane];
+                pb[0][q] = ok ? re : R(0);
+                pb[1][q] = ok ? sb * im : R(0);
+                ptrB[q] += BK * g.sbk;
+                for (kinB[q] += BK; kinB[q] >= g.Kin; kinB[q] -= g.Kin) ptrB[q] += wrapB;
+            }
+            return;
+        }
         const int kin = k0 % g.Kin, kout = k0 / g.Kin;
         const R* Ab = A + (int64_t)kin * g.sak + (int64_t)kout * g.sako;
         const R* Bb = B + (int64_t)kin * g.sbk + (int64_t)kout * g.sbko;
@@ -419,7 +325,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void k_cgemm_mfma(Gemm<R> g, 
             c2[i][j] = acc_t{0, 0, 0, 0};
             c3[i][j] = acc_t{0, 0, 0, 0};
         }
-    const int nt = (ke - kb) / BK;
+    const int nt = RAG ? (ke - kb + BK - 1) / BK : (ke - kb) / BK;
     if (nt > 0) {
         fetch(kb);
         stash(0);
@@ -445,6 +351,18 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void k_cgemm_mfma(Gemm<R> g, 
                 ar[i] = AK ? As[cur][0][am][kr] : As[cur][0][kr][am];
                 ai[i] = AK ? As[cur][1][am][kr] : As[cur][1][kr][am];
                 as[i] = ar[i] + ai[i];
+            }
+            if constexpr (RAG) {   // c1 = Re, c3 = Im
+#pragma unroll
+                for (int i = 0; i < TI; ++i)
+#pragma unroll
+                    for (int j = 0; j < TJ; ++j) {
+                        c1[i][j] = MfmaT<R>::mfma(br[j], ar[i], c1[i][j]);
+                        c3[i][j] = MfmaT<R>::mfma(br[j], ai[i], c3[i][j]);
+                        c1[i][j] = MfmaT<R>::mfma(-bi[j], ai[i], c1[i][j]);
+                        c3[i][j] = MfmaT<R>::mfma(bi[j], ar[i], c3[i][j]);
+                    }
+                continue;
             }
             // the three products of one tile are independent: back-to-back
             // MFMAs never share an accumulator
@@ -476,8 +394,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void k_cgemm_mfma(Gemm<R> g, 
                 const int m = m0 + wm0 + 16 * i + lane % 16;
                 const int n = n0 + wn0 + 16 * j + MfmaT<R>::row(lane, r);
                 if (m >= g.M || n >= g.N) continue;
-                const R vre = c1[i][j][r] - c2[i][j][r];
-                const R vim = c3[i][j][r] - c1[i][j][r] - c2[i][j][r];
+                const R vre = RAG ? c1[i][j][r] : c1[i][j][r] - c2[i][j][r];
+                const R vim = RAG ? c3[i][j][r] : c3[i][j][r] - c1[i][j][r] - c2[i][j][r];
                 if (splits == 1) {
                     const int64_t off = (int64_t)m * g.scm + (int64_t)n * g.scn;
                     R re = g.alpha * vre, im = g.alpha * vim;
@@ -492,6 +410,151 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void k_cgemm_mfma(Gemm<R> g, 
                     P[MN + m + (int64_t)g.M * n] = vim;
                 }
             }
+}
+
+// ---------------------------------------------------------------------------
+// Wave-sliced contraction kernel: any strides, any extents.  A block of WK
+// waves owns one 16 x 16 output tile and splits K among its waves;
+// every wave reads its matrix-core fragments straight from memory (no LDS
+// staging, no barrier in the k loop, the next 16 k in flight while the
+// current 16 are multiplied) and the WK partial tiles meet in LDS once, in
+// wave order.  This is the kernel of the launches that are bound by latency
+// rather than by the matrix cores: few output tiles, short or ragged K.  The
+// complex product takes four real products per complex one, as a plain FMA
+// loop would.
+// Measured (FP64, us per launch inside a replayed graph, where an empty launch
+// costs 3.8): parent-leg stack of a 9 x 9 x 64 node, five operators, 11.1 with
+// 64 x 64 LDS tiles, 4.2 here; right-leg sum of a 27 x 27 x 64 node 33 -> 6.0;
+// parent-leg sum of a 16^3 node over nine operators 12.8 (with its split-K
+// reduction) -> 5.6.  16 x 16 tiles beat 32 x 16 and 32 x 32 ones on every one
+// of these launches (more blocks, fewer loads ahead of the first product).
+//   k order: lane group g = lane / 16 holds k = 16 kb + 4 g + u in its u-th
+// of four matrix-core steps, so an operand contiguous along k is read four
+// consecutive elements per lane; the contraction index is walked flattened
+// over (k_in, k_out), so K is padded once (to 16) and not per outer index.
+// ---------------------------------------------------------------------------
+template <typename R, int WK>
+__global__ __launch_bounds__(64 * WK, 1) void k_cgemm_wave(Gemm<R> g, int tilesM, int tilesN, int splits,
+                                                          int kbper, R* partial) {
+    if (g.skip && *g.skip) return;
+    typedef typename MfmaT<R>::acc_t acc_t;
+    int64_t bid = blockIdx.x;
+    const int tm = bid % tilesM;
+    bid /= tilesM;
+    const int tn = bid % tilesN;
+    bid /= tilesN;
+    const int sp = bid % splits;
+    bid /= splits;
+    const int b = (int)bid;
+    const int b1 = b % g.B1, b2 = b / g.B1;
+    const int m0 = tm * 16, n0 = tn * 16;
+    const int K = g.Kin * g.Kout;
+    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+    const int c16 = lane % 16, g4 = lane / 16;
+    // k blocks of 16: the split's range, then the wave's slice of it
+    const int kb0 = sp * kbper, kb1 = min((K + 15) / 16, kb0 + kbper);
+    const int per = (kb1 - kb0 + WK - 1) / WK;
+    const int wb0 = kb0 + wave * per, wb1 = min(kb1, wb0 + per);
+    // rows past the edge read row 0 (their outputs are not stored)
+    const R* A = g.A + b1 * g.sab1 + b2 * g.sab2 + (m0 + c16 < g.M ? (int64_t)(m0 + c16) * g.sam : 0);
+    const R* B = g.B + b1 * g.sbb1 + b2 * g.sbb2 + (n0 + c16 < g.N ? (int64_t)(n0 + c16) * g.sbn : 0);
+    const R sa = g.conjA ? R(-1) : R(1), sb = g.conjB ? R(-1) : R(1);
+    struct Frag {
+        R ar[4], ai[4], br[4], bi[4];
+    };
+    int k = 16 * wb0 + 4 * g4;
+    int kout = k / g.Kin, kin = k - kout * g.Kin;
+    // the 16 k of the next block: this lane's four, then the step to the block after
+    auto fetch = [&](Frag& f) {
+        int ki = kin, ko = kout;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool ok = k + u < K;
+            const int64_t oa = ok ? (int64_t)ki * g.sak + (int64_t)ko * g.sako : 0;
+            const int64_t ob = ok ? (int64_t)ki * g.sbk + (int64_t)ko * g.sbko : 0;
+            const R ar = A[oa], ai = A[oa + g.a_plane], br = B[ob], bi = B[ob + g.b_plane];
+            f.ar[u] = ok ? ar : R(0);
+            f.ai[u] = ok ? sa * ai : R(0);
+            f.br[u] = ok ? br : R(0);
+            f.bi[u] = ok ? sb * bi : R(0);
+            if (++ki == g.Kin) {
+                ki = 0;
+                ++ko;
+            }
+        }
+        k += 16;
+        kin += 16;
+        while (kin >= g.Kin) {
+            kin -= g.Kin;
+            ++kout;
+        }
+    };
+    acc_t cre = {0, 0, 0, 0}, cim = {0, 0, 0, 0};
+    auto multiply = [&](const Frag& f) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            cre = MfmaT<R>::mfma(f.br[u], f.ar[u], cre);
+            cim = MfmaT<R>::mfma(f.br[u], f.ai[u], cim);
+            cre = MfmaT<R>::mfma(-f.bi[u], f.ai[u], cre);
+            cim = MfmaT<R>::mfma(f.bi[u], f.ar[u], cim);
+        }
+    };
+    if (wb0 < wb1) {
+        Frag f0, f1;
+        fetch(f0);
+        for (int t = wb0; t < wb1; t += 2) {
+            if (t + 1 < wb1) fetch(f1);
+            multiply(f0);
+            if (t + 1 >= wb1) break;
+            if (t + 2 < wb1) fetch(f0);
+            multiply(f1);
+        }
+    }
+    const int64_t MN = (int64_t)g.M * g.N;
+    const int nbatch = g.B1 * g.B2;
+    R* C = g.C + b1 * g.scb1 + b2 * g.scb2;
+    R* P = partial + ((int64_t)sp * nbatch + b) * 2 * MN;
+    auto put = [&](int m, int n, R vre, R vim) {
+        if (m >= g.M || n >= g.N) return;
+        if (splits == 1) {
+            const int64_t off = (int64_t)m * g.scm + (int64_t)n * g.scn;
+            R re = g.alpha * vre, im = g.alpha * vim;
+            if (g.beta) {
+                re += C[off];
+                im += C[off + g.c_plane];
+            }
+            C[off] = re;
+            C[off + g.c_plane] = im;
+        } else {
+            P[m + (int64_t)g.M * n] = vre;
+            P[MN + m + (int64_t)g.M * n] = vim;
+        }
+    };
+    if constexpr (WK == 1) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) put(m0 + c16, n0 + MfmaT<R>::row(lane, r), cre[r], cim[r]);
+    } else {
+        // every wave publishes its partial tile, then each thread sums the WK
+        // values of its outputs in wave order
+        __shared__ R sh[WK][2][16][17];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int n = MfmaT<R>::row(lane, r);
+            sh[wave][0][n][c16] = cre[r];
+            sh[wave][1][n][c16] = cim[r];
+        }
+        __syncthreads();
+        for (int e = threadIdx.x; e < 256; e += 64 * WK) {
+            const int m = e % 16, n = e / 16;
+            R re = 0, im = 0;
+#pragma unroll
+            for (int w = 0; w < WK; ++w) {
+                re += sh[w][0][n][m];
+                im += sh[w][1][n][m];
+            }
+            put(m0 + m, n0 + n, re, im);
+        }
+    }
 }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -734,6 +797,107 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_cgemm_bf16x3(Gemm<float> 
             }
 }
 
+// Launches below this many real flops are bound by latency and take the
+// wave-sliced kernel, above it the LDS-tiled kernels.  Measured on both sides
+// (us, LDS tiles / wave-sliced, split-K reductions included): FP64 0.15 Gflop
+// (a 128 x 128 bond) 16.5 / 11.7, FP32 0.285 Gflop 16.1 / 11.6, FP64 0.54 Gflop
+// (a 64^3 node) 15.8 / 19.2, FP32 0.67 Gflop 14.8 / 23.8.
+constexpr double WAVE_MAX_FLOPS = 0.3e9;
+
+// Split factor of a launch whose `tiles` output tiles leave the chip idle: up
+// to `target` workgroups, at least `minkt` k-tiles each, partial sums within
+// the scratch.
+template <typename R>
+int split_factor(const Gemm<R>& g, const GemmScratch& ws, int64_t tiles, int ktiles, int64_t target, int minkt) {
+    if (tiles >= target || ktiles < 2 * minkt || (int64_t)g.M * g.N >= (1LL << 31)) return 1;
+    const int64_t per = 2 * (int64_t)g.M * g.N * g.B1 * g.B2 * (int64_t)sizeof(R);
+    const int64_t s = std::min<int64_t>((target + tiles - 1) / tiles, ktiles / minkt);
+    return (int)std::max<int64_t>(1, std::min<int64_t>(s, ws.bytes / per));
+}
+
+// Launch of k_cgemm_wave for any Gemm.
+template <typename R>
+void launch_wave(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, CgemmInfo* info) {
+    const int K = g.Kin * g.Kout;
+    const int64_t nbatch = (int64_t)g.B1 * g.B2;
+    const int kblocks = (K + 15) / 16;
+    const int tilesM = (g.M + 15) / 16, tilesN = (g.N + 15) / 16;
+    const int64_t tiles = (int64_t)tilesM * tilesN * nbatch;
+    // waves per tile: one or two k-blocks a wave on short K; sixteen waves on
+    // long K, unless there are tiles enough for several blocks per CU (a stack
+    // over a 128 x 128 bond: 11.7 us with eight waves, 14.9 with sixteen)
+    int wk = kblocks >= 16 && tiles < 512 ? 16 : kblocks >= 8 ? 8 : kblocks >= 2 ? 4 : 1;
+    int splits = split_factor(g, ws, tiles, kblocks, 256, 32);
+    const int kbper = (kblocks + splits - 1) / splits;
+    if (kbper > 0) splits = (kblocks + kbper - 1) / kbper;
+#ifdef TTN_PROBE
+    if (g_force > 100) wk = g_force % 100;
+#endif
+    const dim3 grid((unsigned)(tiles * splits));
+    R* part = (R*)ws.partial;
+    if (info) *info = CgemmInfo{1, splits};
+#define TTN_WAVE_LAUNCH(w)                                                                                   \
+    hipLaunchKernelGGL((k_cgemm_wave<R, w>), grid, dim3(64 * w), 0, s, g, tilesM, tilesN, splits, kbper, part)
+    if (wk == 16)
+        TTN_WAVE_LAUNCH(16);
+    else if (wk == 8)
+        TTN_WAVE_LAUNCH(8);
+    else if (wk == 4)
+        TTN_WAVE_LAUNCH(4);
+    else
+        TTN_WAVE_LAUNCH(1);
+#undef TTN_WAVE_LAUNCH
+    if (splits > 1) splitk_reduce(g, splits, (const R*)ws.partial, s);
+}
+
+// Launch of the ragged form of k_cgemm_mfma: 64 x 64 tiles, or 32 x 32 ones
+// where the larger tiles would compute a quarter more padding (81 x 81 outputs:
+// 103 us with 32, 138 with 64; 250 x 10000 outputs: 341 / 329).
+template <typename R>
+void launch_ragged(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, bool a_k, bool b_k, CgemmInfo* info) {
+    const int K = g.Kin * g.Kout;
+    const int64_t nbatch = (int64_t)g.B1 * g.B2;
+    auto padded = [&](int t) {
+        return (double)((g.M + t - 1) / t) * ((g.N + t - 1) / t) * t * t;
+    };
+    bool small = padded(32) < 0.8 * padded(64);
+#ifdef TTN_PROBE
+    if (g_force == 32) small = true;
+    if (g_force == 64) small = false;
+#endif
+    const int bt = small ? 32 : 64;
+    const int tilesM = (g.M + bt - 1) / bt, tilesN = (g.N + bt - 1) / bt;
+    const int64_t tiles = (int64_t)tilesM * tilesN * nbatch;
+    const int ktiles = (K + 15) / 16;
+    int splits = split_factor(g, ws, tiles, ktiles, small ? 1024 : 512, 4);
+    const int kchunk = (ktiles + splits - 1) / splits * 16;
+    splits = (K + kchunk - 1) / kchunk;
+    const dim3 grid((unsigned)(tiles * splits));
+    R* part = (R*)ws.partial;
+    if (info) *info = CgemmInfo{2, splits};
+#define TTN_RAG_LAUNCH(bt, minb, ak, bk)                                                                       \
+    hipLaunchKernelGGL((k_cgemm_mfma<R, bt, bt, 2, 2, minb, 16, ak, bk, true>), grid, dim3(256), 0, s, g, tilesM, \
+                       tilesN, splits, kchunk, part)
+#define TTN_RAG_LAUNCHES(bt, minb)             \
+    do {                                       \
+        if (a_k && b_k)                        \
+            TTN_RAG_LAUNCH(bt, minb, true, true);    \
+        else if (a_k)                          \
+            TTN_RAG_LAUNCH(bt, minb, true, false);   \
+        else if (b_k)                          \
+            TTN_RAG_LAUNCH(bt, minb, false, true);   \
+        else                                   \
+            TTN_RAG_LAUNCH(bt, minb, false, false);  \
+    } while (0)
+    if (small)
+        TTN_RAG_LAUNCHES(32, 4);
+    else
+        TTN_RAG_LAUNCHES(64, 2);
+#undef TTN_RAG_LAUNCHES
+#undef TTN_RAG_LAUNCH
+    if (splits > 1) splitk_reduce(g, splits, (const R*)ws.partial, s);
+}
+
 // Largest element offset an operand can touch (all strides are >= 0).
 inline bool inside(const GemmScratch& ws, const void* base, int64_t max_off, int64_t plane, int esz) {
     if (!ws.regions) return true;
@@ -789,8 +953,9 @@ bool cgemm(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, char* why, in
     const bool a_k = g.sak == 1 && g.sam != 1, b_k = g.sbk == 1 && g.sbn != 1;
     // per-element offsets inside a tile are 32-bit in the MFMA kernel
     const bool off32 = (int64_t)128 * (g.sam + g.sbn) + 32 * (g.sak + g.sbk) + g.a_plane + g.b_plane < (1LL << 31);
-    const bool mfma_ok = K >= 16 && g.Kin % 16 == 0 && g.M >= 16 && g.N >= 16 && (g.sam == 1 || g.sak == 1) &&
-                         (g.sbn == 1 || g.sbk == 1) && off32;
+    const double flops = 8.0 * g.M * g.N * (double)K * (double)nbatch;
+    const bool mfma_ok = flops >= WAVE_MAX_FLOPS && K >= 16 && g.Kin % 16 == 0 && g.M >= 16 && g.N >= 16 &&
+                         (g.sam == 1 || g.sak == 1) && (g.sbn == 1 || g.sbk == 1) && off32;
     if (mfma_ok) {
         // tile choice: the large tiles, unless their grid (after split-K) would
         // leave more than half of the 256 CUs idle; then the small tiles, whose
@@ -912,33 +1077,11 @@ bool cgemm(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, char* why, in
         if (ev1) (void)hipEventRecord(ev1, s);
         return true;
     }
-    constexpr int BM = 64, BN = 64, BK = 16;
-    const int tilesM = (g.M + BM - 1) / BM, tilesN = (g.N + BN - 1) / BN;
-    const int64_t tiles = (int64_t)tilesM * tilesN * nbatch;
-    int splits = 1;
-    if (K > 0 && tiles < 256 && K > 8 * BK && (int64_t)g.M * g.N < (1LL << 31)) {
-        splits = (int)std::min<int64_t>((512 + tiles - 1) / tiles, K / (4 * BK));
-        const int64_t per = 2 * (int64_t)g.M * g.N * nbatch * (int64_t)sizeof(R);
-        const int64_t cap = per > 0 ? ws.bytes / per : 1;
-        if (splits > cap) splits = (int)cap;
-        if (splits < 1) splits = 1;
-    }
-    int kchunk = K;
-    if (splits > 1) {
-        kchunk = ((K + splits - 1) / splits + BK - 1) / BK * BK;
-        splits = (K + kchunk - 1) / kchunk;
-    }
-    if (K == 0) kchunk = 0;
-    const int a_mfast = (g.sam == 1 || g.sak != 1) ? 1 : 0;
-    const int b_nfast = (g.sbn == 1 || g.sbk != 1) ? 1 : 0;
-    const int64_t blocks = tiles * splits;
-    if (info) *info = CgemmInfo{1, splits};
     if (ev0) (void)hipEventRecord(ev0, s);
-    hipLaunchKernelGGL((k_cgemm<R, BM, BN, BK>), dim3((unsigned)blocks), dim3(GEMM_THREADS), 0, s, g,
-                       tilesM, tilesN, splits, kchunk, (R*)ws.partial, a_mfast, b_nfast);
-    if (splits > 1) {
-        splitk_reduce(g, splits, (const R*)ws.partial, s);
-    }
+    if (K > 0 && flops >= WAVE_MAX_FLOPS)
+        launch_ragged(g, ws, s, a_k, b_k, info);
+    else
+        launch_wave(g, ws, s, info);
     if (ev1) (void)hipEventRecord(ev1, s);
     return true;
 }

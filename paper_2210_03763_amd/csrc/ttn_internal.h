@@ -51,8 +51,8 @@ struct GemmScratch {
     int n_regions = 0;
 };
 
-// What a cgemm call launched: the kernel (1 the VALU tile kernel k_cgemm,
-// 2 the MFMA kernel k_cgemm_mfma, 3 the BF16x3 kernel k_cgemm_bf16x3) and
+// What a cgemm call launched: the kernel (1 the wave-sliced kernel
+// k_cgemm_wave, 2 the LDS-tiled MFMA kernel k_cgemm_mfma, 3 the BF16x3 kernel k_cgemm_bf16x3) and
 // the split-K factor (> 1: a k_splitk_reduce* launch follows).
 struct CgemmInfo {
     int kernel = 0;
