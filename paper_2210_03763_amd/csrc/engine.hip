@@ -110,6 +110,7 @@ struct ttn_handle {
     // eigenvalues (descending) with their column order, split factors
     int64_t n2max = 0, ngmax = 0, mkmax = 0;
     double *Th = nullptr, *G2 = nullptr, *EV = nullptr, *ew = nullptr, *MV = nullptr, *Cm = nullptr;
+    double* ework = nullptr;
     int* eorder = nullptr;
     // program
     int n_seg = 0;
@@ -315,6 +316,7 @@ void plan(ttn_handle* h, Bump& b) {
         h->EV = b.take<double>(2 * h->ngmax * h->ngmax);
         h->ew = b.take<double>(h->ngmax);
         h->eorder = b.take<int>(h->ngmax);
+        h->ework = b.take<double>(herm_eig_work((int)h->ngmax));
         h->MV = b.take<double>(2 * h->mkmax);
         h->Cm = b.take<double>(2 * h->mkmax);
     }
@@ -1440,9 +1442,10 @@ void update_edge2(ttn_handle* h, int v, double tau, bool centre_up) {
     chk(h, h->G2, 2 * ng * ng, "Gram matrix");
     chk(h, h->EV, 2 * ng * ng, "eigenvectors");
     chk(h, h->ew, ng, "eigenvalues");
+    chk(h, h->ework, herm_eig_work((int)ng), "eigensolver work");
     if (n <= m) {
         zgemm(c, (int)n, (int)n, (int)m, h->Th, m, mn, true, h->Th, m, mn, false, h->G2, n, n * n);   // Theta^H Theta
-        herm_eig(h->G2, (int)n, h->EV, h->ew, h->eorder, h->st, h->stream);
+        herm_eig(h->G2, (int)n, h->EV, h->ew, h->eorder, h->ework, h->st, h->stream);
         gather_cols(h->EV, (int)n, h->eorder, (int)k, h->Cm, h->stream);   // V_k (n x k)
         if (centre_up) {
             zgemm(c, (int)m, (int)k, (int)n, h->Th, m, mn, false, h->Cm, n, n * k, false, h->MV, m, m * k);
@@ -1459,7 +1462,7 @@ void update_edge2(ttn_handle* h, int v, double tau, bool centre_up) {
         }
     } else {
         zgemm(c, (int)m, (int)m, (int)n, h->Th, m, mn, false, h->Th, m, mn, true, h->G2, m, m * m);   // Theta Theta^H
-        herm_eig(h->G2, (int)m, h->EV, h->ew, h->eorder, h->st, h->stream);
+        herm_eig(h->G2, (int)m, h->EV, h->ew, h->eorder, h->ework, h->st, h->stream);
         gather_cols(h->EV, (int)m, h->eorder, (int)k, h->MV, h->stream);   // U_k (m x k)
         if (centre_up) {
             copy_d(h->MV, h->T[v], 2 * m * k, nullptr, h->stream);
@@ -2531,9 +2534,11 @@ int ttn_herm_eig(int32_t n, void* d_a, void* d_v, void* d_w, void* d_order, void
     try {
         if (n < 1 || n > JAC_NMAX || !d_a || !d_v || !d_w || !d_order)
             throw StatusError{TTN_EINVAL, "bad size or pointer"};
-        HIPCHECK(hipMalloc(&st, sizeof(StepDev)));
+        // the status block, then the eigensolver's work
+        constexpr size_t off = (sizeof(StepDev) + 255) / 256 * 256;
+        HIPCHECK(hipMalloc(&st, off + (size_t)herm_eig_work(n) * sizeof(double)));
         HIPCHECK(hipMemsetAsync(st, 0, sizeof(StepDev), s));
-        herm_eig((double*)d_a, n, (double*)d_v, (double*)d_w, (int*)d_order, st, s);
+        herm_eig((double*)d_a, n, (double*)d_v, (double*)d_w, (int*)d_order, (double*)((char*)st + off), st, s);
         StepDev hs;
         HIPCHECK(hipMemcpyAsync(&hs, st, sizeof(StepDev), hipMemcpyDeviceToHost, s));
         HIPCHECK(hipStreamSynchronize(s));
