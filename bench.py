@@ -534,14 +534,14 @@ def run_sampling(w, shots, warm_steps=2):
 # (--pmc FETCH_SIZE) and write/ (--pmc WRITE_SIZE), each with its
 # launches.json.  A run's profiling window starts right after the calibration
 # kernel (the dispatch whose name contains "neg_kernel"); in it, contraction
-# launches are the dispatches named k_cgemm_mfma<...>, k_cgemm_bf16x3<...> or
+# launches are the dispatches named k_cgemm_mfma<...>, k_cgemm_split<...> or
 # k_cgemm_wave<...> (the main kernels), each followed by its k_splitk_reduce* dispatch
 # when the launch record says split-K > 1.  The i-th main dispatch after the
 # calibration kernel is the i-th record of launches.json; its kernel class and
 # operand precision are checked against the kernel name.
 
-CONTRACT_MAIN = ("k_cgemm_mfma<", "k_cgemm_bf16x3<", "k_cgemm_wave<")
-KERNEL_CLASS = {"k_cgemm_wave<": 1, "k_cgemm_mfma<": 2, "k_cgemm_bf16x3<": 3}
+CONTRACT_MAIN = ("k_cgemm_mfma<", "k_cgemm_split<3", "k_cgemm_split<2", "k_cgemm_wave<")
+KERNEL_CLASS = {"k_cgemm_wave<": 2, "k_cgemm_mfma<": 2, "k_cgemm_split<3": 2, "k_cgemm_split<2": 3}
 
 
 def _short(name: str) -> str:
@@ -704,7 +704,7 @@ def summarize_profile(profdir, calib_mib=256, out_dir=None):
             "```",
             "",
             "Kernel-name filter of the contraction launches: main kernels `k_cgemm_mfma<...>`,",
-            "`k_cgemm_bf16x3<...>`, `k_cgemm_wave<...>`; each followed by its `k_splitk_reduce<...>` or",
+            "`k_cgemm_split<...>`, `k_cgemm_wave<...>`; each followed by its `k_splitk_reduce<...>` or",
             "`k_splitk_reduce_vec<...>` dispatch when the launch record has split-K > 1 (both counted).",
             "The i-th main dispatch is the i-th record of the library's launch log (kernel class and",
             "operand precision checked); H_eff/K_eff launches are the records flagged heff.",
@@ -874,7 +874,7 @@ def main():
             "frac": round(achieved / PEAK_TFLOPS[dt], 4),
             "traffic": measured_traffic(w.name) if dt == "fp32" else None,
             "kernel": f"H_eff/K_eff matvec launches of the complex {dt.upper()} contraction kernel "
-                      f"(k_cgemm_mfma / k_cgemm_wave with their split-K reductions); each matvec's launches run "
+                      f"(k_cgemm_split / k_cgemm_mfma / k_cgemm_wave with their split-K reductions); each matvec's launches run "
                       f"back to back between one pair of HIP events",
             "launches": int(k.launches), "avg_launch_ms": round(avg_ms, 5),
             "algorithmic_gflop_per_launch": round(k.flops / max(1, k.launches) / 1e9, 4),

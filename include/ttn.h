@@ -326,8 +326,9 @@ typedef struct {
 
 /* One contraction launch of a profiling window, in launch order. */
 typedef struct {
-    int32_t kernel;   /* 1 wave-sliced kernel (k_cgemm_wave), 2 tile kernel
-                         (k_cgemm_mfma), 3 BF16x3 kernel (k_cgemm_bf16x3)     */
+    int32_t kernel;   /* 2 MFMA kernels in the operands' precision
+                         (k_cgemm_wave, k_cgemm_mfma, k_cgemm_split with three
+                         pieces), 3 BF16x3 (k_cgemm_split with two)          */
     int32_t prec;     /* 0 FP64 operands, 1 FP32 operands                     */
     int32_t heff;     /* 1 when the launch applies H_eff / K_eff              */
     int32_t splits;   /* split-K factor; > 1: a k_splitk_reduce* launch follows

@@ -1,7 +1,7 @@
 // Complex contraction (GEMM) kernels of the TDVP library for gfx950: the
-// LDS-tiled MFMA kernel, the wave-sliced kernel of short launches, the
-// BF16-split kernel and the split-K reduction, with the host-side dispatch
-// cgemm().
+// LDS-tiled MFMA kernel, the wave-sliced kernel of short launches, the kernel
+// of FP32 operands split into bf16 pieces and the split-K reduction, with the
+// host-side dispatch cgemm().
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -192,12 +192,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void k_cgemm_mfma(Gemm<R> g, 
     static_assert(QA >= 1 && QB >= 1, "tile smaller than the block");
     typedef typename MfmaT<R>::acc_t acc_t;
     // LDS tiles [buffer][plane][row][col]: an operand whose global layout is
-    // contiguous along k is staged k-contiguous with a row stride of BK + 1
-    // (BK + 2 for 32-wide FP32 k-tiles: a fragment read takes rows r = 0..15
-    // at k + q, q = 0..3, and 34 r + q, unlike 33 r + q, spreads over 64
-    // distinct banks), so that both the coalesced stash and the MFMA fragment
-    // reads hit distinct banks; the others are staged [k][index] with a pad.
-    constexpr int KS = BK + ((sizeof(R) == 4 && BK == 32) ? 2 : 1);
+    // contiguous along k is staged k-contiguous with a row stride of BK + 1, so
+    // that both the coalesced stash and the MFMA fragment reads hit distinct
+    // banks; the others are staged [k][index] with a pad.
+    constexpr int KS = BK + 1;
     constexpr int AR = AK ? BM : BK, AC = AK ? KS : BM + PAD;
     constexpr int BR = BKF ? BN : BK, BC = BKF ? KS : BN + PAD;
     __shared__ R As[2][2][AR][AC];
@@ -558,39 +556,50 @@ __global__ __launch_bounds__(64 * WK, 1) void k_cgemm_wave(Gemm<R> g, int tilesM
 }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // ---------------------------------------------------------------------------
-// BF16-split contraction (precision mode BF16x3): FP32 operands, every real
-// product from bf16 pieces x = hi + lo (hi = bf16(x), lo = bf16(x - hi)) as
-// hi*hi + hi*lo + lo*hi on v_mfma_f32_16x16x32_bf16 with FP32 accumulation
-// (about 16 bits of each operand; relative error near 2^-16 per product).
-// The complex product takes the four real products (Re Re, Im Im, Re Im,
-// Im Re): each operand is staged as four bf16 planes (Re hi, Re lo, Im hi,
-// Im lo), so a matrix-core operation needs a third fewer LDS fragment bytes
-// than the three-product form, whose Re + Im sums add two more planes (that
-// form measured 4-13% slower on the 128^3 stages, and its sums cost accuracy:
-// relative error 1e-5 against 5e-6).  Operand lane layout of the 16x16x32
-// instruction: lane l holds k = 8 (l / 16) .. +7 of row (A) or column (B)
-// l % 16; the output layout is that of 16x16x4.  A 128 x 128 block tile
-// over WGM x WGN waves.  LDS rows are 32 bf16 (64 bytes) with the four 16-byte
-// k-chunks of a row permuted by (row / 4) mod 4, so that the 16 rows of a
-// fragment read fall on distinct banks; two buffers of 64 KB let the next
-// k-tile be stashed while the current one is multiplied (one barrier per
-// k-tile).
+// FP32 operands on the bf16 matrix cores: x is taken as NP bf16 pieces (each
+// the nearest bf16 of what the pieces before it leave of x) and a real product
+// as the products of pieces p, q with p + q < NP on v_mfma_f32_32x32x16_bf16
+// with FP32 accumulation; the complex product takes four real ones.
+//   NP = 3 (FP32 mode): 3 x 8 significant bits hold every FP32 number exactly,
+// the three dropped products are below 2^-24 of the whole.  Against 64 bits
+// the result is closer than that of the FP32 matrix-core kernel it replaced
+// (three FP32 products per complex one, whose Re + Im sums cancel): left-leg
+// stack of a 128^3 node 2.6e-7 (3.9e-7 before), parent-leg sum over 33
+// operators 8.0e-7 (1.17e-6).
+//   NP = 2 (BF16x3 mode): hi hi, hi lo, lo hi, relative error 4.4e-6.
+// Loads are FP32; pieces are made while staging.  A wave owns 64 x 32 outputs
+// (two 32 x 32 tiles); tiles of BM x BN outputs and 16 k, two LDS buffers (98 KB
+// at 128 x 128, NP = 3), so one barrier per k-tile, and the stash of the next
+// tile lies between the products of the current one.
+//   What bounds it (FP32, 256^3 parent-leg sum): the matrix cores are busy
+// 71 % of the cycles, but at 1.7 GHz -- 1.2 PFLOP/s of bf16 products is the
+// chip's power limit (a library bf16 product of 8192^3 reaches 1.13).
+// Measured, us, FP32 matrix cores -> here: 128^3 node, stacks of 17 on the left
+// leg 331 -> 223 and of 16 on the right leg 292 -> 198, right-leg sum over 17
+// 257 -> 183, parent-leg sum over 33 477 -> 337, 256^3 sum over five 1145 ->
+// 804.  BF16x3, kernel with 16x16x32 products and 32-wide k-tiles -> here:
+// 229 -> 156, 243 -> 209 (33), 256^3 right-leg sum over nine 914 -> 840.
+//   RAG: any inner extent, padded to a whole k-tile for every outer index.
 // ---------------------------------------------------------------------------
-template <int WGM, int WGN, bool AK, bool BKF>
-__global__ __launch_bounds__(64 * WGM * WGN, 1) void k_cgemm_bf16x3(Gemm<float> g, int tilesM, int tilesN,
-                                                                    int splits, int kchunk, float* partial, int vec) {
+template <int NP, int BM, int BN, bool AK, bool BKF, bool RAG>
+__global__ __launch_bounds__(64 * (BM / 64) * (BN / 32), 2) void k_cgemm_split(Gemm<float> g, int tilesM, int tilesN,
+                                                                              int splits, int kchunk,
+                                                                              float* partial) {
     if (g.skip && *g.skip) return;
-    constexpr int BM = 128, BN = 128, NT = 64 * WGM * WGN, BK = 32;
-    constexpr int WM = BM / WGM, WN = BN / WGN;
-    constexpr int TI = WM / 16, TJ = WN / 16;
-    constexpr int QA = BM * BK / (4 * NT), QB = BN * BK / (4 * NT);
+    constexpr int BK = 16, NT = 64 * (BM / 64) * (BN / 32);
+    constexpr int TI = 2;   // wave: 64 x 32 outputs, two 32 x 32 tiles along m
+    constexpr int QA = 4 * BM / NT, QB = 4 * BN / NT;
     static_assert(QA >= 1 && QB >= 1, "tile smaller than the block");
-    typedef f32x4 acc_t;
     typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-    __shared__ __attribute__((aligned(16))) __bf16 As[2][4][BM][BK];
-    __shared__ __attribute__((aligned(16))) __bf16 Bs[2][4][BN][BK];
+    typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+    // [buffer][re/im x piece][k / 8][row][8 k]: 16-byte rows, so that the
+    // fragment reads (32 rows of one k half) and the stash are contiguous; the
+    // halves are 64 bytes off the same banks for the stash of k-fast operands
+    __shared__ __attribute__((aligned(16))) __bf16 As[2][2 * NP][2][BM + 4][8];
+    __shared__ __attribute__((aligned(16))) __bf16 Bs[2][2 * NP][2][BN + 4][8];
     int64_t bid = blockIdx.x;
     const int tm = bid % tilesM;
     bid /= tilesM;
@@ -601,168 +610,156 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_cgemm_bf16x3(Gemm<float> 
     const int b = (int)bid;
     const int b1 = b % g.B1, b2 = b / g.B1;
     const int m0 = tm * BM, n0 = tn * BN;
-    const float* A = g.A + b1 * g.sab1 + b2 * g.sab2 + (int64_t)m0 * g.sam;
-    const float* B = g.B + b1 * g.sbb1 + b2 * g.sbb2 + (int64_t)n0 * g.sbn;
-    const int K = g.Kin * g.Kout;
+    // k runs over whole k-tiles of every outer index
+    const int kinP = RAG ? (g.Kin + BK - 1) / BK * BK : g.Kin;
+    const int K = kinP * g.Kout;
     const int kb = sp * kchunk;
     const int ke = min(K, kb + kchunk);
     const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
-    const int wm0 = (wave % WGM) * WM, wn0 = (wave / WGM) * WN;
-    const float sa = g.conjA ? -1.0f : 1.0f, sb = g.conjB ? -1.0f : 1.0f;
-    const int mlim = g.M - m0, nlim = g.N - n0;
-    // slot e (< 1024) of a 128-row tile -> row and k-quad (k = 4 kq .. 4 kq +
-    // 3): a k-fast operand takes eight consecutive slots per row (one row =
-    // 128 contiguous bytes); an index-fast one takes 32 consecutive rows per
-    // k pair
-    auto slot = [&](int e, bool kfast, int& row, int& kq) {
-        if (kfast) {
-            row = e / (BK / 4);
-            kq = e % (BK / 4);
-        } else {
-            row = e % 32 + 32 * ((e / 64) % 4);
-            kq = (e / 32) % 2 + 2 * (e / 256);
-        }
-    };
-    // element offset of (row, k) inside a [rows][32] plane: the 16-byte chunk
-    // k / 8 moves to chunk (k / 8) ^ ((row / 4) % 4)
-    auto lds_off = [](int row, int k) { return row * BK + ((((k >> 3) ^ (row >> 2)) & 3) << 3) + (k & 7); };
-    int offA[QA], offB[QB];
-    float mA[QA], mB[QB];
+    const int wm0 = (wave % (BM / 64)) * 64, wn0 = (wave / (BM / 64)) * 32;
+    // the thread's share of a tile: four k of QA / QB rows, re and im; rows past
+    // the edge read row 0 (their outputs are not stored)
+    auto rowA = [&](int q) { return AK ? (tid + NT * q) / 4 : (tid + NT * q) % BM; };
+    auto rowB = [&](int q) { return BKF ? (tid + NT * q) / 4 : (tid + NT * q) % BN; };
+    auto quadA = [&](int q) { return AK ? tid % 4 : (tid + NT * q) / BM; };
+    auto quadB = [&](int q) { return BKF ? tid % 4 : (tid + NT * q) / BN; };
+    int kin = kb % kinP;
+    const int kout0 = kb / kinP;
+    const float *A[QA], *B[QB];
 #pragma unroll
     for (int q = 0; q < QA; ++q) {
-        int mm, kq;
-        slot(tid + NT * q, AK, mm, kq);
-        const bool ok = mm < mlim;
-        mA[q] = ok ? 1.0f : 0.0f;
-        offA[q] = (ok ? mm : 0) * (int)g.sam + 4 * kq * (int)g.sak;
+        const int r = rowA(q);
+        A[q] = g.A + b1 * g.sab1 + b2 * g.sab2 + (int64_t)m0 * g.sam + kin * g.sak + kout0 * g.sako +
+               (r < g.M - m0 ? r : 0) * g.sam + 4 * quadA(q) * g.sak;
     }
 #pragma unroll
     for (int q = 0; q < QB; ++q) {
-        int nn, kq;
-        slot(tid + NT * q, BKF, nn, kq);
-        const bool ok = nn < nlim;
-        mB[q] = ok ? 1.0f : 0.0f;
-        offB[q] = (ok ? nn : 0) * (int)g.sbn + 4 * kq * (int)g.sbk;
+        const int r = rowB(q);
+        B[q] = g.B + b1 * g.sbb1 + b2 * g.sbb2 + (int64_t)n0 * g.sbn + kin * g.sbk + kout0 * g.sbko +
+               (r < g.N - n0 ? r : 0) * g.sbn + 4 * quadB(q) * g.sbk;
     }
-    float pa[8][QA], pb[8][QB];   // [re k .. k+3, im k .. k+3]
-    auto fetch = [&](int k0) {
-        const int kin = k0 % g.Kin, kout = k0 / g.Kin;
-        const float* Ab = A + (int64_t)kin * g.sak + (int64_t)kout * g.sako;
-        const float* Bb = B + (int64_t)kin * g.sbk + (int64_t)kout * g.sbko;
-        const int ka = (int)g.sak, kbs = (int)g.sbk;
-        const bool va = AK && (vec & 1), vb = BKF && (vec & 2);
+    const int64_t wrapA = g.sako - kinP * g.sak, wrapB = g.sbko - kinP * g.sbk;
+    const float sa = g.conjA ? -1.0f : 1.0f, sb = g.conjB ? -1.0f : 1.0f;
+    float pa[QA][2][4], pb[QB][2][4];
+    // four k of a row, re and im; k0: index of the first of them.  A quad that
+    // reaches past Kin reads its row's k = 0 instead and takes zeros.
+    auto load = [&](float (&x)[2][4], const float* src, int64_t plane, int64_t sk, bool kfast, int k0) {
+        if (RAG && kin + BK > g.Kin) {
 #pragma unroll
-        for (int q = 0; q < QA; ++q)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const float* src = Ab + offA[q] + (h ? g.a_plane : 0);
-                const float sc = h ? sa * mA[q] : mA[q];
-                if (va) {
-                    const float4 t4 = *(const float4*)src;
-                    pa[4 * h][q] = sc * t4.x;
-                    pa[4 * h + 1][q] = sc * t4.y;
-                    pa[4 * h + 2][q] = sc * t4.z;
-                    pa[4 * h + 3][q] = sc * t4.w;
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) pa[4 * h + j][q] = sc * src[j * ka];
-                }
+            for (int j = 0; j < 4; ++j) {
+                const bool ok = k0 + j < g.Kin;
+                const float* s = src + (ok ? j : -k0) * sk;
+                const float re = s[0], im = s[plane];
+                x[0][j] = ok ? re : 0.0f;
+                x[1][j] = ok ? im : 0.0f;
             }
+            return;
+        }
 #pragma unroll
-        for (int q = 0; q < QB; ++q)
+        for (int h = 0; h < 2; ++h) {
+            const float* s = src + (h ? plane : 0);
+            if (kfast) {
+                const f32x4u t4 = *(const f32x4u*)s;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const float* src = Bb + offB[q] + (h ? g.b_plane : 0);
-                const float sc = h ? sb * mB[q] : mB[q];
-                if (vb) {
-                    const float4 t4 = *(const float4*)src;
-                    pb[4 * h][q] = sc * t4.x;
-                    pb[4 * h + 1][q] = sc * t4.y;
-                    pb[4 * h + 2][q] = sc * t4.z;
-                    pb[4 * h + 3][q] = sc * t4.w;
-                } else {
+                for (int j = 0; j < 4; ++j) x[h][j] = t4[j];
+            } else {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) pb[4 * h + j][q] = sc * src[j * kbs];
-                }
+                for (int j = 0; j < 4; ++j) x[h][j] = s[j * sk];
             }
+        }
     };
-    auto put = [](__bf16* hi_dst, __bf16* lo_dst, float x0, float x1, float x2, float x3) {
-        const __bf16 h0 = (__bf16)x0, h1 = (__bf16)x1, h2 = (__bf16)x2, h3 = (__bf16)x3;
-        *(bf16x4*)hi_dst = bf16x4{h0, h1, h2, h3};
-        *(bf16x4*)lo_dst = bf16x4{(__bf16)(x0 - (float)h0), (__bf16)(x1 - (float)h1), (__bf16)(x2 - (float)h2),
-                                  (__bf16)(x3 - (float)h3)};
-    };
-    auto stash = [&](int buf) {
+    // loads this thread's share of the tile at (A, B); advance: on to the next
+    auto fetch = [&](bool advance) {
+        const bool wrap = kin + BK == kinP;
+        const int64_t da = advance ? BK * g.sak + (wrap ? wrapA : 0) : 0;
+        const int64_t db = advance ? BK * g.sbk + (wrap ? wrapB : 0) : 0;
 #pragma unroll
         for (int q = 0; q < QA; ++q) {
-            int mm, kq;
-            slot(tid + NT * q, AK, mm, kq);
-            const int o = lds_off(mm, 4 * kq);
-            put(&As[buf][0][0][0] + o, &As[buf][1][0][0] + o, pa[0][q], pa[1][q], pa[2][q], pa[3][q]);
-            put(&As[buf][2][0][0] + o, &As[buf][3][0][0] + o, pa[4][q], pa[5][q], pa[6][q], pa[7][q]);
+            load(pa[q], A[q], g.a_plane, g.sak, AK, kin + 4 * quadA(q));
+            A[q] += da;
         }
 #pragma unroll
         for (int q = 0; q < QB; ++q) {
-            int nn, kq;
-            slot(tid + NT * q, BKF, nn, kq);
-            const int o = lds_off(nn, 4 * kq);
-            put(&Bs[buf][0][0][0] + o, &Bs[buf][1][0][0] + o, pb[0][q], pb[1][q], pb[2][q], pb[3][q]);
-            put(&Bs[buf][2][0][0] + o, &Bs[buf][3][0][0] + o, pb[4][q], pb[5][q], pb[6][q], pb[7][q]);
+            load(pb[q], B[q], g.b_plane, g.sbk, BKF, kin + 4 * quadB(q));
+            B[q] += db;
+        }
+        kin = advance ? (wrap ? 0 : kin + BK) : kin;
+    };
+    auto stash1 = [&](auto& S, int row, int quad, const float (&x)[2][4], float sg) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            float r[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) r[j] = h ? x[h][j] * sg : x[h][j];
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                bf16x4 v;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    v[j] = (__bf16)r[j];
+                    r[j] -= (float)v[j];
+                }
+                *(bf16x4*)&S[h * NP + p][quad >> 1][row][4 * (quad & 1)] = v;
+            }
         }
     };
-    acc_t crr[TI][TJ], cii[TI][TJ], cim[TI][TJ];
+    auto stash = [&](int buf) {
+#pragma unroll
+        for (int q = 0; q < QA; ++q) stash1(As[buf], rowA(q), quadA(q), pa[q], sa);
+#pragma unroll
+        for (int q = 0; q < QB; ++q) stash1(Bs[buf], rowB(q), quadB(q), pb[q], sb);
+    };
+    f32x16 crr[TI], cii[TI], cim[TI];
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int j = 0; j < TJ; ++j) {
-            crr[i][j] = acc_t{0, 0, 0, 0};
-            cii[i][j] = acc_t{0, 0, 0, 0};
-            cim[i][j] = acc_t{0, 0, 0, 0};
-        }
+        for (int r = 0; r < 16; ++r) crr[i][r] = cii[i][r] = cim[i][r] = 0.0f;
     const int nt = (ke - kb) / BK;
-    const int kg = 8 * (lane / 16), c16 = lane % 16;
+    const int r32 = lane % 32, kh = lane / 32;
     if (nt > 0) {
-        fetch(kb);
+        fetch(nt > 1);
         stash(0);
-        if (nt > 1) fetch(kb + BK);
+        fetch(nt > 2);
     }
     __syncthreads();
     for (int t = 0; t < nt; ++t) {
         const int cur = t & 1;
-        bf16x8 bf[TJ][4];
+        bf16x8 bf[2 * NP], af[TI][2 * NP];
 #pragma unroll
-        for (int j = 0; j < TJ; ++j) {
-            const int o = lds_off(wn0 + 16 * j + c16, kg);
+        for (int p = 0; p < 2 * NP; ++p) bf[p] = *(const bf16x8*)&Bs[cur][p][kh][wn0 + r32][0];
 #pragma unroll
-            for (int p = 0; p < 4; ++p) bf[j][p] = *(const bf16x8*)(&Bs[cur][p][0][0] + o);
-        }
+        for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int i = 0; i < TI; ++i) {
-            bf16x8 af[4];
-            const int o = lds_off(wm0 + 16 * i + c16, kg);
+            for (int p = 0; p < 2 * NP; ++p) af[i][p] = *(const bf16x8*)&As[cur][p][kh][wm0 + 32 * i + r32][0];
 #pragma unroll
-            for (int p = 0; p < 4; ++p) af[p] = *(const bf16x8*)(&As[cur][p][0][0] + o);
+        for (int i = 0; i < TI; ++i)
 #pragma unroll
-            for (int j = 0; j < TJ; ++j) {
-                // planes: 0 Re hi, 1 Re lo, 2 Im hi, 3 Im lo; each real product
-                // hi*hi + lo*hi + hi*lo
-                crr[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j][0], af[0], crr[i][j], 0, 0, 0);
-                cii[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j][2], af[2], cii[i][j], 0, 0, 0);
-                cim[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j][2], af[0], cim[i][j], 0, 0, 0);
-                crr[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j][1], af[0], crr[i][j], 0, 0, 0);
-                cii[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j][3], af[2], cii[i][j], 0, 0, 0);
-                cim[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j][3], af[0], cim[i][j], 0, 0, 0);
-                crr[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j][0], af[1], crr[i][j], 0, 0, 0);
-                cii[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j][2], af[3], cii[i][j], 0, 0, 0);
-                cim[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j][2], af[1], cim[i][j], 0, 0, 0);
-                cim[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j][0], af[2], cim[i][j], 0, 0, 0);
-                cim[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j][1], af[2], cim[i][j], 0, 0, 0);
-                cim[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j][0], af[3], cim[i][j], 0, 0, 0);
+            for (int s2 = NP - 1; s2 >= 0; --s2)   // pieces p + q = s2, the smallest products first
+#pragma unroll
+                for (int p = 0; p <= s2; ++p) {
+                    const int q = s2 - p;
+                    crr[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[p], af[i][q], crr[i], 0, 0, 0);
+                    cii[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[NP + p], af[i][NP + q], cii[i], 0, 0, 0);
+                    cim[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[p], af[i][NP + q], cim[i], 0, 0, 0);
+                    cim[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[NP + p], af[i][q], cim[i], 0, 0, 0);
+                }
+        // the next tile (the last one again past the end) into the other
+        // buffer, its conversions between the products above
+        stash(cur ^ 1);
+        fetch(t + 3 < nt);
+        // BF16x3: fragment reads first, then five vector operations between
+        // two products.  With three pieces the chip runs at its power limit
+        // (1.7 GHz) and the compiler's own order is the faster one.
+        if constexpr (NP == 2) {
+            constexpr int NM = 2 * NP * (NP + 1);       // products per 32 x 32 tile
+            __builtin_amdgcn_sched_group_barrier(0x100, 4 * NP, 0);
+#pragma unroll
+            for (int q = 0; q < 2 * NM; ++q) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                if (q < 2 * NP) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
+                if (q >= 4 && q % 3 == 0) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
             }
-        }
-        if (t + 1 < nt) {
-            stash(cur ^ 1);
-            if (t + 2 < nt) fetch(kb + (t + 2) * BK);
         }
         __syncthreads();
     }
@@ -773,28 +770,26 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_cgemm_bf16x3(Gemm<float> 
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int j = 0; j < TJ; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int m = m0 + wm0 + 16 * i + c16;
-                const int n = n0 + wn0 + 16 * j + 4 * (lane / 16) + r;
-                if (m >= g.M || n >= g.N) continue;
-                const float vre = crr[i][j][r] - cii[i][j][r];
-                const float vim = cim[i][j][r];
-                if (splits == 1) {
-                    const int64_t off = (int64_t)m * g.scm + (int64_t)n * g.scn;
-                    float re = g.alpha * vre, im = g.alpha * vim;
-                    if (g.beta) {
-                        re += C[off];
-                        im += C[off + g.c_plane];
-                    }
-                    C[off] = re;
-                    C[off + g.c_plane] = im;
-                } else {
-                    P[m + (int64_t)g.M * n] = vre;
-                    P[MN + m + (int64_t)g.M * n] = vim;
+        for (int r = 0; r < 16; ++r) {
+            const int m = m0 + wm0 + 32 * i + r32;
+            const int n = n0 + wn0 + 8 * (r / 4) + 4 * kh + r % 4;
+            if (m >= g.M || n >= g.N) continue;
+            const float vre = crr[i][r] - cii[i][r];
+            const float vim = cim[i][r];
+            if (splits == 1) {
+                const int64_t off = (int64_t)m * g.scm + (int64_t)n * g.scn;
+                float re = g.alpha * vre, im = g.alpha * vim;
+                if (g.beta) {
+                    re += C[off];
+                    im += C[off + g.c_plane];
                 }
+                C[off] = re;
+                C[off + g.c_plane] = im;
+            } else {
+                P[m + (int64_t)g.M * n] = vre;
+                P[MN + m + (int64_t)g.M * n] = vim;
             }
+        }
 }
 
 // Launches below this many real flops are bound by latency and take the
@@ -803,6 +798,9 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_cgemm_bf16x3(Gemm<float> 
 // (a 128 x 128 bond) 16.5 / 11.7, FP32 0.285 Gflop 16.1 / 11.6, FP64 0.54 Gflop
 // (a 64^3 node) 15.8 / 19.2, FP32 0.67 Gflop 14.8 / 23.8.
 constexpr double WAVE_MAX_FLOPS = 0.3e9;
+
+// Launches of FP32 arrays from here on may take k_cgemm_split.
+constexpr double SPLIT_MIN_FLOPS = 1e9;
 
 // Split factor of a launch whose `tiles` output tiles leave the chip idle: up
 // to `target` workgroups, at least `minkt` k-tiles each, partial sums within
@@ -830,12 +828,9 @@ void launch_wave(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, CgemmIn
     int splits = split_factor(g, ws, tiles, kblocks, 256, 32);
     const int kbper = (kblocks + splits - 1) / splits;
     if (kbper > 0) splits = (kblocks + kbper - 1) / kbper;
-#ifdef TTN_PROBE
-    if (g_force > 100) wk = g_force % 100;
-#endif
     const dim3 grid((unsigned)(tiles * splits));
     R* part = (R*)ws.partial;
-    if (info) *info = CgemmInfo{1, splits};
+    if (info) *info = CgemmInfo{2, splits};
 #define TTN_WAVE_LAUNCH(w)                                                                                   \
     hipLaunchKernelGGL((k_cgemm_wave<R, w>), grid, dim3(64 * w), 0, s, g, tilesM, tilesN, splits, kbper, part)
     if (wk == 16)
@@ -850,24 +845,19 @@ void launch_wave(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, CgemmIn
     if (splits > 1) splitk_reduce(g, splits, (const R*)ws.partial, s);
 }
 
-// Launch of the ragged form of k_cgemm_mfma: 64 x 64 tiles, or 32 x 32 ones
-// where the larger tiles would compute a quarter more padding (81 x 81 outputs:
-// 103 us with 32, 138 with 64; 250 x 10000 outputs: 341 / 329).
+// Output elements a grid of bm x bn tiles computes, padding included.
+inline double padded(int M, int N, int bm, int bn) {
+    return (double)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * bm * bn;
+}
+
+// Launch of the ragged form of k_cgemm_mfma, 64 x 64 or 32 x 32 tiles.
 template <typename R>
-void launch_ragged(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, bool a_k, bool b_k, CgemmInfo* info) {
+void launch_ragged(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, bool small, bool a_k, bool b_k,
+                   CgemmInfo* info) {
     const int K = g.Kin * g.Kout;
-    const int64_t nbatch = (int64_t)g.B1 * g.B2;
-    auto padded = [&](int t) {
-        return (double)((g.M + t - 1) / t) * ((g.N + t - 1) / t) * t * t;
-    };
-    bool small = padded(32) < 0.8 * padded(64);
-#ifdef TTN_PROBE
-    if (g_force == 32) small = true;
-    if (g_force == 64) small = false;
-#endif
     const int bt = small ? 32 : 64;
     const int tilesM = (g.M + bt - 1) / bt, tilesN = (g.N + bt - 1) / bt;
-    const int64_t tiles = (int64_t)tilesM * tilesN * nbatch;
+    const int64_t tiles = (int64_t)tilesM * tilesN * g.B1 * g.B2;
     const int ktiles = (K + 15) / 16;
     int splits = split_factor(g, ws, tiles, ktiles, small ? 1024 : 512, 4);
     const int kchunk = (ktiles + splits - 1) / splits * 16;
@@ -896,6 +886,57 @@ void launch_ragged(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, bool 
 #undef TTN_RAG_LAUNCHES
 #undef TTN_RAG_LAUNCH
     if (splits > 1) splitk_reduce(g, splits, (const R*)ws.partial, s);
+}
+
+// Launch of k_cgemm_split with bm x bn tiles (128 x 128, 64 x 128, 128 x 64)
+// and np pieces; grids that leave the chip idle (one 128 x 128 block per CU, two
+// of the others) split K, at least four k-tiles each.
+void launch_split(const Gemm<float>& g, const GemmScratch& ws, hipStream_t s, int np, int bm, int bn, bool a_k,
+                  bool b_k, CgemmInfo* info) {
+    const bool rag = g.Kin % 16 != 0;
+    const int K = (g.Kin + 15) / 16 * 16 * g.Kout;
+    const int tilesM = (g.M + bm - 1) / bm, tilesN = (g.N + bn - 1) / bn;
+    const int64_t tiles = (int64_t)tilesM * tilesN * g.B1 * g.B2;
+    const bool wide = bm == 128 && bn == 128;
+    int splits = split_factor(g, ws, tiles, K / 16, wide ? 256 : 512, 4);
+    const int kchunk = (K / 16 + splits - 1) / splits * 16;
+    splits = (K + kchunk - 1) / kchunk;
+    const dim3 grid((unsigned)(tiles * splits)), blk(wide ? 512 : 256);
+    float* part = (float*)ws.partial;
+    if (info) *info = CgemmInfo{np == 2 ? 3 : 2, splits};
+#define TTN_SPLIT_LAUNCH(np, bm, bn, ak, bk, rag)                                                               \
+    hipLaunchKernelGGL((k_cgemm_split<np, bm, bn, ak, bk, rag>), grid, blk, 0, s, g, tilesM, tilesN, splits, kchunk, \
+                       part)
+#define TTN_SPLIT_LAUNCHES(np, bm, bn, rag)                     \
+    do {                                                        \
+        if (a_k && b_k)                                         \
+            TTN_SPLIT_LAUNCH(np, bm, bn, true, true, rag);      \
+        else if (a_k)                                           \
+            TTN_SPLIT_LAUNCH(np, bm, bn, true, false, rag);     \
+        else if (b_k)                                           \
+            TTN_SPLIT_LAUNCH(np, bm, bn, false, true, rag);     \
+        else                                                    \
+            TTN_SPLIT_LAUNCH(np, bm, bn, false, false, rag);    \
+    } while (0)
+#define TTN_SPLIT_TILES(np, rag)                   \
+    do {                                           \
+        if (wide)                                  \
+            TTN_SPLIT_LAUNCHES(np, 128, 128, rag); \
+        else if (bm == 64)                         \
+            TTN_SPLIT_LAUNCHES(np, 64, 128, rag);  \
+        else                                       \
+            TTN_SPLIT_LAUNCHES(np, 128, 64, rag);  \
+    } while (0)
+    if (np == 2)
+        TTN_SPLIT_TILES(2, false);
+    else if (rag)
+        TTN_SPLIT_TILES(3, true);
+    else
+        TTN_SPLIT_TILES(3, false);
+#undef TTN_SPLIT_TILES
+#undef TTN_SPLIT_LAUNCHES
+#undef TTN_SPLIT_LAUNCH
+    if (splits > 1) splitk_reduce(g, splits, (const float*)ws.partial, s);
 }
 
 // Largest element offset an operand can touch (all strides are >= 0).
@@ -951,137 +992,116 @@ bool cgemm(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, char* why, in
     const int K = g.Kin * g.Kout;
     const int64_t nbatch = (int64_t)g.B1 * g.B2;
     const bool a_k = g.sak == 1 && g.sam != 1, b_k = g.sbk == 1 && g.sbn != 1;
-    // per-element offsets inside a tile are 32-bit in the MFMA kernel
-    const bool off32 = (int64_t)128 * (g.sam + g.sbn) + 32 * (g.sak + g.sbk) + g.a_plane + g.b_plane < (1LL << 31);
     const double flops = 8.0 * g.M * g.N * (double)K * (double)nbatch;
-    const bool mfma_ok = flops >= WAVE_MAX_FLOPS && K >= 16 && g.Kin % 16 == 0 && g.M >= 16 && g.N >= 16 &&
-                         (g.sam == 1 || g.sak == 1) && (g.sbn == 1 || g.sbk == 1) && off32;
-    if (mfma_ok) {
-        // tile choice: the large tiles, unless their grid (after split-K) would
-        // leave more than half of the 256 CUs idle; then the small tiles, whose
-        // grid is four times larger and whose splits may be finer
-        struct Plan {
-            bool large;
-            int bm, bn, kq, tilesM, tilesN, splits;
-            int64_t tiles;
-        };
-        auto plan = [&](bool large) {
-            Plan p;
-            p.large = large;
-            p.bm = large ? 128 : 64;
-            p.bn = large ? (sizeof(R) == 4 ? 128 : 64) : 64;
-            // FP32 large tiles take 32-wide k-tiles (half the barriers) where
-            // the inner contraction extent allows them
-            p.kq = (sizeof(R) == 4 && large && g.Kin % 32 == 0) ? 32 : 16;
-            p.tilesM = (g.M + p.bm - 1) / p.bm;
-            p.tilesN = (g.N + p.bn - 1) / p.bn;
-            p.tiles = (int64_t)p.tilesM * p.tilesN * nbatch;
-            p.splits = 1;
-            const int ktiles = K / 16;
-            // split K until the grid covers the chip once: 256 workgroups of the
-            // large tiles (one resident per CU), 512 of the small ones (two per
-            // CU); a split keeps at least four 16-wide k-tiles (large) or two
-            const int64_t target = large ? 256 : 512;
-            const int minkt = large ? 4 : 2;
-            if (p.tiles < 256 && ktiles >= 2 * minkt && (int64_t)g.M * g.N < (1LL << 31)) {
-                p.splits = (int)std::min<int64_t>((target + p.tiles - 1) / p.tiles, ktiles / minkt);
-                const int64_t per = 2 * (int64_t)g.M * g.N * nbatch * (int64_t)sizeof(R);
-                const int64_t cap = per > 0 ? ws.bytes / per : 1;
-                if (p.splits > cap) p.splits = (int)cap;
-                if (p.splits < 1) p.splits = 1;
+    // Tile kernels: the one with the least padded work over its rate (relative
+    // rates measured on shapes without padding).  Launches bound by latency
+    // and K = 0 take the wave-sliced kernel.
+    struct Choice {
+        int bm, bn;
+        double rate;
+    };
+    auto best = [&](std::initializer_list<Choice> cs) {
+        Choice b{0, 0, 0.0};
+        double cost = 0.0;
+        for (const Choice& c : cs) {
+            const double t = padded(g.M, g.N, c.bm, c.bn) / c.rate;
+            if (b.bm == 0 || t < cost) {
+                b = c;
+                cost = t;
             }
-            return p;
-        };
-        Plan pl = plan(g.M >= 128 && g.N >= (sizeof(R) == 4 ? 128 : 64));
-        if (pl.large && pl.tiles * pl.splits < 128) pl = plan(false);
-        const bool big = pl.large;
-        const int BM = pl.bm, kq = pl.kq, tilesM = pl.tilesM, tilesN = pl.tilesN;
-        const int64_t tiles = pl.tiles;
-        int splits = pl.splits;
-        const bool bf16 = sizeof(R) == 4 && g.split && big && kq == 32;
-        int kchunk = K;
-        if (splits > 1) {
-            kchunk = ((K / kq + splits - 1) / splits) * kq;
-            splits = (K + kchunk - 1) / kchunk;
         }
-        const dim3 grid((unsigned)(tiles * splits));
-        R* part = (R*)ws.partial;
-        if (info) *info = CgemmInfo{bf16 ? 3 : 2, splits};
-        // BF16 path: k-fast operands whose k quads are 16-byte aligned load
-        // them as one vector (k tiles start at multiples of 32 in Kin)
-        auto quads = [](const void* p, std::initializer_list<int64_t> strides) {
-            if ((uintptr_t)p % 16) return false;
-            for (int64_t st : strides)
-                if (st % 4) return false;
-            return true;
-        };
-        const int vec = (a_k && quads(g.A, {g.sam, g.sako, g.sab1, g.sab2, g.a_plane}) ? 1 : 0) |
-                        (b_k && quads(g.B, {g.sbn, g.sbko, g.sbb1, g.sbb2, g.b_plane}) ? 2 : 0);
-        if (ev0) (void)hipEventRecord(ev0, s);
-#define TTN_MFMA_LAUNCH(bm, bn, wgm, wgn, minb, bk)                                                        \
-    do {                                                                                                   \
-        const dim3 blk(64 * wgm * wgn);                                                                    \
-        if (a_k && b_k)                                                                                    \
-            hipLaunchKernelGGL((k_cgemm_mfma<R, bm, bn, wgm, wgn, minb, bk, true, true>), grid, blk, 0, s,   \
-                               g, tilesM, tilesN, splits, kchunk, part);                                   \
-        else if (a_k)                                                                                      \
-            hipLaunchKernelGGL((k_cgemm_mfma<R, bm, bn, wgm, wgn, minb, bk, true, false>), grid, blk, 0, s,  \
-                               g, tilesM, tilesN, splits, kchunk, part);                                   \
-        else if (b_k)                                                                                      \
-            hipLaunchKernelGGL((k_cgemm_mfma<R, bm, bn, wgm, wgn, minb, bk, false, true>), grid, blk, 0, s,  \
-                               g, tilesM, tilesN, splits, kchunk, part);                                   \
-        else                                                                                               \
-            hipLaunchKernelGGL((k_cgemm_mfma<R, bm, bn, wgm, wgn, minb, bk, false, false>), grid, blk, 0, s, \
-                               g, tilesM, tilesN, splits, kchunk, part);                                   \
-    } while (0)
-        // large tiles: 16 waves (4 x 4) per block, one block per CU (FP32 waves
-        // own 32 x 32 outputs, FP64 waves 32 x 16); small tiles: 4 waves
-        // (2 x 2), two blocks per CU
-        if constexpr (sizeof(R) == 4) {
-            // BF16x3 mode: the large tiles with 32-wide k-tiles take the split
-            // products; the small shapes stay FP32
-            if (bf16) {
-                // 8 waves (2 x 4) of 64 x 32 outputs
-                const dim3 blk(512);
-                if (a_k && b_k)
-                    hipLaunchKernelGGL((k_cgemm_bf16x3<2, 4, true, true>), grid, blk, 0, s, g, tilesM, tilesN,
-                                       splits, kchunk, part, vec);
-                else if (a_k)
-                    hipLaunchKernelGGL((k_cgemm_bf16x3<2, 4, true, false>), grid, blk, 0, s, g, tilesM, tilesN,
-                                       splits, kchunk, part, vec);
-                else if (b_k)
-                    hipLaunchKernelGGL((k_cgemm_bf16x3<2, 4, false, true>), grid, blk, 0, s, g, tilesM, tilesN,
-                                       splits, kchunk, part, vec);
-                else
-                    hipLaunchKernelGGL((k_cgemm_bf16x3<2, 4, false, false>), grid, blk, 0, s, g, tilesM, tilesN,
-                                       splits, kchunk, part, vec);
-            }
-            else if (BM == 128 && kq == 32)
-                TTN_MFMA_LAUNCH(128, 128, 4, 4, 1, 32);
-            else if (BM == 128)
-                TTN_MFMA_LAUNCH(128, 128, 4, 4, 1, 16);
-            else
-                TTN_MFMA_LAUNCH(64, 64, 2, 2, 2, 16);
-        } else {
-            if (BM == 128)
-                TTN_MFMA_LAUNCH(128, 64, 4, 4, 1, 16);
-            else
-                TTN_MFMA_LAUNCH(64, 64, 2, 2, 2, 16);
-        }
-#undef TTN_MFMA_LAUNCH
-        if (splits > 1) {
-            splitk_reduce(g, splits, (const R*)ws.partial, s);
-        }
-        // the timing window closes after the split-K reduction: a launch's
-        // time is the main kernel plus its reduction
+        return b;
+    };
+    if (ev0) (void)hipEventRecord(ev0, s);
+    if (K == 0 || flops < WAVE_MAX_FLOPS) {
+        launch_wave(g, ws, s, info);
         if (ev1) (void)hipEventRecord(ev1, s);
         return true;
     }
-    if (ev0) (void)hipEventRecord(ev0, s);
-    if (K > 0 && flops >= WAVE_MAX_FLOPS)
-        launch_ragged(g, ws, s, a_k, b_k, info);
-    else
-        launch_wave(g, ws, s, info);
+    // the aligned form of k_cgemm_mfma: per-element offsets inside a tile are
+    // 32-bit there
+    const bool off32 = (int64_t)128 * (g.sam + g.sbn) + 32 * (g.sak + g.sbk) + g.a_plane + g.b_plane < (1LL << 31);
+    const bool mfma_ok = K >= 16 && g.Kin % 16 == 0 && g.M >= 16 && g.N >= 16 && (g.sam == 1 || g.sak == 1) &&
+                         (g.sbn == 1 || g.sbk == 1) && off32;
+    if constexpr (sizeof(R) == 4) {
+        // BF16x3 mode: outputs of at least one 128 x 128 tile whose inner extent
+        // is a multiple of 32, where two blocks in four CUs have work; every
+        // other shape is FP32
+        const Choice t = best({{128, 128, 1.0}, {64, 128, 0.92}, {128, 64, 0.92}});
+        const int64_t tiles128 = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128) * nbatch;
+        const bool bf16 = g.split && mfma_ok && g.M >= 128 && g.N >= 128 && g.Kin % 32 == 0 &&
+                          tiles128 * split_factor(g, ws, tiles128, K / 16, 256, 4) >= 128;
+        // FP32 alternatives on the FP32 matrix cores: the aligned 64 x 64 tiles
+        // (three products), or the ragged tiles (four); below 1 Gflop their
+        // shorter prologue wins (64^3 node, right-leg stack of four, 0.54 Gflop:
+        // 10.6 us against 13.8; 96^3, left-leg stack of five, 3.4 Gflop: 44.5
+        // against 35.7; 208 x 208 x 144, parent-leg sum over three: 305 against
+        // 163 with 128 x 64 tiles)
+        const Choice f = mfma_ok ? Choice{64, 64, 0.55} : best({{64, 64, 0.40}, {32, 32, 0.36}});
+        const double tf = padded(g.M, g.N, f.bm, f.bn) / f.rate, ts = padded(g.M, g.N, t.bm, t.bn) / t.rate;
+        if (bf16 || (flops >= SPLIT_MIN_FLOPS && ts < tf)) {
+            launch_split(g, ws, s, bf16 ? 2 : 3, t.bm, t.bn, a_k, b_k, info);
+            if (ev1) (void)hipEventRecord(ev1, s);
+            return true;
+        }
+    }
+    if (!mfma_ok) {
+        // 32 x 32 tiles where 64 x 64 ones compute much more padding (FP64, 81 x
+        // 81 outputs: 103 us with 32, 138 with 64; 250 x 10000 outputs: 341 / 329)
+        launch_ragged(g, ws, s, best({{64, 64, 1.0}, {32, 32, 0.9}}).bm == 32, a_k, b_k, info);
+        if (ev1) (void)hipEventRecord(ev1, s);
+        return true;
+    }
+    // FP64: 128 x 64 tiles, unless their grid (after split-K) would leave more
+    // than half of the 256 CUs idle; then, and for FP32, 64 x 64 tiles, whose
+    // grid is larger and whose splits may be finer.  Splits cover the chip once:
+    // one workgroup of the large tiles per CU, two of the small ones.
+    bool big = sizeof(R) == 8 && g.M >= 128 && g.N >= 64;
+    int bm = 0, splits = 1;
+    int64_t tiles = 0;
+    for (int pass = 0; pass < 2; ++pass) {
+        bm = big ? 128 : 64;
+        tiles = (int64_t)((g.M + bm - 1) / bm) * ((g.N + 63) / 64) * nbatch;
+        splits = tiles >= 256 ? 1 : split_factor(g, ws, tiles, K / 16, big ? 256 : 512, big ? 4 : 2);
+        if (!big || tiles * splits >= 128) break;
+        big = false;
+    }
+    const int tilesM = (g.M + bm - 1) / bm, tilesN = (g.N + 63) / 64;
+    const int kchunk = (K / 16 + splits - 1) / splits * 16;
+    splits = (K + kchunk - 1) / kchunk;
+    const dim3 grid((unsigned)(tiles * splits));
+    R* part = (R*)ws.partial;
+    if (info) *info = CgemmInfo{2, splits};
+#define TTN_MFMA_LAUNCH(bm, wgm, wgn, minb)                                                                   \
+    do {                                                                                                      \
+        const dim3 blk(64 * wgm * wgn);                                                                       \
+        if (a_k && b_k)                                                                                       \
+            hipLaunchKernelGGL((k_cgemm_mfma<R, bm, 64, wgm, wgn, minb, 16, true, true>), grid, blk, 0, s, g,   \
+                               tilesM, tilesN, splits, kchunk, part);                                         \
+        else if (a_k)                                                                                         \
+            hipLaunchKernelGGL((k_cgemm_mfma<R, bm, 64, wgm, wgn, minb, 16, true, false>), grid, blk, 0, s, g,  \
+                               tilesM, tilesN, splits, kchunk, part);                                         \
+        else if (b_k)                                                                                         \
+            hipLaunchKernelGGL((k_cgemm_mfma<R, bm, 64, wgm, wgn, minb, 16, false, true>), grid, blk, 0, s, g,  \
+                               tilesM, tilesN, splits, kchunk, part);                                         \
+        else                                                                                                  \
+            hipLaunchKernelGGL((k_cgemm_mfma<R, bm, 64, wgm, wgn, minb, 16, false, false>), grid, blk, 0, s, g, \
+                               tilesM, tilesN, splits, kchunk, part);                                         \
+    } while (0)
+    // large tiles: 16 waves (4 x 4) of 32 x 16 outputs, one block per CU; small
+    // tiles: 4 waves (2 x 2), two blocks per CU
+    if constexpr (sizeof(R) == 8) {
+        if (big)
+            TTN_MFMA_LAUNCH(128, 4, 4, 1);
+        else
+            TTN_MFMA_LAUNCH(64, 2, 2, 2);
+    } else {
+        TTN_MFMA_LAUNCH(64, 2, 2, 2);
+    }
+#undef TTN_MFMA_LAUNCH
+    if (splits > 1) splitk_reduce(g, splits, (const R*)ws.partial, s);
+    // the timing window closes after the split-K reduction: a launch's time
+    // is the main kernel plus its reduction
     if (ev1) (void)hipEventRecord(ev1, s);
     return true;
 }

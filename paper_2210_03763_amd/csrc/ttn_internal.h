@@ -51,9 +51,10 @@ struct GemmScratch {
     int n_regions = 0;
 };
 
-// What a cgemm call launched: the kernel (1 the wave-sliced kernel
-// k_cgemm_wave, 2 the LDS-tiled MFMA kernel k_cgemm_mfma, 3 the BF16x3 kernel k_cgemm_bf16x3) and
-// the split-K factor (> 1: a k_splitk_reduce* launch follows).
+// What a cgemm call launched: the kernel (2 a matrix-core kernel in the
+// operands' precision -- k_cgemm_wave, k_cgemm_mfma, or k_cgemm_split with three
+// pieces -- 3 k_cgemm_split with two pieces, the BF16x3 products) and the
+// split-K factor (> 1: a k_splitk_reduce* launch follows).
 struct CgemmInfo {
     int kernel = 0;
     int splits = 0;
