@@ -540,8 +540,8 @@ def run_sampling(w, shots, warm_steps=2):
 # calibration kernel is the i-th record of launches.json; its kernel class and
 # operand precision are checked against the kernel name.
 
-CONTRACT_MAIN = ("k_cgemm_mfma<", "k_cgemm_split<3", "k_cgemm_split<2", "k_cgemm_wave<")
-KERNEL_CLASS = {"k_cgemm_wave<": 2, "k_cgemm_mfma<": 2, "k_cgemm_split<3": 2, "k_cgemm_split<2": 3}
+CONTRACT_MAIN = ("k_cgemm_mfma<", "k_cgemm_split<3", "k_cgemm_split<2", "k_cgemm_wave<", "k_cgemm_wave_group<")
+KERNEL_CLASS = {"k_cgemm_wave<": 2, "k_cgemm_wave_group<": 2, "k_cgemm_mfma<": 2, "k_cgemm_split<3": 2, "k_cgemm_split<2": 3}
 
 
 def _short(name: str) -> str:

@@ -432,11 +432,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void k_cgemm_mfma(Gemm<R> g, 
 // over (k_in, k_out), so K is padded once (to 16) and not per outer index.
 // ---------------------------------------------------------------------------
 template <typename R, int WK>
-__global__ __launch_bounds__(64 * WK, 1) void k_cgemm_wave(Gemm<R> g, int tilesM, int tilesN, int splits,
-                                                          int kbper, R* partial) {
+__device__ inline void wave_tile(const Gemm<R>& g, int64_t bid, int tilesM, int tilesN, int splits, int kbper,
+                                 R* partial) {
     if (g.skip && *g.skip) return;
     typedef typename MfmaT<R>::acc_t acc_t;
-    int64_t bid = blockIdx.x;
     const int tm = bid % tilesM;
     bid /= tilesM;
     const int tn = bid % tilesN;
@@ -553,6 +552,30 @@ __global__ __launch_bounds__(64 * WK, 1) void k_cgemm_wave(Gemm<R> g, int tilesM
             put(m0 + m, n0 + n, re, im);
         }
     }
+}
+
+template <typename R, int WK>
+__global__ __launch_bounds__(64 * WK, 1) void k_cgemm_wave(Gemm<R> g, int tilesM, int tilesN, int splits,
+                                                          int kbper, R* partial) {
+    wave_tile<R, WK>(g, blockIdx.x, tilesM, tilesN, splits, kbper, partial);
+}
+
+// Several independent contractions in one launch (no split K): block b works
+// on the member whose range [first[i], first[i + 1]) holds it.
+template <typename R>
+struct WaveGroup {
+    Gemm<R> g[GROUP_MAX];
+    int first[GROUP_MAX + 1];
+    int count;
+};
+
+template <typename R, int WK>
+__global__ __launch_bounds__(64 * WK, 1) void k_cgemm_wave_group(WaveGroup<R> w) {
+    int i = 0;
+    while (i + 1 < w.count && (int)blockIdx.x >= w.first[i + 1]) ++i;
+    const Gemm<R>& g = w.g[i];
+    wave_tile<R, WK>(g, blockIdx.x - w.first[i], (g.M + 15) / 16, (g.N + 15) / 16, 1,
+                     (g.Kin * g.Kout + 15) / 16, nullptr);
 }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -813,19 +836,33 @@ int split_factor(const Gemm<R>& g, const GemmScratch& ws, int64_t tiles, int kti
     return (int)std::max<int64_t>(1, std::min<int64_t>(s, ws.bytes / per));
 }
 
+// Waves per tile of k_cgemm_wave: one or two k-blocks a wave on short K;
+// sixteen waves on long K, unless there are tiles enough for several blocks
+// per CU (a stack over a 128 x 128 bond: 11.7 us with eight waves, 14.9 with
+// sixteen).
+inline int wave_count(int kblocks, int64_t tiles) {
+    return kblocks >= 16 && tiles < 512 ? 16 : kblocks >= 8 ? 8 : kblocks >= 2 ? 4 : 1;
+}
+
+template <typename R>
+int64_t wave_tiles(const Gemm<R>& g) {
+    return (int64_t)((g.M + 15) / 16) * ((g.N + 15) / 16) * g.B1 * g.B2;
+}
+
+template <typename R>
+int wave_splits(const Gemm<R>& g, const GemmScratch& ws) {
+    return split_factor(g, ws, wave_tiles(g), (g.Kin * g.Kout + 15) / 16, 256, 32);
+}
+
 // Launch of k_cgemm_wave for any Gemm.
 template <typename R>
 void launch_wave(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, CgemmInfo* info) {
     const int K = g.Kin * g.Kout;
-    const int64_t nbatch = (int64_t)g.B1 * g.B2;
     const int kblocks = (K + 15) / 16;
     const int tilesM = (g.M + 15) / 16, tilesN = (g.N + 15) / 16;
-    const int64_t tiles = (int64_t)tilesM * tilesN * nbatch;
-    // waves per tile: one or two k-blocks a wave on short K; sixteen waves on
-    // long K, unless there are tiles enough for several blocks per CU (a stack
-    // over a 128 x 128 bond: 11.7 us with eight waves, 14.9 with sixteen)
-    int wk = kblocks >= 16 && tiles < 512 ? 16 : kblocks >= 8 ? 8 : kblocks >= 2 ? 4 : 1;
-    int splits = split_factor(g, ws, tiles, kblocks, 256, 32);
+    const int64_t tiles = wave_tiles(g);
+    const int wk = wave_count(kblocks, tiles);
+    int splits = wave_splits(g, ws);
     const int kbper = (kblocks + splits - 1) / splits;
     if (kbper > 0) splits = (kblocks + kbper - 1) / kbper;
     const dim3 grid((unsigned)(tiles * splits));
@@ -963,31 +1000,77 @@ inline bool inside(const GemmScratch& ws, const void* base, int64_t max_off, int
 bool g_dry_run = false;
 
 template <typename R>
+bool cgemm_check(const Gemm<R>& g, const GemmScratch& ws, char* why, int whylen) {
+    const int64_t km = g.Kin > 0 ? g.Kin - 1 : 0, ko = g.Kout > 0 ? g.Kout - 1 : 0;
+    const int64_t b1 = g.B1 - 1, b2 = g.B2 - 1;
+    const int64_t amax = (g.M - 1) * g.sam + km * g.sak + ko * g.sako + b1 * g.sab1 + b2 * g.sab2;
+    const int64_t bmax = (g.N - 1) * g.sbn + km * g.sbk + ko * g.sbko + b1 * g.sbb1 + b2 * g.sbb2;
+    const int64_t cmax = (g.M - 1) * g.scm + (g.N - 1) * g.scn + b1 * g.scb1 + b2 * g.scb2;
+    const bool neg = g.sam < 0 || g.sak < 0 || g.sako < 0 || g.sab1 < 0 || g.sab2 < 0 || g.sbn < 0 ||
+                     g.sbk < 0 || g.sbko < 0 || g.sbb1 < 0 || g.sbb2 < 0 || g.scm < 0 || g.scn < 0 ||
+                     g.scb1 < 0 || g.scb2 < 0 || g.a_plane < 0 || g.b_plane < 0 || g.c_plane < 0;
+    const char* bad = neg ? "negative stride"
+                      : !inside(ws, g.A, amax, g.a_plane, sizeof(R)) ? "operand A out of its region"
+                      : !inside(ws, g.B, bmax, g.b_plane, sizeof(R)) ? "operand B out of its region"
+                      : !inside(ws, g.C, cmax, g.c_plane, sizeof(R)) ? "operand C out of its region"
+                                                                     : nullptr;
+    if (bad) {
+        if (why)
+            snprintf(why, whylen, "%s (M=%d N=%d Kin=%d Kout=%d B=%dx%d)", bad, g.M, g.N, g.Kin, g.Kout,
+                     g.B1, g.B2);
+        return false;
+    }
+    return true;
+}
+
+template <typename R>
+bool cgemm_groupable(const Gemm<R>& g, const GemmScratch& ws) {
+    const double flops = 8.0 * g.M * g.N * (double)g.Kin * g.Kout * (double)g.B1 * g.B2;
+    return flops > 0 && flops < WAVE_MAX_FLOPS && wave_splits(g, ws) == 1;
+}
+
+template <typename R>
+int cgemm_group(const Gemm<R>* g, int count, const GemmScratch& ws, hipStream_t s) {
+    if (g_dry_run || count <= 0) return 0;
+    WaveGroup<R> w;
+    w.count = count;
+    w.first[0] = 0;
+    int wk = 1;
+    int64_t total = 0, waves = 0;
+    for (int i = 0; i < count; ++i) {
+        w.g[i] = g[i];
+        total += wave_tiles(g[i]);
+        w.first[i + 1] = (int)total;
+    }
+    for (int i = 0; i < count; ++i) {
+        const int k = wave_count((g[i].Kin * g[i].Kout + 15) / 16, total);
+        wk = std::max(wk, k);
+        waves += k * wave_tiles(g[i]);
+    }
+    // one launch has one wave count: apart, if that would be more than the chip
+    // holds (8192 waves) for the sake of a member with few tiles
+    if (count == 1 || (wk * total > 8192 && wk * total > 2 * waves)) {
+        for (int i = 0; i < count; ++i) launch_wave(g[i], ws, s, nullptr);
+        return count;
+    }
+    const dim3 grid((unsigned)total);
+    if (wk == 16)
+        hipLaunchKernelGGL((k_cgemm_wave_group<R, 16>), grid, dim3(1024), 0, s, w);
+    else if (wk == 8)
+        hipLaunchKernelGGL((k_cgemm_wave_group<R, 8>), grid, dim3(512), 0, s, w);
+    else if (wk == 4)
+        hipLaunchKernelGGL((k_cgemm_wave_group<R, 4>), grid, dim3(256), 0, s, w);
+    else
+        hipLaunchKernelGGL((k_cgemm_wave_group<R, 1>), grid, dim3(64), 0, s, w);
+    return 1;
+}
+
+template <typename R>
 bool cgemm(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, char* why, int whylen, hipEvent_t ev0,
            hipEvent_t ev1, CgemmInfo* info) {
     if (info) *info = CgemmInfo{};
     if (g.M <= 0 || g.N <= 0 || g.B1 * g.B2 <= 0) return true;
-    {
-        const int64_t km = g.Kin > 0 ? g.Kin - 1 : 0, ko = g.Kout > 0 ? g.Kout - 1 : 0;
-        const int64_t b1 = g.B1 - 1, b2 = g.B2 - 1;
-        const int64_t amax = (g.M - 1) * g.sam + km * g.sak + ko * g.sako + b1 * g.sab1 + b2 * g.sab2;
-        const int64_t bmax = (g.N - 1) * g.sbn + km * g.sbk + ko * g.sbko + b1 * g.sbb1 + b2 * g.sbb2;
-        const int64_t cmax = (g.M - 1) * g.scm + (g.N - 1) * g.scn + b1 * g.scb1 + b2 * g.scb2;
-        const bool neg = g.sam < 0 || g.sak < 0 || g.sako < 0 || g.sab1 < 0 || g.sab2 < 0 || g.sbn < 0 ||
-                         g.sbk < 0 || g.sbko < 0 || g.sbb1 < 0 || g.sbb2 < 0 || g.scm < 0 || g.scn < 0 ||
-                         g.scb1 < 0 || g.scb2 < 0 || g.a_plane < 0 || g.b_plane < 0 || g.c_plane < 0;
-        const char* bad = neg ? "negative stride"
-                          : !inside(ws, g.A, amax, g.a_plane, sizeof(R)) ? "operand A out of its region"
-                          : !inside(ws, g.B, bmax, g.b_plane, sizeof(R)) ? "operand B out of its region"
-                          : !inside(ws, g.C, cmax, g.c_plane, sizeof(R)) ? "operand C out of its region"
-                                                                         : nullptr;
-        if (bad) {
-            if (why)
-                snprintf(why, whylen, "%s (M=%d N=%d Kin=%d Kout=%d B=%dx%d)", bad, g.M, g.N, g.Kin, g.Kout,
-                         g.B1, g.B2);
-            return false;
-        }
-    }
+    if (!cgemm_check(g, ws, why, whylen)) return false;
     if (g_dry_run) return true;
     const int K = g.Kin * g.Kout;
     const int64_t nbatch = (int64_t)g.B1 * g.B2;
@@ -1106,6 +1189,12 @@ bool cgemm(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, char* why, in
     return true;
 }
 
+template bool cgemm_check<double>(const Gemm<double>&, const GemmScratch&, char*, int);
+template bool cgemm_check<float>(const Gemm<float>&, const GemmScratch&, char*, int);
+template bool cgemm_groupable<double>(const Gemm<double>&, const GemmScratch&);
+template bool cgemm_groupable<float>(const Gemm<float>&, const GemmScratch&);
+template int cgemm_group<double>(const Gemm<double>*, int, const GemmScratch&, hipStream_t);
+template int cgemm_group<float>(const Gemm<float>*, int, const GemmScratch&, hipStream_t);
 template bool cgemm<double>(const Gemm<double>&, const GemmScratch&, hipStream_t, char*, int, hipEvent_t,
                             hipEvent_t, CgemmInfo*);
 template bool cgemm<float>(const Gemm<float>&, const GemmScratch&, hipStream_t, char*, int, hipEvent_t,

@@ -28,6 +28,12 @@ constexpr double COMPLETION_TOL = 1e-8;   // Gram-Schmidt acceptance for initial
 // single-workgroup final sums shrink), 4096 and 8192 slower
 constexpr int RED_BLOCKS = 1024;
 
+// Operators up to this many entries keep the sums of a matvec over different
+// legs in outputs of their own, so that they go out in one launch (above it
+// the sums are launches of their own anyway)
+constexpr int64_t LZ_OUT2_N = 16384;
+static_assert(LZ_OUT2_N >= LZ_BLOCK_N, "the block path sums two or three outputs");
+
 struct StatusError {
     int code;
     std::string msg;
@@ -92,7 +98,8 @@ struct ttn_handle {
     int64_t nmax = 0, stack_max = 0, env_max = 0;
     int max_sites = 0, Dmax = 0;
     double *X = nullptr, *W = nullptr, *Vk = nullptr, *Qtmp = nullptr, *Ttmp = nullptr;
-    float *Xf = nullptr, *Yf = nullptr;
+    double* W2 = nullptr;
+    float *Xf = nullptr, *Yf = nullptr, *Yf2 = nullptr;
     double *Bstk = nullptr, *Astk = nullptr;
     float *Lf = nullptr, *Rf = nullptr, *Bf = nullptr, *Wf = nullptr, *Ef = nullptr;
     // FP32 stacks of the fused-left matvec: [N_i (S_L), H_L] and
@@ -306,7 +313,9 @@ void plan(ttn_handle* h, Bump& b) {
     h->d_leaf_site = b.take<int>(h->N);
     h->X = b.take<double>(2 * h->stack_max);
     h->W = b.take<double>(2 * nvec);
-    // planar bases (small path, n <= LZ_SMALL_N) or chunked ones: padded to whole chunks
+    // second and third matvec outputs of short operators
+    h->W2 = b.take<double>(2 * 2 * LZ_OUT2_N);
+    // planar bases (n <= LZ_BLOCK_N) or chunked ones: padded to whole chunks
     h->Vk = b.take<double>(2 * kch_pad(nvec) * (h->m + 1));
     h->Qtmp = b.take<double>(2 * nqr);
     h->Ttmp = b.take<double>(2 * h->nmax);
@@ -323,6 +332,7 @@ void plan(ttn_handle* h, Bump& b) {
     if (h->prec == TTN_PREC_FP32) {
         h->Xf = b.take<float>(2 * h->stack_max);
         h->Yf = b.take<float>(2 * h->nmax);
+        h->Yf2 = b.take<float>(2 * LZ_OUT2_N);
         h->Lf = b.take<float>(2 * smax * D2);
         h->Rf = b.take<float>(2 * smax * D2);
         h->Bf = b.take<float>(2 * smax * D2);
@@ -376,37 +386,97 @@ int take_events(ttn_handle* h, int k) {
     return idx;
 }
 
+// Issues the contractions of a sequence.  Between begin() and end() (Group)
+// short ones are held back and leave as one launch; a contraction that reads or
+// writes what a held one writes, or writes what one reads, sends them off
+// first, so the sequence means what it says.  Only contractions may be issued
+// inside a Group.
 template <typename R>
 struct Ctx {
     ttn_handle* h;
     const int* skip;
     double flops_less = 0;   // flops of the next launches that are not algorithmic (padding terms)
+    struct Span {
+        uintptr_t lo, hi;
+    };
+    int depth = 0, held = 0;
+    Gemm<R> hold[GROUP_MAX];
+    Span rd[GROUP_MAX][2], wr[GROUP_MAX];
+    double held_flops = 0;
+
+    static Span span(const R* p, int64_t last) { return Span{(uintptr_t)p, (uintptr_t)p + (uintptr_t)(last + 1) * sizeof(R)}; }
+    static bool meet(const Span& a, const Span& b) { return a.lo < b.hi && b.lo < a.hi; }
+
+    void record(double fl, int splits, int kernel, int idx) {
+        h->prof_recs.push_back({idx, sizeof(R) == 4 ? 1 : 0, fl, h->in_heff, kernel, splits,
+                                h->in_heff ? (int)h->prof_matvecs - 1 : -1});
+    }
+    // launches inside an H_eff / K_eff matvec are timed per matvec (one event
+    // pair around all its launches), the others one by one
+    int events() { return h->prof_timed && !h->in_heff ? take_events(h, 2) : -1; }
+
+    void flush() {
+        if (held == 0) return;
+        const int cnt = held;
+        held = 0;
+        const bool rec = h->prof && !h->dry;
+        const int idx = rec ? events() : -1;
+        if (idx >= 0) (void)hipEventRecord(h->ev_pool[idx], h->stream);
+        const int launches = cgemm_group<R>(hold, cnt, h->gs, h->stream);
+        if (idx >= 0) (void)hipEventRecord(h->ev_pool[idx + 1], h->stream);
+        for (int i = 0; rec && i < launches; ++i) record(i == 0 ? held_flops : 0.0, 1, 2, i == 0 ? idx : -1);
+        held_flops = 0;
+    }
+
     void run(const Gemm<R>& g) {
         char why[256];
+        const double fl = 8.0 * g.M * g.N * (double)g.Kin * g.Kout * (double)g.B1 * g.B2 - flops_less;
+        if (depth > 0 && g.M > 0 && g.N > 0 && g.B1 * g.B2 > 0 && cgemm_groupable<R>(g, h->gs)) {
+            if (!cgemm_check<R>(g, h->gs, why, sizeof(why)))
+                throw StatusError{TTN_EINVAL, std::string("launch extent check failed: ") + why};
+            const int64_t km = g.Kin - 1, ko = g.Kout - 1, b1 = g.B1 - 1, b2 = g.B2 - 1;
+            const Span a = span(g.A, (g.M - 1) * g.sam + km * g.sak + ko * g.sako + b1 * g.sab1 + b2 * g.sab2 + g.a_plane);
+            const Span b = span(g.B, (g.N - 1) * g.sbn + km * g.sbk + ko * g.sbko + b1 * g.sbb1 + b2 * g.sbb2 + g.b_plane);
+            const Span c = span(g.C, (g.M - 1) * g.scm + (g.N - 1) * g.scn + b1 * g.scb1 + b2 * g.scb2 + g.c_plane);
+            for (int i = 0; i < held; ++i)
+                if (meet(wr[i], a) || meet(wr[i], b) || meet(wr[i], c) || meet(rd[i][0], c) || meet(rd[i][1], c)) {
+                    flush();
+                    break;
+                }
+            hold[held] = g;
+            rd[held][0] = a;
+            rd[held][1] = b;
+            wr[held] = c;
+            held_flops += fl;
+            if (++held == GROUP_MAX) flush();
+            return;
+        }
+        flush();
         hipEvent_t e0 = nullptr, e1 = nullptr;
         const bool rec = h->prof && !h->dry && g.M > 0 && g.N > 0;
+        int idx = -1;
         if (rec) {
-            // launches inside an H_eff / K_eff matvec are timed per matvec
-            // (one event pair around all its launches), the others one by one
-            int idx = -1;
-            if (h->prof_timed && !h->in_heff) {
-                idx = take_events(h, 2);
+            idx = events();
+            if (idx >= 0) {
                 e0 = h->ev_pool[idx];
                 e1 = h->ev_pool[idx + 1];
             }
-            const double fl = 8.0 * g.M * g.N * (double)g.Kin * g.Kout * (double)g.B1 * g.B2 - flops_less;
-            h->prof_recs.push_back({idx, sizeof(R) == 4 ? 1 : 0, fl, h->in_heff, 0, 0,
-                                    h->in_heff ? (int)h->prof_matvecs - 1 : -1});
         }
         Gemm<R> gg = g;
         if (sizeof(R) == 4 && h->split_bf16) gg.split = 1;
         CgemmInfo info;
         if (!cgemm<R>(gg, h->gs, h->stream, why, sizeof(why), e0, e1, &info))
             throw StatusError{TTN_EINVAL, std::string("launch extent check failed: ") + why};
-        if (rec) {
-            h->prof_recs.back().kernel = info.kernel;
-            h->prof_recs.back().splits = info.splits;
-        }
+        if (rec) record(fl, info.splits, info.kernel, idx);
+    }
+};
+
+template <typename R>
+struct Group {
+    Ctx<R>& c;
+    explicit Group(Ctx<R>& ctx) : c(ctx) { ++c.depth; }
+    ~Group() {
+        if (--c.depth == 0) c.flush();
     }
 };
 
@@ -789,10 +859,13 @@ OpDesc bond_op(ttn_handle* h, int v) {
     return o;
 }
 
-// Y = H X with X in slot 0 of the stack Xs (slot stride 2n).
+// Y = H X with X in slot 0 of the stack Xs (slot stride 2n); with Y2 the
+// result is Y + Y2 (the parent-leg sum goes to Y2, so that it need not wait for
+// the right-leg sum).
 template <typename R>
 void apply_op(Ctx<R>& c, const OpDesc& o, const R* Lb, const R* Rb, const R* Bb, const R* Wb, R* Xs,
-              R* Y) {
+              R* Y, R* Y2 = nullptr) {
+    Group<R> group(c);
     const int DL = o.DL, DR = o.DR, DP = o.DP, sL = o.sL, sR = o.sR;
     const int64_t n = (int64_t)DL * DR * DP, sx = 2 * n;
     const int64_t L2 = (int64_t)DL * DL, R2 = (int64_t)DR * DR, P2 = (int64_t)DP * DP;
@@ -803,8 +876,8 @@ void apply_op(Ctx<R>& c, const OpDesc& o, const R* Lb, const R* Rb, const R* Bb,
     if (Wb && sR > 0) leg_apply<R>(c, 1, Rb + 2 * R2, 2 * R2, Xs, 0, Xs + sx * (1 + sL), sx, DL, DR, DP, sR, 0);
     // stage C: Y += H_R X + sum_i A_i U_i on the right leg
     if (Bb) leg_apply_sum<R>(c, 1, Bb, 2 * R2, Xs, sx, Y, DL, DR, DP, 1 + sL, 1);
-    // stage D: Y += H_P X + sum_i W_i U_i + sum_j W_j Z_j on the parent leg
-    if (Wb) leg_apply_sum<R>(c, 2, Wb, 2 * P2, Xs, sx, Y, DL, DR, DP, 1 + sL + sR, 1);
+    // stage D: Y (or Y2) += H_P X + sum_i W_i U_i + sum_j W_j Z_j on the parent leg
+    if (Wb) leg_apply_sum<R>(c, 2, Wb, 2 * P2, Xs, sx, Y2 ? Y2 : Y, DL, DR, DP, 1 + sL + sR, Y2 ? 0 : 1);
 }
 
 // Y = H_eff2 X for the merged tensor X[l, r, s, p] (slot 0 of the stack Xs,
@@ -814,7 +887,10 @@ void apply_op(Ctx<R>& c, const OpDesc& o, const R* Lb, const R* Rb, const R* Bb,
 // of u (leaf order: left subtree of u first) meet their tensors in order.
 // Every leg operation is a leg contraction of a three-leg view:
 // l, r on (DL, DR, DS DP); s, p on (DL DR, DS, DP).
-void apply_op2(Ctx<double>& c, const Op2& o, double* Xs, double* Y) {
+// With Y2 and Y3 the result is Y + Y2 + Y3 (the s-leg and p-leg sums apart, so
+// that they need not wait for each other).
+void apply_op2(Ctx<double>& c, const Op2& o, double* Xs, double* Y, double* Y2 = nullptr, double* Y3 = nullptr) {
+    Group<double> group(c);
     const Edge2& e = o.e;
     const int DL = e.DL, DR = e.DR, DS = e.DS, DP = e.DP, sL = e.sL, sR = e.sR, sS = e.sS;
     const int64_t sx = 2 * e.m * e.n;
@@ -824,6 +900,9 @@ void apply_op2(Ctx<double>& c, const Op2& o, double* Xs, double* Y) {
     const int oU = e.leg == 0 ? 1 : 1 + sS;
     const int oZ = oU + sL;
     const int DSP = DS * DP, DLR = DL * DR;
+    double* Ys = Y2 ? Y2 : Y;
+    double* Yp = Y3 ? Y3 : Y;
+    const int bs = Y2 ? 0 : 1, bp = Y3 ? 0 : 1;
     // l leg: Y = H_L X, U_i = N_i X
     leg_apply<double>(c, 0, o.Lb, 0, Xs, 0, Y, 0, DL, DR, DSP, 1, 0);
     leg_apply<double>(c, 0, o.Lb + 2 * L2, 2 * L2, Xs, 0, Xs + oU * sx, sx, DL, DR, DSP, sL, 0);
@@ -831,26 +910,29 @@ void apply_op2(Ctx<double>& c, const Op2& o, double* Xs, double* Y) {
     leg_apply<double>(c, 1, o.Rb + 2 * R2, 2 * R2, Xs, 0, Xs + oZ * sx, sx, DL, DR, DSP, sR, 0);
     // s leg: V_k = N_k X (they only feed the parent-leg terms)
     if (hasP) leg_apply<double>(c, 1, o.Sb + 2 * S2, 2 * S2, Xs, 0, Xs + oV * sx, sx, DLR, DS, DP, sS, 0);
-    // r leg sums: H_R X + sum_i A_i U_i
+    // r leg sums: H_R X + sum_i A_i U_i; s leg sums: H_S X + sum_{i below v}
+    // A'_i (U_i or Z_i)
     if (oU == 1) {
         leg_apply_sum<double>(c, 1, o.Bv, 2 * R2, Xs, sx, Y, DL, DR, DSP, 1 + sL, 1);
+        leg_apply_sum<double>(c, 1, o.Sa, 2 * S2, Xs, sx, Ys, DLR, DS, DP, 1 + sL + sR, bs);
     } else {
+        if (Y2) leg_apply_sum<double>(c, 1, o.Sa, 2 * S2, Xs, sx, Ys, DLR, DS, DP, 1, 0);   // beside the l leg
         leg_apply_sum<double>(c, 1, o.Bv, 2 * R2, Xs, sx, Y, DL, DR, DSP, 1, 1);
+        if (!Y2) leg_apply_sum<double>(c, 1, o.Sa, 2 * S2, Xs, sx, Y, DLR, DS, DP, 1, 1);
+        leg_apply_sum<double>(c, 1, o.Sa + 2 * S2, 2 * S2, Xs + oU * sx, sx, Ys, DLR, DS, DP, sL + sR, 1);
         leg_apply_sum<double>(c, 1, o.Bv + 2 * R2, 2 * R2, Xs + oU * sx, sx, Y, DL, DR, DSP, sL, 1);
     }
-    // s leg sums: H_S X + sum_{i below v} A'_i (U_i or Z_i)
-    if (oU == 1) {
-        leg_apply_sum<double>(c, 1, o.Sa, 2 * S2, Xs, sx, Y, DLR, DS, DP, 1 + sL + sR, 1);
-    } else {
-        leg_apply_sum<double>(c, 1, o.Sa, 2 * S2, Xs, sx, Y, DLR, DS, DP, 1, 1);
-        leg_apply_sum<double>(c, 1, o.Sa + 2 * S2, 2 * S2, Xs + oU * sx, sx, Y, DLR, DS, DP, sL + sR, 1);
-    }
     // p leg sums: H_P X + sum over every site below u of W_i on its tensor
-    if (hasP) leg_apply_sum<double>(c, 2, o.Wu, 2 * P2, Xs, sx, Y, DLR, DS, DP, 1 + sL + sR + sS, 1);
+    if (hasP) leg_apply_sum<double>(c, 2, o.Wu, 2 * P2, Xs, sx, Yp, DLR, DS, DP, 1 + sL + sR + sS, bp);
 }
+
+// Operators whose Krylov iterations run in one block between the matvecs.
+inline bool block_path(const OpDesc& o) { return (int64_t)o.DL * o.DR * o.DP <= LZ_BLOCK_N; }
+inline bool short_op(const OpDesc& o) { return (int64_t)o.DL * o.DR * o.DP <= LZ_OUT2_N; }
 
 // FP32 copies of an operator's stacks for the mixed-precision matvec
 void stage_f32(ttn_handle* h, const OpDesc& o, const int* skip) {
+    const bool fused_left = o.Wb && !short_op(o);
     const int64_t L2 = (int64_t)o.DL * o.DL, R2 = (int64_t)o.DR * o.DR, P2 = (int64_t)o.DP * o.DP;
     chk(h, o.Lb, 2 * (1 + o.sL) * L2, "L stack");
     chk(h, h->Lf, (1 + o.sL) * L2, "L stack fp32");
@@ -861,7 +943,7 @@ void stage_f32(ttn_handle* h, const OpDesc& o, const int* skip) {
         chk(h, h->Wf, (1 + o.sL + o.sR) * P2, "W stack fp32");
     }
     const int64_t wl = 2 * (1 + o.sL) * P2;   // [H_P, W_i (S_L)]
-    if (o.Wb) {
+    if (fused_left) {
         chk(h, h->Lf2, (1 + o.sL) * L2, "fused-left L stack fp32");
         chk(h, h->Wf2, (2 + o.sL + o.sR) * P2, "fused-left W stack fp32");
     }
@@ -869,12 +951,12 @@ void stage_f32(ttn_handle* h, const OpDesc& o, const int* skip) {
                       {o.Rb, h->Rf, 2 * (1 + o.sR) * R2},
                       {o.Bb, h->Bf, 2 * (1 + o.sL) * R2},
                       {o.Wb, h->Wf, 2 * (1 + o.sL + o.sR) * P2},
-                      // the fused-left matvec's stacks (nodes below the root)
-                      {o.Wb ? o.Lb + 2 * L2 : nullptr, h->Lf2, 2 * o.sL * L2},
-                      {o.Wb ? o.Lb : nullptr, h->Lf2 + 2 * o.sL * L2, 2 * L2},
-                      {o.Wb, h->Wf2, wl},
-                      {nullptr, h->Wf2 + wl, 2 * P2, o.Wb ? o.DP : 0},
-                      {o.Wb ? o.Wb + wl : nullptr, h->Wf2 + wl + 2 * P2, 2 * o.sR * P2}},
+                      // the fused-left matvec's stacks (larger nodes below the root)
+                      {fused_left ? o.Lb + 2 * L2 : nullptr, h->Lf2, 2 * o.sL * L2},
+                      {fused_left ? o.Lb : nullptr, h->Lf2 + 2 * o.sL * L2, 2 * L2},
+                      {fused_left ? o.Wb : nullptr, h->Wf2, wl},
+                      {nullptr, h->Wf2 + wl, 2 * P2, fused_left ? o.DP : 0},
+                      {fused_left ? o.Wb + wl : nullptr, h->Wf2 + wl + 2 * P2, 2 * o.sR * P2}},
                      skip, h->stream);
 }
 
@@ -903,78 +985,58 @@ void apply_op_fused_left(Ctx<float>& c, const OpDesc& o, const float* Lf2, const
     c.flops_less = 0;
 }
 
-// staged: the mixed-precision matvec whose input is already in the FP32 slot
-// (h->Xf) and whose output stays in h->Yf (the Lanczos kernels convert).
-// xS != 0: x is a slot of a chunked Krylov basis with that chunk stride.
-void apply_op_prec(ttn_handle* h, const OpDesc& o, const double* x, double* y, const int* skip,
-                   bool force_fp64 = false, bool staged = false, int64_t xS = 0) {
+// marks the contraction launches of one matvec; in a timed profiling window
+// one event pair brackets them (no events between its launches)
+struct HeffMark {
+    ttn_handle* h;
+    int idx = -1;
+    size_t first = 0;
+    explicit HeffMark(ttn_handle* hh) : h(hh) {
+        if (h->prof) h->prof_matvecs += 1;
+        if (h->prof && h->prof_timed && !h->dry) {
+            idx = take_events(h, 2);
+            first = h->prof_recs.size();
+            (void)hipEventRecord(h->ev_pool[idx], h->stream);
+        }
+        h->in_heff = true;
+    }
+    ~HeffMark() {
+        h->in_heff = false;
+        if (idx >= 0) {
+            (void)hipEventRecord(h->ev_pool[idx + 1], h->stream);
+            double fl = 0;
+            for (size_t i = first; i < h->prof_recs.size(); ++i) fl += h->prof_recs[i].flops;
+            h->mv_recs.push_back({idx, fl});
+        }
+    }
+};
+
+// H x with the input already in stack slot 0.  FP64: h->X to h->W, with out2 to
+// h->W + h->W2 (two-site: and a third output behind h->W2).  Mixed: h->Xf to
+// h->Yf, with out2 to h->Yf + h->Yf2; the Lanczos kernels widen and add.
+void apply_staged(ttn_handle* h, const OpDesc& o, bool out2, const int* skip) {
+    HeffMark mark(h);
     const int64_t n = (int64_t)o.DL * o.DR * o.DP;
-    // marks the contraction launches of one matvec; in a timed profiling
-    // window one event pair brackets them (no events between its launches)
-    struct HeffMark {
-        ttn_handle* h;
-        int idx = -1;
-        size_t first = 0;
-        explicit HeffMark(ttn_handle* hh) : h(hh) {
-            if (h->prof) h->prof_matvecs += 1;
-            if (h->prof && h->prof_timed && !h->dry) {
-                idx = take_events(h, 2);
-                first = h->prof_recs.size();
-                (void)hipEventRecord(h->ev_pool[idx], h->stream);
-            }
-            h->in_heff = true;
-        }
-        ~HeffMark() {
-            h->in_heff = false;
-            if (idx >= 0) {
-                (void)hipEventRecord(h->ev_pool[idx + 1], h->stream);
-                double fl = 0;
-                for (size_t i = first; i < h->prof_recs.size(); ++i) fl += h->prof_recs[i].flops;
-                h->mv_recs.push_back({idx, fl});
-            }
-        }
-    };
-    // the FP64 input slot: a copy of x, or its planar image when x is chunked
-    auto to_slot0 = [&]() {
-        if (xS)
-            krylov_unchunk(x, xS, n, 1, h->X, skip, h->stream);
+    if (h->prec == TTN_PREC_FP32) {
+        Ctx<float> c{h, skip};
+        if (o.Wb && !out2)
+            apply_op_fused_left(c, o, h->Lf2, h->Rf, o.Bb ? h->Bf : nullptr, h->Wf2, h->Xf, h->Yf);
         else
-            copy_d(x, h->X, 2 * n, skip, h->stream);
-    };
-    if (o.e2) {   // two-site update: FP64
-        Ctx<double> c{h, skip};
-        to_slot0();
-        HeffMark mark(h);
-        apply_op2(c, *o.e2, h->X, y);
+            apply_op<float>(c, o, h->Lf, o.Rb ? h->Rf : nullptr, o.Bb ? h->Bf : nullptr, o.Wb ? h->Wf : nullptr,
+                            h->Xf, h->Yf, out2 ? h->Yf2 : nullptr);
         return;
     }
-    if (h->prec == TTN_PREC_FP32 && !force_fp64) {
-        Ctx<float> c{h, skip};
-        if (!staged) {
-            if (xS) throw StatusError{TTN_ENOTSUP, "unstaged mixed matvec on a chunked basis slot"};
-            convert_d2f(x, h->Xf, 2 * n, skip, h->stream);
-        }
-        {
-            HeffMark mark(h);
-            if (o.Wb)
-                apply_op_fused_left(c, o, h->Lf2, h->Rf, o.Bb ? h->Bf : nullptr, h->Wf2, h->Xf, h->Yf);
-            else
-                apply_op<float>(c, o, h->Lf, o.Rb ? h->Rf : nullptr, o.Bb ? h->Bf : nullptr, nullptr, h->Xf,
-                                h->Yf);
-        }
-        if (!staged) convert_f2d(h->Yf, y, 2 * n, skip, h->stream);
-    } else {
-        Ctx<double> c{h, skip};
-        to_slot0();
-        HeffMark mark(h);
-        apply_op<double>(c, o, o.Lb, o.Rb, o.Bb, o.Wb, h->X, y);
-    }
+    Ctx<double> c{h, skip};
+    if (o.e2)   // two-site update: FP64
+        apply_op2(c, *o.e2, h->X, h->W, out2 ? h->W2 : nullptr, out2 ? h->W2 + 2 * n : nullptr);
+    else
+        apply_op<double>(c, o, o.Lb, o.Rb, o.Bb, o.Wb, h->X, h->W, out2 ? h->W2 : nullptr);
 }
 
 // chunk stride of the Krylov basis of an operator of n entries: the general
-// path stores it in chunks (0: the planar basis of the small path)
+// path stores it in chunks (0: the planar basis of the block path)
 int64_t krylov_stride(const ttn_handle* h, int64_t n) {
-    return n > LZ_SMALL_N ? 2 * (int64_t)KCH * (h->m + 1) : 0;
+    return n > LZ_BLOCK_N ? 2 * (int64_t)KCH * (h->m + 1) : 0;
 }
 
 // x <- exp(-i tau Op) x by Lanczos (full re-orthogonalisation, device scalars)
@@ -995,36 +1057,58 @@ void lanczos_basis(ttn_handle* h, const OpDesc& o, const double* x) {
         chk(h, h->Yf, n, "fp32 output");
         stage_f32(h, o, nullptr);
     }
+    const bool mixed = h->prec == TTN_PREC_FP32;
+    if (block_path(o)) {
+        // the matvec input (FP64 or FP32 stack slot 0) comes from the kernel
+        // that forms v_j, its outputs are summed where they are projected
+        double* x0 = mixed ? nullptr : h->X;
+        float* xf0 = mixed ? h->Xf : nullptr;
+        chk(h, h->W2, 2 * (o.e2 ? 2 : 1) * n, "matvec outputs");
+        if (mixed) chk(h, h->Yf2, n, "fp32 matvec output");
+        lz_start_block(x, n, h->Vk, lz, s, h->nonherm ? 1 : 0, x0, xf0);
+        for (int j = 0; j < h->m; ++j) {
+            apply_staged(h, o, true, &lz->done);
+            const bool two = o.e2 || o.Wb;
+            if (mixed)
+                lz_iter<float>(h->Vk, j, h->m, h->Yf, two ? h->Yf2 : nullptr, nullptr, n, lz, LANCZOS_TOL, x0, xf0, s);
+            else
+                lz_iter<double>(h->Vk, j, h->m, h->W, two ? h->W2 : nullptr,
+                                o.e2 && o.e2->Wu ? h->W2 + 2 * n : nullptr, n, lz, LANCZOS_TOL, x0, xf0, s);
+        }
+        return;
+    }
     // mixed precision: the Lanczos kernels write the FP32 input of the next
     // matvec and widen its FP32 output themselves
-    float* xf = (h->prec == TTN_PREC_FP32 && n > LZ_SMALL_N) ? h->Xf : nullptr;
+    float* xf = mixed ? h->Xf : nullptr;
+    double* xp = mixed ? nullptr : h->X;
+    // short operators: sums over different legs in outputs of their own
+    const bool out2 = short_op(o) && (o.e2 || o.Wb), out3 = out2 && o.e2 && o.e2->Wu;
+    if (out2) chk(h, h->W2, 2 * (o.e2 ? 2 : 1) * n, "matvec outputs");
+    if (out2 && mixed) chk(h, h->Yf2, n, "fp32 matvec output");
     // bytes per call: 16 per complex FP64 element, 8 per FP32 element
     const double E = 16.0 * (double)n, Ef = xf ? 8.0 * (double)n : 0.0;
     {
         VecTimer t(h, 3 * E + Ef, n);   // norm of x, then v0 = x / |x| (+ its FP32 copy)
-        lz_start(x, n, h->Vk, S, lz, h->red, nb, s, h->nonherm ? 1 : 0, xf);
-    }
-    if (n <= LZ_SMALL_N) {
-        for (int j = 0; j < h->m; ++j) {
-            apply_op_prec(h, o, h->Vk + 2 * n * j, h->W, &lz->done);
-            lz_iter_small(h->Vk, j, h->m, h->W, n, lz, LANCZOS_TOL, s);
-        }
-        return;
+        lz_start(x, n, h->Vk, S, lz, h->red, nb, s, h->nonherm ? 1 : 0, xf, xp);
     }
     // operators of at most LZ_FUSE_NB reduction blocks take the totals of each
     // pass inside the following kernel
     const bool fuse = nb <= LZ_FUSE_NB;
     static_assert((int64_t)RED_BLOCKS * KRYLOV_MAX * 2 >= 2 * LZ_PARTIAL_HALF, "reduction buffer too small");
     for (int j = 0; j < h->m; ++j) {
-        double* vj = h->Vk + 2 * KCH * j;
-        apply_op_prec(h, o, vj, h->W, &lz->done, false, xf != nullptr, S);
+        apply_staged(h, o, out2, &lz->done);
         // classical Gram-Schmidt, two passes: the first projection also gives alpha_j
         const bool last = j == h->m - 1;
         const double kc = j + 1;
         {
             // V^H w over j + 1 vectors; w read, or widened from the FP32 matvec output
             VecTimer t(h, kc * E + (xf ? 0.5 * E + E : E), n);
-            lz_project(h->Vk, S, j + 1, h->W, n, h->red, nb, lz, j, s, xf ? h->Yf : nullptr, last || !fuse);
+            if (mixed)
+                lz_project<float>(h->Vk, S, j + 1, h->W, n, h->red, nb, lz, j, s, h->Yf, out2 ? h->Yf2 : nullptr,
+                                  nullptr, last || !fuse);
+            else
+                lz_project<double>(h->Vk, S, j + 1, h->W, n, h->red, nb, lz, j, s, out2 ? h->W : nullptr,
+                                   out2 ? h->W2 : nullptr, out3 ? h->W2 + 2 * n : nullptr, last || !fuse);
         }
         if (last) break;
         {
@@ -1035,7 +1119,7 @@ void lanczos_basis(ttn_handle* h, const OpDesc& o, const double* x) {
             // w -= V c' with |w|^2, then v_{j+1} = w / beta_j (+ its FP32 copy)
             VecTimer t(h, kc * E + 2 * E + 2 * E + Ef, n);
             lz_subtract_next(h->Vk, S, j + 1, h->W, n, h->Vk + 2 * KCH * (j + 1), lz, j, h->red, nb, LANCZOS_TOL,
-                             s, xf, fuse);
+                             s, xf, fuse, xp);
         }
     }
 }
@@ -1070,9 +1154,8 @@ void lanczos_expm(ttn_handle* h, const OpDesc& o, double* x, double tau) {
         return;
     }
     lanczos_basis(h, o, x);
-    lz_expm(h->lz, tau, h->st, h->stream);
     VecTimer t(h, 16.0 * (double)n * (h->m + 1), n);   // x = |x| V y: m basis vectors read, x written
-    lz_combine(h->Vk, krylov_stride(h, n), n, x, h->lz, h->stream);
+    lz_expm_combine(h->Vk, krylov_stride(h, n), n, x, h->lz, {tau}, false, h->st, h->stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -1161,6 +1244,7 @@ void absorb(ttn_handle* h, int v, int leg, const double* Op, bool trans) {
 template <typename R>
 void build_up_core(Ctx<R>& c, int DL, int DR, int DP, int sL, int sR, const R* Q, const R* Lb, const R* Rb,
                    const R* Bb, R* Xs, R* Y, R* E) {
+    Group<R> group(c);
     const int64_t n = (int64_t)DL * DR * DP, sx = 2 * n;
     const int64_t L2 = (int64_t)DL * DL, R2 = (int64_t)DR * DR, P2 = (int64_t)DP * DP;
     leg_apply<R>(c, 0, Lb, 0, Q, 0, Y, 0, DL, DR, DP, 1, 0);
@@ -1181,6 +1265,7 @@ void build_up_core(Ctx<R>& c, int DL, int DR, int DP, int sL, int sR, const R* Q
 template <typename R>
 void build_down_core(Ctx<R>& c, int leg, int DL, int DR, int DP, int sL, int sR, const R* Q, const R* Lb,
                      const R* Rb, const R* Wb, const R* Ab, R* Xs, R* Y, R* E) {
+    Group<R> group(c);
     const int64_t n = (int64_t)DL * DR * DP, sx = 2 * n;
     const int64_t L2 = (int64_t)DL * DL, R2 = (int64_t)DR * DR, P2 = (int64_t)DP * DP;
     const int Dc = leg == 0 ? DL : DR;
@@ -1737,7 +1822,8 @@ void dot_c(ttn_handle* h, const double* x, const double* y, int64_t n, double ou
     chk(h, x, 2 * n, "dot x");
     chk(h, y, 2 * n, "dot y");
     h2d(h, h->lz_obs, &h->h_lzinit, sizeof(LanczosDev));
-    lz_project(x, 0, 1, y, n, h->red, nb, h->lz_obs, -1, h->stream);
+    lz_project<double>(x, 0, 1, const_cast<double*>(y), n, h->red, nb, h->lz_obs, -1, h->stream, nullptr, nullptr,
+                       nullptr, true);
     d2h(h, &h->h_lzout, h->lz_obs, sizeof(LanczosDev));
     sync(h);
     out[0] = h->h_lzout.c[0];
@@ -1750,7 +1836,8 @@ void observables(ttn_handle* h, double* norm2, double* energy) {
     const int64_t n = nsize(h, r);
     Ctx<double> c{h, nullptr};
     OpDesc o = node_op(h, c, r);
-    apply_op_prec(h, o, h->T[r], h->W, nullptr, true);
+    copy_d(h->T[r], h->X, 2 * n, nullptr, h->stream);
+    apply_op<double>(c, o, o.Lb, o.Rb, o.Bb, o.Wb, h->X, h->W);
     double a[2], b[2];
     dot_c(h, h->T[r], h->T[r], n, a);
     dot_c(h, h->T[r], h->W, n, b);

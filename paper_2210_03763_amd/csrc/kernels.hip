@@ -137,11 +137,11 @@ __global__ void k_lz_begin(const double* partial, int nb, LanczosDev* lz, int no
     }
 }
 
-// y = x / beta (FP64), and its FP32 copy yf when yf != nullptr (the input of
-// the next mixed-precision matvec); y planar (S == 0) or a slot of a chunked
+// y = x / beta (FP64), and its FP32 or planar FP64 copy yf, yp when not null
+// (the input of the next matvec); y planar (S == 0) or a slot of a chunked
 // Krylov basis with chunk stride S
 __global__ void k_scale_by(const double* x, int64_t n, double* y, int64_t S, const LanczosDev* lz, int use_beta0,
-                           int j, float* yf) {
+                           int j, float* yf, double* yp) {
     if (lz->done) return;
     const double s = 1.0 / (use_beta0 ? lz->beta0 : lz->beta[j]);
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < 2 * n;
@@ -149,6 +149,7 @@ __global__ void k_scale_by(const double* x, int64_t n, double* y, int64_t S, con
         const double v = x[i] * s;
         y[S ? kch_elem(i, n, S) : i] = v;
         if (yf) yf[i] = (float)v;
+        if (yp) yp[i] = v;
     }
 }
 
@@ -159,7 +160,7 @@ __global__ void k_scale_by(const double* x, int64_t n, double* y, int64_t S, con
 // FP32 copy yf when yf != nullptr.
 __global__ __launch_bounds__(256) void k_scale_next(const double* x, int64_t n, double* y, int64_t S,
                                                   LanczosDev* lz, const double* pnorm, int nb, int j, double tol,
-                                                  float* yf) {
+                                                  float* yf, double* yp) {
     if (lz->done) return;
     __shared__ double sh[16];
     __shared__ double s_b;
@@ -182,19 +183,45 @@ __global__ __launch_bounds__(256) void k_scale_next(const double* x, int64_t n, 
         const double v = x[i] * inv;
         y[S ? kch_elem(i, n, S) : i] = v;
         if (yf) yf[i] = (float)v;
+        if (yp) yp[i] = v;
     }
 }
 
-// partial[blk][k] = sum_i conj(V_k[i]) w[i] for k < KC (2 KC reals per
-// block); with wf != nullptr w is first widened from the FP32 matvec output
-// wf (and stored).  KC is a template argument so that the per-thread arrays
-// hold exactly the vectors in use.
-template <int KC, int W>
-__device__ inline void multidot_body(const double* V, int64_t S, const double* w, int64_t n, const float* wf,
+// The matvec outputs that a Lanczos vector w is the sum of (y[1], y[2] may be
+// null); y[0] null: w is there already.
+template <typename R>
+struct LzOut {
+    const R* y[3];
+};
+
+// w[i .. i + W) (re, im) from the matvec outputs
+template <int W, typename R, typename DV>
+__device__ inline void lz_out_load(const LzOut<R>& in, int64_t i, int64_t n, DV& wr, DV& wi) {
+    typedef R rv __attribute__((ext_vector_type(W)));
+    const rv a = *(const rv*)(in.y[0] + i), b = *(const rv*)(in.y[0] + i + n);
+#pragma unroll
+    for (int e = 0; e < W; ++e) {
+        wr[e] = (double)a[e];
+        wi[e] = (double)b[e];
+    }
+#pragma unroll
+    for (int q = 1; q < 3; ++q)
+        if (in.y[q]) {
+            const rv c = *(const rv*)(in.y[q] + i), d = *(const rv*)(in.y[q] + i + n);
+#pragma unroll
+            for (int e = 0; e < W; ++e) {
+                wr[e] += (double)c[e];
+                wi[e] += (double)d[e];
+            }
+        }
+}
+
+// re, im [k] += conj(V_k[i]) w[i] over the thread's elements, W consecutive ones
+// per step (16-byte loads for W = 2); w is first formed from `in` (and stored).
+template <int KC, int W, typename R>
+__device__ inline void multidot_body(const double* V, int64_t S, double* w, int64_t n, const LzOut<R>& in,
                                      double (&re)[KC], double (&im)[KC]) {
-    // W consecutive elements per thread and step (16-byte loads for W = 2)
     typedef double dv __attribute__((ext_vector_type(W)));
-    typedef float fv __attribute__((ext_vector_type(W)));
     const int64_t nw = n / W;
     // slot and plane strides: chunked basis (S > 0) or planar vectors (S == 0)
     const int64_t ks = S ? 2 * KCH : 2 * n, ps = S ? KCH : n;
@@ -208,15 +235,10 @@ __device__ inline void multidot_body(const double* V, int64_t S, const double* w
             vi[k] = *(const dv*)(Vi + ks * k + ps);
         }
         dv wr, wi;
-        if (wf) {
-            const fv a = *(const fv*)(wf + i), b = *(const fv*)(wf + i + n);
-#pragma unroll
-            for (int e = 0; e < W; ++e) {
-                wr[e] = (double)a[e];
-                wi[e] = (double)b[e];
-            }
-            *(dv*)(const_cast<double*>(w) + i) = wr;
-            *(dv*)(const_cast<double*>(w) + i + n) = wi;
+        if (in.y[0]) {
+            lz_out_load<W>(in, i, n, wr, wi);
+            *(dv*)(w + i) = wr;
+            *(dv*)(w + i + n) = wi;
         } else {
             wr = *(const dv*)(w + i);
             wi = *(const dv*)(w + i + n);
@@ -232,23 +254,22 @@ __device__ inline void multidot_body(const double* V, int64_t S, const double* w
 }
 
 // partial[blk][k] = sum_i conj(V_k[i]) w[i] for k < KC (2 KC reals per
-// block); with wf != nullptr w is first widened from the FP32 matvec output
-// wf (and stored).  KC is a template argument so that the per-thread arrays
-// hold exactly the vectors in use; vectors of even length are read two
-// elements at a time.
-template <int KC>
-__global__ __launch_bounds__(256) void k_multidot_partial(const double* V, int64_t S, const double* w, int64_t n,
-                                                         double* partial, const LanczosDev* lz, const float* wf) {
+// block).  KC is a template argument so that the per-thread arrays hold exactly
+// the vectors in use; vectors of even length are read two elements at a time.
+template <int KC, typename R>
+__global__ __launch_bounds__(256) void k_multidot_partial(const double* V, int64_t S, double* w, int64_t n,
+                                                         double* partial, const LanczosDev* lz, LzOut<R> in) {
     if (lz->done) return;
     constexpr int P = pow2_pairs(KC);
     __shared__ double shp[4 * P];
     double re[KC], im[KC];
 #pragma unroll
     for (int k = 0; k < KC; ++k) re[k] = im[k] = 0;
-    if (n % 2 == 0 && (((uintptr_t)V | (uintptr_t)w | (uintptr_t)wf) & 15) == 0)
-        multidot_body<KC, 2>(V, S, w, n, wf, re, im);
+    const uintptr_t al = (uintptr_t)V | (uintptr_t)w | (uintptr_t)in.y[0] | (uintptr_t)in.y[1] | (uintptr_t)in.y[2];
+    if (n % 2 == 0 && (al & 15) == 0)
+        multidot_body<KC, 2, R>(V, S, w, n, in, re, im);
     else
-        multidot_body<KC, 1>(V, S, w, n, wf, re, im);
+        multidot_body<KC, 1, R>(V, S, w, n, in, re, im);
     double a[P];
 #pragma unroll
     for (int k = 0; k < P / 2; ++k) {
@@ -433,104 +454,150 @@ __global__ __launch_bounds__(256) void k_sub_fused(const double* V, int64_t S, d
     }
 }
 
-// One whole Lanczos iteration after the matvec for short vectors (one block):
-// c = V^H w (alpha_j = Re c_j); unless j is the last index: w -= V c,
-// c' = V^H w, w -= V c', beta_j = |w| with the breakdown test, v_{j+1} = w / beta_j.
-__global__ __launch_bounds__(256) void k_lz_iter_small(double* V, int j, int m, double* w, int64_t n, LanczosDev* lz,
-                                                       double tol) {
+// One block does everything between two matvecs of an operator of n <=
+// LZ_BLOCK_N entries (the basis V planar, slot stride 2 n): w is the sum of up
+// to three matvec outputs (widened from FP32 in the mixed path), c = V^H w
+// (alpha_j = Re c_j); unless j is the last index: w -= V c, c' = V^H w, w -= V
+// c', beta_j = |w| with the breakdown test, v_{j+1} = w / beta_j, also written to
+// x, the next matvec's input.  At these sizes an iteration is bound by its
+// launches (four of 4-8 us over many blocks).  A thread owns E elements of w and
+// of every basis vector and keeps them in registers, so V is read once: reading
+// it again for every pass took 16 us at n = 1296 and eleven vectors, and at n =
+// 4096, where it does not fit, 33 us against 25 for the four launches.
+constexpr int LZB_THREADS = 512;
+static_assert(LZ_BLOCK_N <= 3 * LZB_THREADS, "at most three elements a thread");
+
+// totals of the KC complex partial sums of a block into c (LDS)
+template <int KC>
+__device__ inline void lzb_totals(const double (&re)[KC], const double (&im)[KC], double* sh, double* c) {
+    constexpr int P = pow2_pairs(KC);
+    double a[P];
+#pragma unroll
+    for (int k = 0; k < P / 2; ++k) {
+        a[2 * k] = k < KC ? re[k] : 0.0;
+        a[2 * k + 1] = k < KC ? im[k] : 0.0;
+    }
+    const double t = block_sum_p<P>(a, sh);
+    if (threadIdx.x < 2 * KC) c[threadIdx.x] = t;
+    __syncthreads();
+}
+
+template <int KC, int E, typename R>
+__global__ __launch_bounds__(LZB_THREADS) void k_lz_iter(double* V, int m, LzOut<R> in, int n, LanczosDev* lz,
+                                                        double tol, double* x, float* xf) {
     if (lz->done) return;
-    __shared__ double sh32[4 * 32];
-    __shared__ double c[32];
-    __shared__ double s_beta;
-    __shared__ int s_stop;
-    const int kc = j + 1;
-    double a[32];
+    constexpr int j = KC - 1;
+    __shared__ double sh[(LZB_THREADS / 64) * pow2_pairs(KC)];
+    __shared__ double sh1[LZB_THREADS / 64 + 1];
+    __shared__ double c[2 * KRYLOV_MAX];
+    // element e of the thread: tid + LZB_THREADS e (zero past the end)
+    double vr[KC][E], vi[KC][E], wr[E], wi[E];
 #pragma unroll
-    for (int k = 0; k < 32; ++k) a[k] = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-        const double wr = w[i], wi = w[i + n];
+    for (int e = 0; e < E; ++e) {
+        const int i = threadIdx.x + LZB_THREADS * e;
+        const bool ok = i < n;
+        wr[e] = wi[e] = 0.0;
 #pragma unroll
-        for (int k = 0; k < KRYLOV_MAX; ++k)
-            if (k < kc) {
-                const double vr = V[2 * n * k + i], vi = V[2 * n * k + n + i];
-                a[2 * k] += vr * wr + vi * wi;
-                a[2 * k + 1] += vr * wi - vi * wr;
+        for (int k = 0; k < KC; ++k) {
+            vr[k][e] = ok ? V[2 * n * k + i] : 0.0;
+            vi[k][e] = ok ? V[2 * n * k + n + i] : 0.0;
+        }
+        if (ok) {
+            wr[e] = (double)in.y[0][i];
+            wi[e] = (double)in.y[0][n + i];
+#pragma unroll
+            for (int q = 1; q < 3; ++q)
+                if (in.y[q]) {
+                    wr[e] += (double)in.y[q][i];
+                    wi[e] += (double)in.y[q][n + i];
+                }
+        }
+    }
+    auto project = [&]() {
+        double re[KC], im[KC];
+#pragma unroll
+        for (int k = 0; k < KC; ++k) {
+            re[k] = im[k] = 0.0;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                re[k] += vr[k][e] * wr[e] + vi[k][e] * wi[e];
+                im[k] += vr[k][e] * wi[e] - vi[k][e] * wr[e];
             }
-    }
-    double t = block_sum32(a, sh32);
-    if (threadIdx.x < 32) c[threadIdx.x] = t;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        lz->alpha[j] = c[2 * j];
-        lz->m_eff = j + 1;
-    }
-    const int nonherm = lz->nonherm;
-    if (nonherm && threadIdx.x < 2 * kc) lz->hs[2 * j * KRYLOV_MAX + threadIdx.x] = c[threadIdx.x];
+        }
+        lzb_totals<KC>(re, im, sh, c);
+    };
+    auto subtract = [&]() {
+#pragma unroll
+        for (int k = 0; k < KC; ++k) {
+            const double cr = c[2 * k], ci = c[2 * k + 1];
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                wr[e] -= cr * vr[k][e] - ci * vi[k][e];
+                wi[e] -= cr * vi[k][e] + ci * vr[k][e];
+            }
+        }
+    };
+    project();
+    if (threadIdx.x < KC) lz_record_projection(lz, c, KC, j, threadIdx.x);
     if (j == m - 1) return;
-    // subtract, second projection
+    subtract();
+    __syncthreads();   // c is read before the second totals replace it
+    project();
+    if (threadIdx.x < KC && lz->nonherm) lz_record_projection(lz, c, KC, -1, threadIdx.x);
+    subtract();
+    double nrm = 0.0;
 #pragma unroll
-    for (int k = 0; k < 32; ++k) a[k] = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-        double wr = w[i], wi = w[i + n];
-        double vr[KRYLOV_MAX], vi[KRYLOV_MAX];
-#pragma unroll
-        for (int k = 0; k < KRYLOV_MAX; ++k)
-            if (k < kc) {
-                vr[k] = V[2 * n * k + i];
-                vi[k] = V[2 * n * k + n + i];
-                wr -= c[2 * k] * vr[k] - c[2 * k + 1] * vi[k];
-                wi -= c[2 * k] * vi[k] + c[2 * k + 1] * vr[k];
-            }
-        w[i] = wr;
-        w[i + n] = wi;
-#pragma unroll
-        for (int k = 0; k < KRYLOV_MAX; ++k)
-            if (k < kc) {
-                a[2 * k] += vr[k] * wr + vi[k] * wi;
-                a[2 * k + 1] += vr[k] * wi - vi[k] * wr;
-            }
-    }
-    t = block_sum32(a, sh32);
-    __syncthreads();
-    if (threadIdx.x < 32) c[threadIdx.x] = t;
-    if (nonherm && threadIdx.x < 2 * kc) lz->hs[2 * j * KRYLOV_MAX + threadIdx.x] += t;
-    __syncthreads();
-    // subtract again, norm
-    double nrm[32];
-#pragma unroll
-    for (int k = 0; k < 32; ++k) nrm[k] = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-        double wr = w[i], wi = w[i + n];
-#pragma unroll
-        for (int k = 0; k < KRYLOV_MAX; ++k)
-            if (k < kc) {
-                const double vr = V[2 * n * k + i], vi = V[2 * n * k + n + i];
-                wr -= c[2 * k] * vr - c[2 * k + 1] * vi;
-                wi -= c[2 * k] * vi + c[2 * k + 1] * vr;
-            }
-        w[i] = wr;
-        w[i + n] = wi;
-        nrm[0] += wr * wr + wi * wi;
-    }
-    t = block_sum32(nrm, sh32);
+    for (int e = 0; e < E; ++e) nrm += wr[e] * wr[e] + wi[e] * wi[e];
+    const double b = sqrt(block_sum_all(nrm, sh1));
+    const double bprev = j > 0 ? lz->beta[j > 0 ? j - 1 : 0] : 0.0;
+    const bool stop = !(b > tol * (fabs(lz->alpha[j]) + bprev));
     if (threadIdx.x == 0) {
-        const double b = sqrt(t);
-        const double bprev = j > 0 ? lz->beta[j - 1] : 0.0;
-        const bool stop = !(b > tol * (fabs(lz->alpha[j]) + bprev));
         if (stop)
             lz->done = 1;
         else
             lz->beta[j] = b;
-        s_stop = stop;
-        s_beta = b;
     }
-    __syncthreads();
-    if (s_stop) return;
-    const double inv = 1.0 / s_beta;
-    double* vn = V + 2 * n * (j + 1);
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-        vn[i] = w[i] * inv;
-        vn[i + n] = w[i + n] * inv;
+    if (stop) return;
+    const double inv = 1.0 / b;
+    double* vn = V + 2 * n * KC;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int i = threadIdx.x + LZB_THREADS * e;
+        if (i >= n) continue;
+        const double r = wr[e] * inv, q = wi[e] * inv;
+        vn[i] = r;
+        vn[n + i] = q;
+        if (x) {
+            x[i] = r;
+            x[n + i] = q;
+        }
+        if (xf) {
+            xf[i] = (float)r;
+            xf[n + i] = (float)q;
+        }
+    }
+}
+
+// v_0 = x / |x| for the same operators, with its copies for the first matvec
+__global__ __launch_bounds__(LZB_THREADS) void k_lz_begin_block(const double* x, int n, double* v0, LanczosDev* lz,
+                                                               int nonherm, double* x0, float* xf) {
+    __shared__ double sh[LZB_THREADS / 64 + 1];
+    double acc = 0.0;
+    for (int i = threadIdx.x; i < 2 * n; i += LZB_THREADS) acc += x[i] * x[i];
+    const double t = block_sum_all(acc, sh);
+    if (threadIdx.x == 0) {
+        lz->beta0 = sqrt(t);
+        lz->zero = lz->done = t == 0.0 ? 1 : 0;
+        lz->m_eff = 0;
+        lz->nonherm = nonherm;
+    }
+    if (t == 0.0) return;
+    const double s = 1.0 / sqrt(t);
+    for (int i = threadIdx.x; i < 2 * n; i += LZB_THREADS) {
+        const double v = x[i] * s;
+        v0[i] = v;
+        if (x0) x0[i] = v;
+        if (xf) xf[i] = (float)v;
     }
 }
 
@@ -589,7 +656,8 @@ __device__ inline double wave_max(double v) {
     return v;
 }
 
-__device__ __forceinline__ void lz_expm_hessenberg(LanczosDev* lz, double tau, StepDev* st) {
+// y: 2 KRYLOV_MAX doubles in LDS
+__device__ __forceinline__ void lz_expm_hessenberg(const LanczosDev* lz, double tau, double* y, StepDev* st) {
     constexpr int KM = KRYLOV_MAX;
     const int t = threadIdx.x;
     if (t < 64) {
@@ -660,17 +728,12 @@ __device__ __forceinline__ void lz_expm_hessenberg(LanczosDev* lz, double tau, S
             vi = wi;
         }
         if (t < KM) {
-            lz->y[2 * t] = t < m ? vr : 0.0;
-            lz->y[2 * t + 1] = t < m ? vi : 0.0;
+            y[2 * t] = t < m ? vr : 0.0;
+            y[2 * t + 1] = t < m ? vi : 0.0;
         }
-        if (t == 0) atomicMin(&st->min_krylov, m);
+        if (t == 0 && st) atomicMin(&st->min_krylov, m);
     }
     __syncthreads();
-}
-
-__global__ void k_lz_expm(LanczosDev* lz, double tau, StepDev* st) {
-    if (lz->zero) return;
-    lz_expm_hessenberg(lz, tau, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -912,13 +975,12 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_evolve(const double* gL
         __syncthreads();
     }
     // y = exp(-i tau H_m) e_1, then x = beta0 sum_k y_k v_k
-    lz_expm_hessenberg(&lz, tau, st);
-    __syncthreads();
+    lz_expm_hessenberg(&lz, tau, c, st);
     const int me = lz.m_eff;
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         double re = 0, im = 0;
         for (int k = 0; k < me; ++k) {
-            const double yr = lz.y[2 * k] * lz.beta0, yi = lz.y[2 * k + 1] * lz.beta0;
+            const double yr = c[2 * k] * lz.beta0, yi = c[2 * k + 1] * lz.beta0;
             const double vr = V[2 * n * k + i], vi = V[2 * n * k + n + i];
             re += yr * vr - yi * vi;
             im += yr * vi + yi * vr;
@@ -939,12 +1001,28 @@ __global__ void k_unchunk(const double* V, int64_t S, int64_t n, int slots, doub
     }
 }
 
-// out = beta0 sum_k y_k v_k; V planar (S == 0, slot stride 2 n) or chunked
-__global__ void k_lz_combine(const double* V, int64_t S, int64_t n, double* out, const LanczosDev* lz) {
-    if (lz->zero) return;
+// out_q = beta0 sum_k y_k v_k, y = exp(-i tau_q H_m) e_1, for q = blockIdx.y (outputs
+// 2 n apart); V planar (S == 0, slot stride 2 n) or chunked.  Every block forms
+// the small exponential itself (one wave, the same numbers in every block),
+// which takes as long as a launch of its own would.  A zero vector stays as it
+// is in out, or (fill) its image is written.
+struct LzTaus {
+    double t[LZ_TAUS];
+};
+__global__ __launch_bounds__(256) void k_lz_combine(const double* V, int64_t S, int64_t n, double* out0,
+                                                   const LanczosDev* lz, LzTaus taus, int fill, StepDev* st) {
+    double* out = out0 + 2 * n * blockIdx.y;
+    if (lz->zero) {
+        if (fill)
+            for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < 2 * n;
+                 i += (int64_t)gridDim.x * blockDim.x)
+                out[i] = 0.0;
+        return;
+    }
     __shared__ double y[2 * KRYLOV_MAX];
     const int m = lz->m_eff;
-    if (threadIdx.x < 2 * KRYLOV_MAX) y[threadIdx.x] = lz->y[threadIdx.x] * lz->beta0;
+    lz_expm_hessenberg(lz, taus.t[blockIdx.y], y, blockIdx.x == 0 ? st : nullptr);
+    if (threadIdx.x < 2 * KRYLOV_MAX) y[threadIdx.x] *= lz->beta0;
     __syncthreads();
     if (n % 2 == 0 && (((uintptr_t)V | (uintptr_t)out) & 15) == 0) {   // two elements per step, 16-byte loads
         typedef double d2 __attribute__((ext_vector_type(2)));
@@ -989,12 +1067,12 @@ inline int grid_for(int64_t n) {
 }  // namespace
 
 void lz_start(const double* x, int64_t n, double* v0, int64_t S, LanczosDev* lz, double* partial, int nb,
-              hipStream_t s, int nonherm, float* v0f) {
+              hipStream_t s, int nonherm, float* v0f, double* v0p) {
     if (g_dry_run) return;
     hipLaunchKernelGGL(k_norm2_partial, dim3(nb), dim3(RED_THREADS), 0, s, x, n, partial,
                        (const int*)nullptr);
     hipLaunchKernelGGL(k_lz_begin, dim3(1), dim3(64), 0, s, partial, nb, lz, nonherm);
-    hipLaunchKernelGGL(k_scale_by, dim3(grid_for(2 * n)), dim3(256), 0, s, x, n, v0, S, lz, 1, 0, v0f);
+    hipLaunchKernelGGL(k_scale_by, dim3(grid_for(2 * n)), dim3(256), 0, s, x, n, v0, S, lz, 1, 0, v0f, v0p);
 }
 
 // Instantiates a launch for every basis size 1 .. KRYLOV_MAX.
@@ -1022,16 +1100,22 @@ void lz_start(const double* x, int64_t n, double* v0, int64_t S, LanczosDev* lz,
     } while (0)
 static_assert(KRYLOV_MAX == 16, "TTN_KC_DISPATCH covers basis sizes up to 16");
 
-void lz_project(const double* V, int64_t S, int kcount, const double* w, int64_t n, double* partial, int nb,
-                LanczosDev* lz, int alpha_index, hipStream_t s, const float* wf, bool total) {
+template <typename R>
+void lz_project(const double* V, int64_t S, int kcount, double* w, int64_t n, double* partial, int nb, LanczosDev* lz,
+                int alpha_index, hipStream_t s, const R* y0, const R* y1, const R* y2, bool total) {
     if (g_dry_run) return;
+    const LzOut<R> in{{y0, y1, y2}};
 #define TTN_L(KC) \
-    hipLaunchKernelGGL(k_multidot_partial<KC>, dim3(nb), dim3(RED_THREADS), 0, s, V, S, w, n, partial, lz, wf)
+    hipLaunchKernelGGL((k_multidot_partial<KC, R>), dim3(nb), dim3(RED_THREADS), 0, s, V, S, w, n, partial, lz, in)
     TTN_KC_DISPATCH(kcount, TTN_L);
 #undef TTN_L
     if (total)
         hipLaunchKernelGGL(k_multidot_final, dim3(1), dim3(1024), 0, s, partial, nb, kcount, lz, alpha_index);
 }
+template void lz_project<double>(const double*, int64_t, int, double*, int64_t, double*, int, LanczosDev*, int,
+                                 hipStream_t, const double*, const double*, const double*, bool);
+template void lz_project<float>(const double*, int64_t, int, double*, int64_t, double*, int, LanczosDev*, int,
+                                hipStream_t, const float*, const float*, const float*, bool);
 
 // With fuse (nb <= LZ_FUSE_NB) the totals of the first pass are taken inside
 // k_sub_fused<1> from the partials lz_project left at `partial`, and its own
@@ -1058,7 +1142,8 @@ void lz_subtract_project(const double* V, int64_t S, int kcount, double* w, int6
 // With fuse the second pass's totals are taken inside k_sub_fused<2> from
 // partial + LZ_PARTIAL_HALF, and beta_j inside the scaling kernel.
 void lz_subtract_next(const double* V, int64_t S, int kcount, double* w, int64_t n, double* vnext, LanczosDev* lz,
-                      int j, double* partial, int nb, double tol, hipStream_t s, float* vnextf, bool fuse) {
+                      int j, double* partial, int nb, double tol, hipStream_t s, float* vnextf, bool fuse,
+                      double* vnextp) {
     if (g_dry_run) return;
     if (fuse) {
 #define TTN_L(KC)                                                                                              \
@@ -1067,7 +1152,7 @@ void lz_subtract_next(const double* V, int64_t S, int kcount, double* w, int64_t
         TTN_KC_DISPATCH(kcount, TTN_L);
 #undef TTN_L
         hipLaunchKernelGGL(k_scale_next, dim3(grid_for(2 * n)), dim3(256), 0, s, w, n, vnext, S, lz,
-                           (const double*)partial, nb, j, tol, vnextf);
+                           (const double*)partial, nb, j, tol, vnextf, vnextp);
         return;
     }
 #define TTN_L(KC)                                                                                         \
@@ -1076,18 +1161,37 @@ void lz_subtract_next(const double* V, int64_t S, int kcount, double* w, int64_t
     TTN_KC_DISPATCH(kcount, TTN_L);
 #undef TTN_L
     hipLaunchKernelGGL(k_lz_beta, dim3(1), dim3(256), 0, s, partial, nb, lz, j, tol);
-    hipLaunchKernelGGL(k_scale_by, dim3(grid_for(2 * n)), dim3(256), 0, s, w, n, vnext, S, lz, 0, j, vnextf);
+    hipLaunchKernelGGL(k_scale_by, dim3(grid_for(2 * n)), dim3(256), 0, s, w, n, vnext, S, lz, 0, j, vnextf, vnextp);
 }
 
-void lz_iter_small(double* V, int j, int m, double* w, int64_t n, LanczosDev* lz, double tol, hipStream_t s) {
+void lz_start_block(const double* x, int64_t n, double* v0, LanczosDev* lz, hipStream_t s, int nonherm, double* x0,
+                    float* xf) {
     if (g_dry_run) return;
-    hipLaunchKernelGGL(k_lz_iter_small, dim3(1), dim3(256), 0, s, V, j, m, w, n, lz, tol);
+    hipLaunchKernelGGL(k_lz_begin_block, dim3(1), dim3(LZB_THREADS), 0, s, x, (int)n, v0, lz, nonherm, x0, xf);
 }
 
-void lz_expm(LanczosDev* lz, double tau, StepDev* st, hipStream_t s) {
+template <typename R>
+void lz_iter(double* V, int j, int m, const R* y0, const R* y1, const R* y2, int64_t n, LanczosDev* lz, double tol,
+             double* x, float* xf, hipStream_t s) {
     if (g_dry_run) return;
-    hipLaunchKernelGGL(k_lz_expm, dim3(1), dim3(64), 0, s, lz, tau, st);
+    const LzOut<R> in{{y0, y1, y2}};
+#define TTN_LE(KC, E)                                                                                               \
+    hipLaunchKernelGGL((k_lz_iter<KC, E, R>), dim3(1), dim3(LZB_THREADS), 0, s, V, m, in, (int)n, lz, tol, x, xf)
+#define TTN_L(KC)                      \
+    if (n <= LZB_THREADS)              \
+        TTN_LE(KC, 1);                 \
+    else if (n <= 2 * LZB_THREADS)     \
+        TTN_LE(KC, 2);                 \
+    else                               \
+        TTN_LE(KC, 3)
+    TTN_KC_DISPATCH(j + 1, TTN_L);
+#undef TTN_L
+#undef TTN_LE
 }
+template void lz_iter<double>(double*, int, int, const double*, const double*, const double*, int64_t, LanczosDev*,
+                              double, double*, float*, hipStream_t);
+template void lz_iter<float>(double*, int, int, const float*, const float*, const float*, int64_t, LanczosDev*,
+                             double, double*, float*, hipStream_t);
 
 int64_t small_evolve_doubles(int DL, int DR, int DP, int sL, int sR, int m, bool hasB, bool hasW) {
     const int64_t n = (int64_t)DL * DR * DP;
@@ -1105,9 +1209,13 @@ void small_evolve(const double* L, const double* R, const double* B, const doubl
                        tol, nonherm ? 1 : 0, x, st);
 }
 
-void lz_combine(const double* V, int64_t S, int64_t n, double* out, LanczosDev* lz, hipStream_t s) {
-    if (g_dry_run) return;
-    hipLaunchKernelGGL(k_lz_combine, dim3(grid_for(n)), dim3(256), 0, s, V, S, n, out, lz);
+void lz_expm_combine(const double* V, int64_t S, int64_t n, double* out, const LanczosDev* lz,
+                     std::initializer_list<double> taus, bool fill, StepDev* st, hipStream_t s) {
+    if (g_dry_run || taus.size() == 0) return;
+    LzTaus t{};
+    int k = 0;
+    for (double x : taus) t.t[k++] = x;
+    hipLaunchKernelGGL(k_lz_combine, dim3(grid_for(n), k), dim3(256), 0, s, V, S, n, out, lz, t, fill ? 1 : 0, st);
 }
 
 void krylov_unchunk(const double* V, int64_t S, int64_t n, int slots, double* out, const int* skip, hipStream_t s) {

@@ -68,6 +68,20 @@ template <typename R>
 bool cgemm(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, char* why, int whylen,
            hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr, CgemmInfo* info = nullptr);
 
+// The extent check of cgemm alone.
+template <typename R>
+bool cgemm_check(const Gemm<R>& g, const GemmScratch& ws, char* why, int whylen);
+
+// Independent short contractions (cgemm_groupable: those that cgemm would give
+// to the wave-sliced kernel without split K) in one launch, for sequences
+// whose cost is their launches.  The caller has checked their extents and that
+// none reads or writes what another writes.  Returns the launches made.
+constexpr int GROUP_MAX = 6;
+template <typename R>
+bool cgemm_groupable(const Gemm<R>& g, const GemmScratch& ws);
+template <typename R>
+int cgemm_group(const Gemm<R>* g, int count, const GemmScratch& ws, hipStream_t s);
+
 // When set, launchers validate but enqueue nothing (plan checking without a
 // device).
 extern bool g_dry_run;
@@ -78,7 +92,6 @@ struct LanczosDev {
     double alpha[KRYLOV_MAX];
     double beta[KRYLOV_MAX];
     double c[2 * KRYLOV_MAX];
-    double y[2 * KRYLOV_MAX];
     int m_eff;
     int done;
     int zero;
@@ -118,34 +131,47 @@ void krylov_unchunk(const double* V, int64_t S, int64_t n, int slots, double* ou
 // nonherm != 0 starts an Arnoldi basis (non-Hermitian operator): the
 // projections of both Gram-Schmidt passes are kept as Hessenberg columns and
 // lz_expm exponentiates the Hessenberg matrix instead of the tridiagonal one
-// v0f != nullptr also receives v0 in FP32 (the next mixed matvec's input)
+// v0f, v0p != nullptr also receive v0 in FP32 or planar FP64 (the next matvec's input)
 // v0 planar (S == 0) or slot 0 of a chunked basis
 void lz_start(const double* x, int64_t n, double* v0, int64_t S, LanczosDev* lz, double* partial, int nb,
-              hipStream_t s, int nonherm = 0, float* v0f = nullptr);
+              hipStream_t s, int nonherm = 0, float* v0f = nullptr, double* v0p = nullptr);
 // Reductions over at most LZ_FUSE_NB blocks may take their totals inside the
 // next kernel of the iteration (every block sums the block partials itself),
 // which saves the one-block total kernels; their partials alternate between
 // `partial` and partial + LZ_PARTIAL_HALF (the reduction buffer holds both).
 constexpr int LZ_FUSE_NB = 256;
 constexpr int64_t LZ_PARTIAL_HALF = (int64_t)LZ_FUSE_NB * 2 * KRYLOV_MAX;
-// wf != nullptr: w is first written from the FP32 matvec output wf (widened);
-// total = false leaves the projections as block partials for a fused
-// lz_subtract_project
+// c = V^H w; y0 != nullptr: w is first written as the sum of the matvec outputs
+// y0, y1, y2 (y1, y2 may be null; y0 may be w itself).  total = false leaves the
+// projections as block partials for a fused lz_subtract_project.
 // V: chunked basis (chunk stride S) or planar vectors (S == 0); vnext: a slot of V
-void lz_project(const double* V, int64_t S, int kcount, const double* w, int64_t n, double* partial, int nb,
-                LanczosDev* lz, int alpha_index, hipStream_t s, const float* wf = nullptr, bool total = true);
+template <typename R>
+void lz_project(const double* V, int64_t S, int kcount, double* w, int64_t n, double* partial, int nb, LanczosDev* lz,
+                int alpha_index, hipStream_t s, const R* y0, const R* y1, const R* y2, bool total);
 // w -= V c, then c <- V^H w (second Gram-Schmidt pass), fused
 void lz_subtract_project(const double* V, int64_t S, int kcount, double* w, int64_t n, double* partial, int nb,
                          LanczosDev* lz, hipStream_t s, bool fuse = false);
 // w -= V c, then beta_j = ||w||, breakdown test, v_{j+1} = w / beta_j
 void lz_subtract_next(const double* V, int64_t S, int kcount, double* w, int64_t n, double* vnext, LanczosDev* lz,
                       int j, double* partial, int nb, double tol, hipStream_t s, float* vnextf = nullptr,
-                      bool fuse = false);
-// a whole iteration after the matvec (projection, two Gram-Schmidt passes,
-// beta_j and breakdown, v_{j+1}) in one block, for n <= LZ_SMALL_N
-constexpr int64_t LZ_SMALL_N = 1024;
-void lz_iter_small(double* V, int j, int m, double* w, int64_t n, LanczosDev* lz, double tol, hipStream_t s);
-void lz_expm(LanczosDev* lz, double tau, StepDev* st, hipStream_t s);
+                      bool fuse = false, double* vnextp = nullptr);
+// Operators of at most LZ_BLOCK_N entries keep a planar basis and run the
+// whole iteration between two matvecs (projection, two Gram-Schmidt passes,
+// beta_j and breakdown, v_{j+1}) in one block.  The matvec output is y0 + y1 + y2
+// (y1, y2 may be null); x / xf (may be null): v_{j+1} for the next matvec, in
+// FP64 / FP32.
+constexpr int64_t LZ_BLOCK_N = 1536;
+void lz_start_block(const double* x, int64_t n, double* v0, LanczosDev* lz, hipStream_t s, int nonherm, double* x0,
+                    float* xf);
+template <typename R>
+void lz_iter(double* V, int j, int m, const R* y0, const R* y1, const R* y2, int64_t n, LanczosDev* lz, double tol,
+             double* x, float* xf, hipStream_t s);
+// out_q = |x| V exp(-i tau_q H_m) e_1 for every tau (outputs 2 n apart, at most
+// LZ_TAUS); V planar (S == 0) or chunked with stride S; fill: x = 0 writes zeros
+// (else out is left alone)
+constexpr int LZ_TAUS = 8;
+void lz_expm_combine(const double* V, int64_t S, int64_t n, double* out, const LanczosDev* lz,
+                     std::initializer_list<double> taus, bool fill, StepDev* st, hipStream_t s);
 // x <- exp(-i tau Op) x in one workgroup for small operators (the four
 // matvec stages, Krylov recursion with two Gram-Schmidt passes, exponential
 // and recombination, all in LDS, FP64): usable when n = DL DR DP <=
@@ -159,8 +185,6 @@ int64_t small_evolve_doubles(int DL, int DR, int DP, int sL, int sR, int m, bool
 void small_evolve(const double* L, const double* R, const double* B, const double* W, int DL, int DR, int DP,
                   int sL, int sR, int m, double tau, double tol, bool nonherm, double* x, StepDev* st,
                   hipStream_t s);
-// V planar (S == 0, the small path) or chunked with stride S
-void lz_combine(const double* V, int64_t S, int64_t n, double* out, LanczosDev* lz, hipStream_t s);
 
 // conversions and copies
 void convert_d2f(const double* x, float* y, int64_t count, const int* skip, hipStream_t s);
