@@ -136,6 +136,14 @@ void splitk_reduce(const Gemm<R>& g, int splits, const R* partial, hipStream_t s
     hipLaunchKernelGGL((k_splitk_reduce<R>), dim3(nb), dim3(256), 0, s, g, splits, partial, G);
 }
 
+// Consecutive workgroups go to the eight XCDs in turn, each with an L2 of its
+// own: block b of n works on tile xcd_order(b, n), which gives every XCD one
+// contiguous range of tiles (each of 0 .. n - 1 once).
+__device__ inline unsigned xcd_order(unsigned b, unsigned n) {
+    const unsigned x = b % 8, q = n / 8, r = n % 8;
+    return x * q + min(x, r) + b / 8;
+}
+
 // ---------------------------------------------------------------------------
 // MFMA contraction kernel (gfx950).  Complex C = A B with three real
 // products per complex product (Gauss): P1 = Ar Br, P2 = Ai Bi,
@@ -179,11 +187,15 @@ struct MfmaT<double> {
 // flattened over (k_in, k_out), each element stepping its own address, loads
 // past K give zero, and the complex product takes four real products (no
 // Re + Im sums), as accurate as a plain FMA loop.
-template <typename R, int BM, int BN, int WGM, int WGN, int MINB, int BK, bool AK, bool BKF, bool RAG = false>
-__global__ __launch_bounds__(64 * WGM * WGN, MINB) void k_cgemm_mfma(Gemm<R> g, int tilesM, int tilesN,
-                                                                    int splits, int kchunk, R* partial) {
+//   WGK > 1: the block is WGK groups of WGM x WGN waves on the same tile; group
+// q takes every WGK-th k-tile from tile q, through LDS buffers of its own,
+// and the groups' sums meet in LDS once, in group order.
+template <typename R, int BM, int BN, int WGM, int WGN, int WGK, int MINB, int BK, bool AK, bool BKF, bool RAG = false>
+__global__ __launch_bounds__(64 * WGM * WGN * WGK, MINB) void k_cgemm_mfma(Gemm<R> g, int tilesM, int tilesN,
+                                                                          int splits, int kchunk, R* partial) {
     if (g.skip && *g.skip) return;
-    constexpr int NT = 64 * WGM * WGN;
+    constexpr int NT = 64 * WGM * WGN;   // threads of a group
+    static_assert(WGK == 1 || !RAG, "K groups are for the aligned form");
     constexpr int WM = BM / WGM, WN = BN / WGN;
     constexpr int TI = WM / 16, TJ = WN / 16;
     static_assert(TI >= 1 && TJ >= 1, "wave tile below 16 x 16");
@@ -198,9 +210,13 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void k_cgemm_mfma(Gemm<R> g, 
     constexpr int KS = BK + 1;
     constexpr int AR = AK ? BM : BK, AC = AK ? KS : BM + PAD;
     constexpr int BR = BKF ? BN : BK, BC = BKF ? KS : BN + PAD;
-    __shared__ R As[2][2][AR][AC];
-    __shared__ R Bs[2][2][BR][BC];
-    int64_t bid = blockIdx.x;
+    constexpr int ASZ = 4 * AR * AC, BSZ = 4 * BR * BC;
+    static_assert(WGK == 1 || WGK * (ASZ + BSZ) >= 2 * WGK * 4 * TI * TJ * NT, "sums of the groups in LDS");
+    __shared__ R lds[WGK * (ASZ + BSZ)];
+    const int kg = WGK == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
+    R(*As)[2][AR][AC] = reinterpret_cast<R(*)[2][AR][AC]>(lds + kg * ASZ);
+    R(*Bs)[2][BR][BC] = reinterpret_cast<R(*)[2][BR][BC]>(lds + WGK * ASZ + kg * BSZ);
+    int64_t bid = xcd_order(blockIdx.x, gridDim.x);
     const int tm = bid % tilesM;
     bid /= tilesM;
     const int tn = bid % tilesN;
@@ -213,9 +229,9 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void k_cgemm_mfma(Gemm<R> g, 
     const R* A = g.A + b1 * g.sab1 + b2 * g.sab2 + (int64_t)m0 * g.sam;
     const R* B = g.B + b1 * g.sbb1 + b2 * g.sbb2 + (int64_t)n0 * g.sbn;
     const int K = g.Kin * g.Kout;
-    const int kb = sp * kchunk;
-    const int ke = min(K, kb + kchunk);
-    const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
+    const int ke = min(K, (sp + 1) * kchunk);
+    const int kb = sp * kchunk + kg * BK;
+    const int tid = WGK == 1 ? threadIdx.x : threadIdx.x % NT, lane = tid % 64, wave = tid / 64;
     const int wm0 = (wave % WGM) * WM, wn0 = (wave / WGM) * WN;
     const R sa = g.conjA ? R(-1) : R(1), sb = g.conjB ? R(-1) : R(1);
     const int mlim = g.M - m0, nlim = g.N - n0;
@@ -323,15 +339,20 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void k_cgemm_mfma(Gemm<R> g, 
             c2[i][j] = acc_t{0, 0, 0, 0};
             c3[i][j] = acc_t{0, 0, 0, 0};
         }
-    const int nt = RAG ? (ke - kb + BK - 1) / BK : (ke - kb) / BK;
+    // k-tiles of this group, and of the first one, which has the most: every
+    // wave takes part in each round's barrier
+    constexpr int KSTEP = BK * WGK;
+    const int nt = max(0, (ke - kb + KSTEP - 1) / KSTEP);
+    const int rounds = WGK == 1 ? nt : (ke - sp * kchunk + KSTEP - 1) / KSTEP;
     if (nt > 0) {
         fetch(kb);
         stash(0);
-        if (nt > 1) fetch(kb + BK);
+        if (nt > 1) fetch(kb + KSTEP);
     }
     __syncthreads();
-    for (int t = 0; t < nt; ++t) {
+    for (int t = 0; t < rounds; ++t) {
         const int cur = t & 1;
+        if (WGK == 1 || t < nt)
 #pragma unroll
         for (int kk = 0; kk < BK; kk += 4) {
             const int kr = kk + lane / 16, c16 = lane % 16;
@@ -375,8 +396,23 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void k_cgemm_mfma(Gemm<R> g, 
         }
         if (t + 1 < nt) {
             stash(cur ^ 1);
-            if (t + 2 < nt) fetch(kb + (t + 2) * BK);
+            if (t + 2 < nt) fetch(kb + (t + 2) * KSTEP);
         }
+        __syncthreads();
+    }
+    // sums of the groups, [group][plane][register][thread]
+    constexpr int REGS = 4 * TI * TJ;
+    if constexpr (WGK > 1) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    R* dst = lds + ((2 * kg) * REGS + 4 * (i * TJ + j) + r) * NT + tid;
+                    dst[0] = c1[i][j][r] - c2[i][j][r];
+                    dst[REGS * NT] = c3[i][j][r] - c1[i][j][r] - c2[i][j][r];
+                }
         __syncthreads();
     }
     const int64_t MN = (int64_t)g.M * g.N;
@@ -392,8 +428,21 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void k_cgemm_mfma(Gemm<R> g, 
                 const int m = m0 + wm0 + 16 * i + lane % 16;
                 const int n = n0 + wn0 + 16 * j + MfmaT<R>::row(lane, r);
                 if (m >= g.M || n >= g.N) continue;
-                const R vre = RAG ? c1[i][j][r] : c1[i][j][r] - c2[i][j][r];
-                const R vim = RAG ? c3[i][j][r] : c3[i][j][r] - c1[i][j][r] - c2[i][j][r];
+                R vre, vim;
+                if constexpr (WGK > 1) {   // group q finishes registers q, q + WGK, ...
+                    const int e = 4 * (i * TJ + j) + r;
+                    if (e % WGK != kg) continue;
+                    vre = lds[e * NT + tid];
+                    vim = lds[(REGS + e) * NT + tid];
+#pragma unroll
+                    for (int q = 1; q < WGK; ++q) {
+                        vre += lds[(2 * q * REGS + e) * NT + tid];
+                        vim += lds[((2 * q + 1) * REGS + e) * NT + tid];
+                    }
+                } else {
+                    vre = RAG ? c1[i][j][r] : c1[i][j][r] - c2[i][j][r];
+                    vim = RAG ? c3[i][j][r] : c3[i][j][r] - c1[i][j][r] - c2[i][j][r];
+                }
                 if (splits == 1) {
                     const int64_t off = (int64_t)m * g.scm + (int64_t)n * g.scn;
                     R re = g.alpha * vre, im = g.alpha * vim;
@@ -844,6 +893,34 @@ inline int wave_count(int kblocks, int64_t tiles) {
     return kblocks >= 16 && tiles < 512 ? 16 : kblocks >= 8 ? 8 : kblocks >= 2 ? 4 : 1;
 }
 
+// Whether k_cgemm_mfma's aligned form takes a Gemm: k-tiles of 16 inside the
+// inner extent, unit strides to stage along, and 32-bit element offsets inside
+// a tile.
+template <typename R>
+bool aligned_form(const Gemm<R>& g) {
+    const bool off32 = (int64_t)128 * (g.sam + g.sbn) + 32 * (g.sak + g.sbk) + g.a_plane + g.b_plane < (1LL << 31);
+    return g.Kout > 0 && g.Kin >= 16 && g.Kin % 16 == 0 && g.M >= 16 && g.N >= 16 && (g.sam == 1 || g.sak == 1) &&
+           (g.sbn == 1 || g.sbk == 1) && off32;
+}
+
+// Tiles of bm x bn outputs of all batches.
+template <typename R>
+int64_t tile_count(const Gemm<R>& g, int bm, int bn) {
+    return (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.B1 * g.B2;
+}
+
+// Launches for the wave-sliced kernel: below WAVE_MAX_FLOPS, unless the aligned
+// 32 x 32 tiles cover half the chip, where staging through LDS reads the
+// operands half as often (us, wave-sliced / tiles: 128 tiles with K = 64, FP64
+// 9.9 / 7.8, FP32 8.0 / 6.2; 512 tiles with K = 32, 23.3 / 11.5; below, 64 tiles
+// with K = 64 5.9 / 7.4; K = 192 over 144 tiles, FP32, 8.3 / 9.1).
+template <typename R>
+bool takes_wave(const Gemm<R>& g) {
+    const int64_t K = (int64_t)g.Kin * g.Kout;
+    if (8.0 * g.M * g.N * (double)K * g.B1 * (double)g.B2 >= WAVE_MAX_FLOPS) return false;
+    return !(aligned_form(g) && g.M >= 32 && g.N >= 32 && tile_count(g, 32, 32) >= (K > 128 ? 256 : 128));
+}
+
 template <typename R>
 int64_t wave_tiles(const Gemm<R>& g) {
     return (int64_t)((g.M + 15) / 16) * ((g.N + 15) / 16) * g.B1 * g.B2;
@@ -903,7 +980,7 @@ void launch_ragged(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, bool 
     R* part = (R*)ws.partial;
     if (info) *info = CgemmInfo{2, splits};
 #define TTN_RAG_LAUNCH(bt, minb, ak, bk)                                                                       \
-    hipLaunchKernelGGL((k_cgemm_mfma<R, bt, bt, 2, 2, minb, 16, ak, bk, true>), grid, dim3(256), 0, s, g, tilesM, \
+    hipLaunchKernelGGL((k_cgemm_mfma<R, bt, bt, 2, 2, 1, minb, 16, ak, bk, true>), grid, dim3(256), 0, s, g, tilesM, \
                        tilesN, splits, kchunk, part)
 #define TTN_RAG_LAUNCHES(bt, minb)             \
     do {                                       \
@@ -922,6 +999,71 @@ void launch_ragged(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, bool 
         TTN_RAG_LAUNCHES(64, 2);
 #undef TTN_RAG_LAUNCHES
 #undef TTN_RAG_LAUNCH
+    if (splits > 1) splitk_reduce(g, splits, (const R*)ws.partial, s);
+}
+
+// Launch of the aligned form of k_cgemm_mfma.  64 x 64 tiles (8 waves, two blocks
+// per CU) where they cover every CU; 32 x 32 tiles (4 waves) where those do not
+// or pad less, with two or four groups of waves on a tile when there are few
+// of them, so that a CU always has 8 to 16 waves and no split's partial sums
+// pass through memory; FP64 launches with a long K take 128 x 64 tiles (16
+// waves).  K is split over the grid only where the 32 x 32 tiles leave CUs
+// without a block, or where a long K meets one 64 x 64 tile per CU.
+// Measured, FP64, us (128 x 64 tiles or 64 x 64 ones of four waves with K split
+// over the grid / the rule here): right-leg sum of a 64^3 node over 4, 8, 16
+// operators 29.7 / 15.6, 34.2 / 26.5, 51.0 / 46.2; stack of 8 over 64^3 25.8 /
+// 25.1, over 128^3 281 / 268; 96^3 sum over 8 201 / 116; 32 x 32 x 128 node,
+// parent-leg stack of 8 36.5 / 24.7.  FP32, 64^3 sum over 4: 21.7 / 11.4.
+template <typename R>
+void launch_aligned(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, bool a_k, bool b_k, CgemmInfo* info) {
+    const int K = g.Kin * g.Kout, kt = K / 16;
+    const int64_t t32 = tile_count(g, 32, 32), t64 = tile_count(g, 64, 64), t128 = tile_count(g, 128, 64);
+    // 32 x 32 tiles reach 0.87 of the larger ones' rate (FP32: 0.8) where both fill
+    // the chip (128^3: 305 / 268 us)
+    const double r32 = sizeof(R) == 8 ? 0.87 : 0.8;
+    // few outputs and a long K, split either way (128 x 128 outputs, K = 16384: 53.7 us
+    // with 32 x 32 tiles, 48.4 with 64 x 64; half the flops: 31.3 / 32.2)
+    const bool deep = t32 < 256 && t64 * (kt / 8) >= 512;
+    const bool small = !deep && (t64 < 256 || padded(g.M, g.N, 32, 32) / r32 < padded(g.M, g.N, 64, 64));
+    const bool big = !small && sizeof(R) == 8 && K >= 512 && t128 >= 256 &&
+                     padded(g.M, g.N, 128, 64) <= padded(g.M, g.N, 64, 64);
+    const int bm = small ? 32 : big ? 128 : 64, bn = small ? 32 : 64;
+    const int64_t tiles = small ? t32 : big ? t128 : t64;
+    int splits = big ? 1 : split_factor(g, ws, tiles, kt, small ? 256 : 512, small || deep ? 8 : 32);
+    const int kchunk = (kt + splits - 1) / splits * 16;
+    splits = (K + kchunk - 1) / kchunk;
+    const int64_t blocks = tiles * splits;
+    const int groups = !small || kchunk < 128 ? 1 : blocks <= 256 ? 4 : blocks <= 512 ? 2 : 1;
+    const int tilesM = (g.M + bm - 1) / bm, tilesN = (g.N + bn - 1) / bn;
+    const dim3 grid((unsigned)blocks);
+    R* part = (R*)ws.partial;
+    if (info) *info = CgemmInfo{2, splits};
+#define TTN_MFMA_LAUNCH(bm, bn, wgm, wgn, wgk, minb, ak, bk)                                                        \
+    hipLaunchKernelGGL((k_cgemm_mfma<R, bm, bn, wgm, wgn, wgk, minb, 16, ak, bk>), grid, dim3(64 * wgm * wgn * wgk), \
+                       0, s, g, tilesM, tilesN, splits, kchunk, part)
+#define TTN_MFMA_LAUNCHES(bm, bn, wgm, wgn, wgk, minb)                        \
+    do {                                                                      \
+        if (a_k && b_k)                                                       \
+            TTN_MFMA_LAUNCH(bm, bn, wgm, wgn, wgk, minb, true, true);         \
+        else if (a_k)                                                         \
+            TTN_MFMA_LAUNCH(bm, bn, wgm, wgn, wgk, minb, true, false);        \
+        else if (b_k)                                                         \
+            TTN_MFMA_LAUNCH(bm, bn, wgm, wgn, wgk, minb, false, true);        \
+        else                                                                  \
+            TTN_MFMA_LAUNCH(bm, bn, wgm, wgn, wgk, minb, false, false);       \
+    } while (0)
+    if (groups == 4)
+        TTN_MFMA_LAUNCHES(32, 32, 2, 2, 4, 1);
+    else if (groups == 2)
+        TTN_MFMA_LAUNCHES(32, 32, 2, 2, 2, 2);
+    else if (small)
+        TTN_MFMA_LAUNCHES(32, 32, 2, 2, 1, 4);
+    else if (!big)
+        TTN_MFMA_LAUNCHES(64, 64, 2, 4, 1, 2);
+    else if constexpr (sizeof(R) == 8)
+        TTN_MFMA_LAUNCHES(128, 64, 4, 4, 1, 1);
+#undef TTN_MFMA_LAUNCHES
+#undef TTN_MFMA_LAUNCH
     if (splits > 1) splitk_reduce(g, splits, (const R*)ws.partial, s);
 }
 
@@ -1025,8 +1167,8 @@ bool cgemm_check(const Gemm<R>& g, const GemmScratch& ws, char* why, int whylen)
 
 template <typename R>
 bool cgemm_groupable(const Gemm<R>& g, const GemmScratch& ws) {
-    const double flops = 8.0 * g.M * g.N * (double)g.Kin * g.Kout * (double)g.B1 * g.B2;
-    return flops > 0 && flops < WAVE_MAX_FLOPS && wave_splits(g, ws) == 1;
+    const bool any = g.M > 0 && g.N > 0 && g.Kin > 0 && g.Kout > 0 && g.B1 > 0 && g.B2 > 0;
+    return any && takes_wave(g) && wave_splits(g, ws) == 1;
 }
 
 template <typename R>
@@ -1096,16 +1238,12 @@ bool cgemm(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, char* why, in
         return b;
     };
     if (ev0) (void)hipEventRecord(ev0, s);
-    if (K == 0 || flops < WAVE_MAX_FLOPS) {
+    if (K == 0 || takes_wave(g)) {
         launch_wave(g, ws, s, info);
         if (ev1) (void)hipEventRecord(ev1, s);
         return true;
     }
-    // the aligned form of k_cgemm_mfma: per-element offsets inside a tile are
-    // 32-bit there
-    const bool off32 = (int64_t)128 * (g.sam + g.sbn) + 32 * (g.sak + g.sbk) + g.a_plane + g.b_plane < (1LL << 31);
-    const bool mfma_ok = K >= 16 && g.Kin % 16 == 0 && g.M >= 16 && g.N >= 16 && (g.sam == 1 || g.sak == 1) &&
-                         (g.sbn == 1 || g.sbk == 1) && off32;
+    const bool mfma_ok = aligned_form(g);
     if constexpr (sizeof(R) == 4) {
         // BF16x3 mode: outputs of at least one 128 x 128 tile whose inner extent
         // is a multiple of 32, where two blocks in four CUs have work; every
@@ -1114,13 +1252,14 @@ bool cgemm(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, char* why, in
         const int64_t tiles128 = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128) * nbatch;
         const bool bf16 = g.split && mfma_ok && g.M >= 128 && g.N >= 128 && g.Kin % 32 == 0 &&
                           tiles128 * split_factor(g, ws, tiles128, K / 16, 256, 4) >= 128;
-        // FP32 alternatives on the FP32 matrix cores: the aligned 64 x 64 tiles
-        // (three products), or the ragged tiles (four); below 1 Gflop their
-        // shorter prologue wins (64^3 node, right-leg stack of four, 0.54 Gflop:
-        // 10.6 us against 13.8; 96^3, left-leg stack of five, 3.4 Gflop: 44.5
+        // FP32 alternatives on the FP32 matrix cores: the aligned tiles (three
+        // products), or the ragged tiles (four); below 1 Gflop their shorter
+        // prologue wins (64^3 node, right-leg stack of four, 0.54 Gflop: 10.7 us
+        // against 13.8; 96^3, left-leg stack of five, 3.4 Gflop: 44.5
         // against 35.7; 208 x 208 x 144, parent-leg sum over three: 305 against
         // 163 with 128 x 64 tiles)
-        const Choice f = mfma_ok ? Choice{64, 64, 0.55} : best({{64, 64, 0.40}, {32, 32, 0.36}});
+        const Choice f = best(mfma_ok ? std::initializer_list<Choice>{{64, 64, 0.55}, {32, 32, 0.44}}
+                                       : std::initializer_list<Choice>{{64, 64, 0.40}, {32, 32, 0.36}});
         const double tf = padded(g.M, g.N, f.bm, f.bn) / f.rate, ts = padded(g.M, g.N, t.bm, t.bn) / t.rate;
         if (bf16 || (flops >= SPLIT_MIN_FLOPS && ts < tf)) {
             launch_split(g, ws, s, bf16 ? 2 : 3, t.bm, t.bn, a_k, b_k, info);
@@ -1135,54 +1274,7 @@ bool cgemm(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, char* why, in
         if (ev1) (void)hipEventRecord(ev1, s);
         return true;
     }
-    // FP64: 128 x 64 tiles, unless their grid (after split-K) would leave more
-    // than half of the 256 CUs idle; then, and for FP32, 64 x 64 tiles, whose
-    // grid is larger and whose splits may be finer.  Splits cover the chip once:
-    // one workgroup of the large tiles per CU, two of the small ones.
-    bool big = sizeof(R) == 8 && g.M >= 128 && g.N >= 64;
-    int bm = 0, splits = 1;
-    int64_t tiles = 0;
-    for (int pass = 0; pass < 2; ++pass) {
-        bm = big ? 128 : 64;
-        tiles = (int64_t)((g.M + bm - 1) / bm) * ((g.N + 63) / 64) * nbatch;
-        splits = tiles >= 256 ? 1 : split_factor(g, ws, tiles, K / 16, big ? 256 : 512, big ? 4 : 2);
-        if (!big || tiles * splits >= 128) break;
-        big = false;
-    }
-    const int tilesM = (g.M + bm - 1) / bm, tilesN = (g.N + 63) / 64;
-    const int kchunk = (K / 16 + splits - 1) / splits * 16;
-    splits = (K + kchunk - 1) / kchunk;
-    const dim3 grid((unsigned)(tiles * splits));
-    R* part = (R*)ws.partial;
-    if (info) *info = CgemmInfo{2, splits};
-#define TTN_MFMA_LAUNCH(bm, wgm, wgn, minb)                                                                   \
-    do {                                                                                                      \
-        const dim3 blk(64 * wgm * wgn);                                                                       \
-        if (a_k && b_k)                                                                                       \
-            hipLaunchKernelGGL((k_cgemm_mfma<R, bm, 64, wgm, wgn, minb, 16, true, true>), grid, blk, 0, s, g,   \
-                               tilesM, tilesN, splits, kchunk, part);                                         \
-        else if (a_k)                                                                                         \
-            hipLaunchKernelGGL((k_cgemm_mfma<R, bm, 64, wgm, wgn, minb, 16, true, false>), grid, blk, 0, s, g,  \
-                               tilesM, tilesN, splits, kchunk, part);                                         \
-        else if (b_k)                                                                                         \
-            hipLaunchKernelGGL((k_cgemm_mfma<R, bm, 64, wgm, wgn, minb, 16, false, true>), grid, blk, 0, s, g,  \
-                               tilesM, tilesN, splits, kchunk, part);                                         \
-        else                                                                                                  \
-            hipLaunchKernelGGL((k_cgemm_mfma<R, bm, 64, wgm, wgn, minb, 16, false, false>), grid, blk, 0, s, g, \
-                               tilesM, tilesN, splits, kchunk, part);                                         \
-    } while (0)
-    // large tiles: 16 waves (4 x 4) of 32 x 16 outputs, one block per CU; small
-    // tiles: 4 waves (2 x 2), two blocks per CU
-    if constexpr (sizeof(R) == 8) {
-        if (big)
-            TTN_MFMA_LAUNCH(128, 4, 4, 1);
-        else
-            TTN_MFMA_LAUNCH(64, 2, 2, 2);
-    } else {
-        TTN_MFMA_LAUNCH(64, 2, 2, 2);
-    }
-#undef TTN_MFMA_LAUNCH
-    if (splits > 1) splitk_reduce(g, splits, (const R*)ws.partial, s);
+    launch_aligned(g, ws, s, a_k, b_k, info);
     // the timing window closes after the split-K reduction: a launch's time
     // is the main kernel plus its reduction
     if (ev1) (void)hipEventRecord(ev1, s);
