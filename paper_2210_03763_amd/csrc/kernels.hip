@@ -616,16 +616,59 @@ __global__ __launch_bounds__(256) void k_lz_beta(const double* partial, int nb, 
     }
 }
 
+// Lane exchanges inside a row of 16 lanes without a trip through LDS (DPP): the
+// value of the lane the control word names, 0 where that lane does not exist
+// or the row is masked off.
+template <int CTRL, int ROWS = 0xf>
+__device__ inline double dpp_move(double v) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffff), CTRL, ROWS, 0xf, false);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+constexpr int DPP_QUAD_XOR1 = 0xB1, DPP_QUAD_XOR2 = 0x4E, DPP_ROW_SHL1 = 0x101, DPP_ROW_SHR1 = 0x111,
+              DPP_ROW_SHR2 = 0x112, DPP_ROW_SHR4 = 0x114, DPP_ROW_SHR8 = 0x118, DPP_ROW_MIRROR = 0x140, DPP_ROW_HALF_MIRROR = 0x141,
+              DPP_ROW_BCAST15 = 0x142, DPP_ROW_BCAST31 = 0x143;
+
+__device__ inline double lane_value(double v, int lane) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_readlane((int)(b & 0xffffffff), lane);
+    const unsigned hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// sum over each row of 16 lanes, in all of its lanes
+__device__ inline double row_total(double v) {
+    v += dpp_move<DPP_QUAD_XOR1>(v);
+    v += dpp_move<DPP_QUAD_XOR2>(v);
+    v += dpp_move<DPP_ROW_HALF_MIRROR>(v);
+    return v + dpp_move<DPP_ROW_MIRROR>(v);
+}
+
+// sum over a whole wave (all 64 lanes active), the same value in every lane
+__device__ inline double wave_total(double v) {
+    v += dpp_move<DPP_ROW_SHR1>(v);
+    v += dpp_move<DPP_ROW_SHR2>(v);
+    v += dpp_move<DPP_ROW_SHR4>(v);
+    v += dpp_move<DPP_ROW_SHR8>(v);
+    v += dpp_move<DPP_ROW_BCAST15, 0xa>(v);
+    v += dpp_move<DPP_ROW_BCAST31, 0xc>(v);
+    return lane_value(v, 63);
+}
+
 // y = exp(-i tau H) e_1 for the m_eff x m_eff projection H of the Krylov
 // basis: the Taylor series of exp(B/s), B = -i tau H, applied s times to the
-// vector, with s chosen so that ||B/s||_1 <= 1/4 and as many terms as make
-// the remainder bound of the series fall below double precision.  H is the
-// real symmetric tridiagonal (alpha, beta) of a Lanczos basis, or the complex
-// upper Hessenberg matrix of an Arnoldi basis (columns in hs, subdiagonal
-// beta) when lz->nonherm.  The first wave does all of it, lane t holding row
-// t of H and element t of the vectors (products with H by lane shuffles, the
-// norm by one wave reduction); the other waves of the block only meet it at
-// the closing barrier.
+// vector, with s chosen so that theta = ||B/s||_1 <= 1 and as many terms as
+// make the remainder bound of the series, theta^(K+1) / (K+1)! e^theta, fall
+// below 1e-18 for every such theta (K = 20: 5e-20).  theta near 1 is where the
+// rounding bound of the whole product, s e^theta, and the number of terms per
+// unit of tau are both small (theta <= 1/4 takes 2.2 times the terms).  H is
+// the real symmetric tridiagonal (alpha, beta) of a Lanczos basis, or the
+// complex upper Hessenberg matrix of an Arnoldi basis (columns in hs,
+// subdiagonal beta) when lz->nonherm.  The first wave does all of it, lane t
+// holding row t of H and element t of the vectors (neighbours by DPP, the norm
+// by one wave reduction); a serial chain, so what counts is its latency.  The
+// other waves of the block only meet it at the closing barrier.
 
 // entry (row, col) of the projection (re, im), zero outside m x m
 __device__ inline double2 lz_h_entry(const LanczosDev* lz, bool herm, int m, int row, int col) {
@@ -647,13 +690,14 @@ __device__ inline double2 lz_h_entry(const LanczosDev* lz, bool herm, int m, int
     return make_double2(a, b);
 }
 
-__device__ inline double wave_max(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const double u = __shfl_xor(v, o, 64);
-        v = u > v ? u : v;
-    }
-    return v;
+// maximum over the first row of 16 lanes, the same value in every lane
+__device__ inline double row0_max(double v) {
+    auto step = [](double a, double u) { return u > a ? u : a; };
+    v = step(v, dpp_move<DPP_QUAD_XOR1>(v));
+    v = step(v, dpp_move<DPP_QUAD_XOR2>(v));
+    v = step(v, dpp_move<DPP_ROW_HALF_MIRROR>(v));
+    v = step(v, dpp_move<DPP_ROW_MIRROR>(v));
+    return lane_value(v, 0);
 }
 
 // y: 2 KRYLOV_MAX doubles in LDS
@@ -676,47 +720,38 @@ __device__ __forceinline__ void lz_expm_hessenberg(const LanczosDev* lz, double 
         const double dl = herm ? lz_h_entry(lz, true, m, t, t - 1).x : 0.0;
         const double dd = herm ? lz_h_entry(lz, true, m, t, t).x : 0.0;
         const double du = herm ? lz_h_entry(lz, true, m, t, t + 1).x : 0.0;
-        // 1-norm bound of tau H: the largest column sum (lane t sums column t
-        // in row order)
-        double cs = 0;
-        for (int row = 0; row < m; ++row) {
-            const double2 e = lz_h_entry(lz, herm, m, row, t);
-            cs += fabs(e.x) + fabs(e.y);
-        }
-        double nrm = wave_max(t < m ? cs : 0.0) * fabs(tau);
-        int ns = (int)ceil(nrm / 0.25);
+        // 1-norm bound of tau H: the largest column sum (the tridiagonal H is
+        // symmetric; else lane t sums column t in row order)
+        double cs = fabs(dl) + fabs(dd) + fabs(du);
+        if (!herm)
+            for (int row = 0; row < m; ++row) {
+                const double2 e = lz_h_entry(lz, false, m, row, t);
+                cs += fabs(e.x) + fabs(e.y);
+            }
+        double nrm = row0_max(t < m ? cs : 0.0) * fabs(tau);
+        int ns = (int)ceil(nrm);
         if (ns < 1) ns = 1;
-        const double h = tau / ns;
-        // number of Taylor terms K: with theta = ||h H||_1 <= 1/4 the
-        // remainder after K terms is at most theta^(K+1) / (K+1)! e^theta
-        // (e^theta < 1.3) of the vector, kept below 1e-18 (the same K in
-        // every lane, no reductions inside the series)
-        const double theta = nrm / ns;
-        int K = 0;
-        for (double a = 1.0; K < 40; ++K) {
-            a *= theta / (K + 1);   // theta^(K+1) / (K+1)!
-            if (1.3 * a <= 1e-18) break;
-        }
+        constexpr int TERMS = 20;
+        const double fk = tau / ns / (t + 1);   // lane k - 1: h / k
         double vr = t == 0 ? 1.0 : 0.0, vi = 0.0;
         for (int rep = 0; rep < ns; ++rep) {
             double tr = vr, ti = vi, wr = vr, wi = vi;
-            for (int k = 1; k <= K; ++k) {
+#pragma unroll 4
+            for (int k = 1; k <= TERMS; ++k) {
                 // term <- (-i h H term) / k
                 double sr = 0, si = 0;
-                if (herm) {
-                    const double trl = __shfl(tr, t > 0 ? t - 1 : 0, 64), til = __shfl(ti, t > 0 ? t - 1 : 0, 64);
-                    const double tru = __shfl(tr, t < 63 ? t + 1 : 63, 64), tiu = __shfl(ti, t < 63 ? t + 1 : 63, 64);
-                    sr = dl * trl + dd * tr + du * tru;
-                    si = dl * til + dd * ti + du * tiu;
+                if (herm) {   // rows 0 .. 15 of H lie in one row of lanes
+                    sr = dl * dpp_move<DPP_ROW_SHR1>(tr) + dd * tr + du * dpp_move<DPP_ROW_SHL1>(tr);
+                    si = dl * dpp_move<DPP_ROW_SHR1>(ti) + dd * ti + du * dpp_move<DPP_ROW_SHL1>(ti);
                 } else {
 #pragma unroll
                     for (int c = 0; c < KM; ++c) {
-                        const double trc = __shfl(tr, c, 64), tic = __shfl(ti, c, 64);
+                        const double trc = lane_value(tr, c), tic = lane_value(ti, c);
                         sr += hr[c] * trc - hi[c] * tic;
                         si += hr[c] * tic + hi[c] * trc;
                     }
                 }
-                const double f = h / k;
+                const double f = lane_value(fk, k - 1);
                 if (t < m) {
                     tr = f * si;
                     ti = -f * sr;
@@ -747,246 +782,328 @@ __device__ __forceinline__ void lz_expm_hessenberg(const LanczosDev* lz, double 
 // ---------------------------------------------------------------------------
 constexpr int SMALL_THREADS = 1024;
 
-// Two ownerships of the elements i < n <= SMALL_EVOLVE_N.  In the matvec
-// four lanes share each element and split its terms (images and operator
-// stacks dealt round-robin), summed by two lane exchanges: lane e + 16 q of
-// wave w (e < 16, q < 4) takes part q of the elements i = e + 16 w +
-// SMALL_GROUPS t, t < SMALL_PER.  Each 16-lane row of a wave then reads 16
-// consecutive entries of one vector and one operator entry (no LDS bank
-// conflicts; the four parts of an element on adjacent lanes had put three
-// vectors 4 KB apart on the same banks).  The (l, r, p) split of every
-// element is tabulated in LDS once per launch (10 bits each).  The
-// projections give wave k Krylov vector k; the subtractions, norms and
-// scaling give thread i element i.
+// What bounds it: a serial chain of m Krylov steps in one workgroup (waits for
+// LDS, lane reductions and barriers; the arithmetic is small).  So: complex
+// numbers interleaved (one 16-byte LDS access each); wave k keeps basis vector
+// k in registers and forms the k-th projection alone; subtractions deal the
+// basis over the four lanes of a quad; every wave forms the norm for itself,
+// and the next product takes the unscaled vector and scales its result: five
+// barriers a step.  Operators of n <= SMALL_DENSE_N are formed once as an
+// n x n matrix in registers (16 lanes two rows), which leaves one pass per
+// product instead of images and sums.
+// Measured, m = 12 (us; planar LDS vectors, two passes a product, projections
+// through LDS reductions / this): 3 x 3 x 9 node (n = 81) 95 / 48, 16 x 16
+// bond over five operators (n = 256) 163 / 109.
+constexpr int SMALL_DENSE_N = 96;
+constexpr int SMALL_DENSE_COLS = SMALL_DENSE_N / 16;   // of each of a thread's two rows
+
+// The structured product deals the elements i < n <= SMALL_EVOLVE_N so: four
+// lanes share each element and split its terms (images and operator stacks
+// dealt round-robin), summed by two lane exchanges: lane e + 16 q of wave w
+// (e < 16, q < 4) takes part q of the elements i = e + 16 w + SMALL_GROUPS t.
+// Each 16-lane row of a wave then reads 16 consecutive entries of one vector
+// and one operator entry (no LDS bank conflicts).  The (l, r, p) split of every
+// element is tabulated in LDS once per launch (10 bits each).
 constexpr int SMALL_SPLIT = 4;
 constexpr int SMALL_GROUPS = SMALL_THREADS / SMALL_SPLIT;
-constexpr int SMALL_PER = (int)(SMALL_EVOLVE_N / SMALL_GROUPS);
-static_assert(SMALL_PER * SMALL_GROUPS == SMALL_EVOLVE_N, "elements must split evenly over the quads");
-static_assert(SMALL_EVOLVE_N == SMALL_THREADS, "one element per thread in the vector passes");
 static_assert(SMALL_SPLIT * 16 == 64 && SMALL_GROUPS == 16 * (SMALL_THREADS / 64), "four 16-lane parts per wave");
 static_assert(SMALL_EVOLVE_N <= 1024, "leg dimensions must fit the 10-bit fields of the index table");
+static_assert(KRYLOV_MAX <= SMALL_THREADS / 64, "one wave per Krylov vector");
+static_assert(SMALL_DENSE_N * 8 <= SMALL_THREADS && SMALL_DENSE_N % 16 == 0, "16 threads per two rows");
 
-// acc += sum_q op[o + D q] src[base + sq q], q < D (complex, planar op of D^2
-// entries and src of n entries)
-__device__ inline void small_term(const double* op, int D, int o, const double* src, int n, int base, int sq,
-                                  double& ar, double& ai) {
-    const int D2 = D * D;
-#pragma unroll 4
-    for (int q = 0; q < D; ++q) {
-        const double orr = op[o + D * q], oi = op[D2 + o + D * q];
-        const double xr = src[base + sq * q], xi = src[n + base + sq * q];
-        ar += orr * xr - oi * xi;
-        ai += orr * xi + oi * xr;
-    }
+// Row stride of the basis in LDS: 4 (mod 16) entries, so that the four rows a
+// quad reads at one element lie on different banks.
+inline __host__ __device__ int small_stride(int n) { return (n + 11) / 16 * 16 + 4; }
+
+__device__ inline void cmul_add(double2 a, double2 b, double& re, double& im) {
+    re += a.x * b.x - a.y * b.y;
+    im += a.x * b.y + a.y * b.x;
 }
 
-// y = Op x; S holds the left (U_k = L_k x_L x, k = 1..sL) and right (Z_j =
-// R_j x_R x) images, slot stride 2n.  Ends with a barrier (y is complete).
-__device__ void small_matvec(const double* L, const double* Rr, const double* B, const double* W, int DL, int DR,
-                             int DP, int sL, int sR, const int* sidx, const double* x, double* S, double* y) {
+// acc += sum_q op[o + D q] src[base + sq q], q < D
+__device__ inline void small_term(const double2* op, int D, int o, const double2* src, int base, int sq, double& ar,
+                                  double& ai) {
+#pragma unroll 4
+    for (int q = 0; q < D; ++q) cmul_add(op[o + D * q], src[base + sq * q], ar, ai);
+}
+
+struct SmallOp {
+    const double2 *L, *R, *B, *W;   // stacks in LDS (R, B, W may be null)
+    int DL, DR, DP, sL, nz;
+};
+
+// y = inv Op x; S holds the left (U_k = L_k x, k = 1..sL) and right (Z_j = R_j x)
+// images, n entries each.  Ends with a barrier (y is complete).
+__device__ void small_matvec(const SmallOp& o, const int* sidx, const double2* x, double inv, double2* S, double2* y) {
+    const int DL = o.DL, DR = o.DR, DP = o.DP, sL = o.sL, nz = o.nz;
     const int n = DL * DR * DP;
-    const int nz = (W && sR > 0) ? sR : 0;
     const int q = (threadIdx.x >> 4) & (SMALL_SPLIT - 1), g = (threadIdx.x & 15) + 16 * (threadIdx.x >> 6);
     // images: lane q of a quad forms images k = q, q + 4, ... of its elements
     for (int k = q; k < sL + nz; k += SMALL_SPLIT) {
         const bool left = k < sL;
-#pragma unroll 1
-        for (int t = 0; t < SMALL_PER; ++t) {
-            const int i = g + SMALL_GROUPS * t;
-            if (i < n) {
-                const int lx = sidx[i] & 1023, rx = (sidx[i] >> 10) & 1023;
-                double ar = 0, ai = 0;
-                if (left)
-                    small_term(L + 2 * DL * DL * (k + 1), DL, lx, x, n, i - lx, 1, ar, ai);
-                else
-                    small_term(Rr + 2 * DR * DR * (k - sL + 1), DR, rx, x, n, i - DL * rx, DL, ar, ai);
-                S[2 * n * k + i] = ar;
-                S[2 * n * k + n + i] = ai;
-            }
+        for (int i = g; i < n; i += SMALL_GROUPS) {
+            const int lx = sidx[i] & 1023, rx = (sidx[i] >> 10) & 1023;
+            double ar = 0, ai = 0;
+            if (left)
+                small_term(o.L + DL * DL * (k + 1), DL, lx, x, i - lx, 1, ar, ai);
+            else
+                small_term(o.R + DR * DR * (k - sL + 1), DR, rx, x, i - DL * rx, DL, ar, ai);
+            S[n * k + i] = make_double2(ar, ai);
         }
     }
     __syncthreads();
     // sums: unit 0 is the left block Hamiltonian, units 1..sL+1 the right-leg
-    // stack (H_R x, A_i U_i), the next sL+nz+1 the parent-leg stack (H_P x,
+    // stack (H_R x, B_i U_i), the next sL+nz+1 the parent-leg stack (H_P x,
     // W U, W Z); lane q takes the units u = q mod 4
-    const int uW = 1 + (B ? sL + 1 : 0);
-#pragma unroll 1
-    for (int t = 0; t < SMALL_PER; ++t) {
-        const int i = g + SMALL_GROUPS * t;
+    const int uW = 1 + (o.B ? sL + 1 : 0);
+    for (int i0 = 0; i0 < n; i0 += SMALL_GROUPS) {
+        const int i = i0 + g;
         double ar = 0, ai = 0;
         if (i < n) {
             const int e = sidx[i];
             const int l = e & 1023, r = (e >> 10) & 1023, p = e >> 20;
-            if (q == 0) small_term(L, DL, l, x, n, i - l, 1, ar, ai);
-            if (B)
+            if (q == 0) small_term(o.L, DL, l, x, i - l, 1, ar, ai);
+            if (o.B)
                 for (int k = (q - 1) & (SMALL_SPLIT - 1); k <= sL; k += SMALL_SPLIT)
-                    small_term(B + 2 * DR * DR * k, DR, r, k == 0 ? x : S + 2 * n * (k - 1), n, i - DL * r, DL,
-                               ar, ai);
-            if (W)
+                    small_term(o.B + DR * DR * k, DR, r, k == 0 ? x : S + n * (k - 1), i - DL * r, DL, ar, ai);
+            if (o.W)
                 for (int k = (q - uW) & (SMALL_SPLIT - 1); k <= sL + nz; k += SMALL_SPLIT)
-                    small_term(W + 2 * DP * DP * k, DP, p, k == 0 ? x : S + 2 * n * (k - 1), n,
-                               i - DL * DR * p, DL * DR, ar, ai);
+                    small_term(o.W + DP * DP * k, DP, p, k == 0 ? x : S + n * (k - 1), i - DL * DR * p, DL * DR, ar,
+                               ai);
         }
         // the four lanes of element i (16 apart) all take part
         ar += __shfl_xor(ar, 16, 64);
         ai += __shfl_xor(ai, 16, 64);
         ar += __shfl_xor(ar, 32, 64);
         ai += __shfl_xor(ai, 32, 64);
-        if (q == 0 && i < n) {
-            y[i] = ar;
-            y[n + i] = ai;
-        }
+        if (q == 0 && i < n) y[i] = make_double2(ar * inv, ai * inv);
     }
     __syncthreads();
 }
 
-// c_k = <v_k, w> for k < kc (planar vectors of n in LDS, w complete on
-// entry): wave k forms product k over all n elements and reduces it across
-// its lanes; the totals land in c[2 kc] (LDS) behind one barrier.
-static_assert(KRYLOV_MAX <= SMALL_THREADS / 64, "one wave per Krylov vector in the projections");
-__device__ void small_project(const double* V, int kc, const double* w, int n, double* c) {
-    const int lane = threadIdx.x & 63, k = threadIdx.x >> 6;
-    if (k < kc) {
-        const double* v = V + 2 * n * k;
-        double re = 0, im = 0;
-        for (int i = lane; i < n; i += 64) {
-            const double vr = v[i], vi = v[n + i], wr = w[i], wi = w[n + i];
-            re += vr * wr + vi * wi;
-            im += vr * wi - vi * wr;
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            re += __shfl_xor(re, o, 64);
-            im += __shfl_xor(im, o, 64);
-        }
-        if (lane == 0) {
-            c[2 * k] = re;
-            c[2 * k + 1] = im;
-        }
+// entry (row, col) of the operator as a matrix; ir, ic are their table entries
+__device__ double2 small_entry(const SmallOp& o, int ir, int ic) {
+    const int l = ir & 1023, r = (ir >> 10) & 1023, p = ir >> 20;
+    const int l2 = ic & 1023, r2 = (ic >> 10) & 1023, p2 = ic >> 20;
+    const int el = l + o.DL * l2, er = r + o.DR * r2, ep = p + o.DP * p2;
+    const int L2 = o.DL * o.DL, R2 = o.DR * o.DR, P2 = o.DP * o.DP;
+    double re = 0, im = 0;
+    const double2 one = make_double2(1.0, 0.0);
+    if (r == r2 && p == p2) cmul_add(o.L[el], one, re, im);
+    if (o.B && p == p2) {
+        if (l == l2) cmul_add(o.B[er], one, re, im);
+        for (int k = 1; k <= o.sL; ++k) cmul_add(o.L[L2 * k + el], o.B[R2 * k + er], re, im);
     }
-    __syncthreads();
+    if (o.W && r == r2) {
+        if (l == l2) cmul_add(o.W[ep], one, re, im);
+        for (int k = 1; k <= o.sL; ++k) cmul_add(o.L[L2 * k + el], o.W[P2 * k + ep], re, im);
+    }
+    if (o.W && l == l2)
+        for (int k = 1; k <= o.nz; ++k) cmul_add(o.R[R2 * k + er], o.W[P2 * (o.sL + k) + ep], re, im);
+    return make_double2(re, im);
 }
 
+// E: entries of a vector per lane (n <= 64 E); up to 4 of them, a wave keeps its
+// basis vector in registers, else it reads it from LDS.
+template <int E, bool DENSE>
 __global__ __launch_bounds__(SMALL_THREADS) void k_small_evolve(const double* gL, const double* gR, const double* gB,
                                                              const double* gW, int DL, int DR, int DP, int sL,
                                                              int sR, int m, double tau, double tol, int nonherm,
                                                              double* x, StepDev* st) {
-    __shared__ double pool[SMALL_EVOLVE_POOL];
+    __shared__ double2 pool[SMALL_EVOLVE_POOL / 2];
     __shared__ LanczosDev lz;
-    __shared__ double sh2[2 * (SMALL_THREADS / 64)];
     __shared__ int sidx[SMALL_EVOLVE_N];
-    __shared__ double c[32];
-    __shared__ double s_beta;
-    __shared__ int s_stop;
-    const int n = DL * DR * DP;
+    __shared__ double2 c[KRYLOV_MAX];
+    constexpr bool KEEP = E <= 4;
+    constexpr int UNROLL = KEEP ? E : 4;
+    const int n = DL * DR * DP, NS = small_stride(n);
     const int L2 = DL * DL, R2 = DR * DR, P2 = DP * DP;
     const int nz = (gW && sR > 0) ? sR : 0;
-    // carve: V[(m+1)], w, S[sL + nz], L, R, B, W
-    double* V = pool;
-    double* w = V + 2 * n * (m + 1);
-    double* S = w + 2 * n;
-    double* L = S + 2 * n * (sL + nz);
-    double* Rr = L + 2 * L2 * (1 + sL);
-    double* B = Rr + (nz ? 2 * R2 * (1 + sR) : 0);
-    double* W = B + (gB ? 2 * R2 * (1 + sL) : 0);
-    for (int e = threadIdx.x; e < 2 * L2 * (1 + sL); e += blockDim.x) L[e] = gL[e];
-    if (nz)
-        for (int e = threadIdx.x; e < 2 * R2 * (1 + sR); e += blockDim.x) Rr[e] = gR[e];
-    if (gB)
-        for (int e = threadIdx.x; e < 2 * R2 * (1 + sL); e += blockDim.x) B[e] = gB[e];
-    if (gW)
-        for (int e = threadIdx.x; e < 2 * P2 * (1 + sL + sR); e += blockDim.x) W[e] = gW[e];
-    for (int i = threadIdx.x; i < n; i += blockDim.x) sidx[i] = (i % DL) | ((i / DL) % DR) << 10 | (i / (DL * DR)) << 20;
-    const int me_i = threadIdx.x;   // this thread's element in the vector passes
-    // v_0 = x / ||x||
-    double a[2] = {0.0, 0.0};
-    if (me_i < n) {
-        const double xr = x[me_i], xi = x[n + me_i];
-        w[me_i] = xr;
-        w[n + me_i] = xi;
-        a[0] += xr * xr + xi * xi;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // carve: V[m] (stride NS), the current and the next vector, S[sL + nz], L, R, B, W
+    double2* V = pool;
+    double2* cur = V + NS * m;
+    double2* nxt = cur + n;
+    double2* S = nxt + n;
+    double2* L = S + n * (sL + nz);
+    double2* Rr = L + L2 * (1 + sL);
+    double2* B = Rr + (nz ? R2 * (1 + sR) : 0);
+    double2* W = B + (gB ? R2 * (1 + sL) : 0);
+    // stacks: slots of D^2 entries, planes inside a slot
+    auto stage = [&](const double* src, double2* dst, int D2, int slots) {
+        for (int e = tid; e < D2 * slots; e += SMALL_THREADS) {
+            const int k = e / D2;
+            dst[e] = make_double2(src[e + D2 * k], src[e + D2 * (k + 1)]);
+        }
+    };
+    stage(gL, L, L2, 1 + sL);
+    if (nz) stage(gR, Rr, R2, 1 + sR);
+    if (gB) stage(gB, B, R2, 1 + sL);
+    if (gW) stage(gW, W, P2, 1 + sL + sR);
+    const SmallOp op{L, nz ? Rr : nullptr, gB ? B : nullptr, gW ? W : nullptr, DL, DR, DP, sL, nz};
+    for (int i = tid; i < n; i += SMALL_THREADS) {
+        sidx[i] = (i % DL) | ((i / DL) % DR) << 10 | (i / (DL * DR)) << 20;
+        cur[i] = make_double2(x[i], x[n + i]);
     }
-    double tot = block_sum_p<2>(a, sh2);
-    if (threadIdx.x == 0) {
-        lz.beta0 = sqrt(tot);
-        lz.zero = tot == 0.0 ? 1 : 0;
+    __syncthreads();
+    // sum of |u|^2, the same in every wave
+    auto norm2 = [&](const double2* u) {
+        double a = 0;
+#pragma unroll(UNROLL)
+        for (int e = 0; e < E; ++e) {
+            const int i = lane + 64 * e;
+            const double2 z = i < n ? u[i] : make_double2(0.0, 0.0);
+            a += z.x * z.x + z.y * z.y;
+        }
+        return wave_total(a);
+    };
+    // basis vector of this wave
+    double2 own[KEEP ? E : 1];
+#pragma unroll
+    for (int e = 0; e < (KEEP ? E : 1); ++e) own[e] = make_double2(0.0, 0.0);
+    auto take = [&](int k, const double2* u, double s) {   // v_k = s u, by wave k
+        if (wave != k) return;
+#pragma unroll(UNROLL)
+        for (int e = 0; e < E; ++e) {
+            const int i = lane + 64 * e;
+            if (i < n) {
+                const double2 z = u[i], v = make_double2(z.x * s, z.y * s);
+                if constexpr (KEEP) own[e] = v;
+                V[NS * k + i] = v;
+            }
+        }
+    };
+    auto project = [&](int kc, const double2* u) {   // c_k = <v_k, u>, k < kc
+        if (wave < kc) {
+            double re = 0, im = 0;
+#pragma unroll(UNROLL)
+            for (int e = 0; e < E; ++e) {
+                const int i = lane + 64 * e;
+                const double2 z = i < n ? u[i] : make_double2(0.0, 0.0);
+                double2 v;
+                if constexpr (KEEP)
+                    v = own[e];
+                else
+                    v = i < n ? V[NS * wave + i] : make_double2(0.0, 0.0);
+                re += v.x * z.x + v.y * z.y;
+                im += v.x * z.y - v.y * z.x;
+            }
+            re = wave_total(re);
+            im = wave_total(im);
+            if (lane == 0) c[wave] = make_double2(re, im);
+        }
+        __syncthreads();
+    };
+    // sum_k c_k v_k[i] for i = tid / 4 + 256 t, in all four lanes of a quad
+    auto expand = [&](int kc, int i, double& re, double& im) {
+        re = im = 0;
+        if (i < n)
+#pragma unroll 2
+            for (int k = tid & 3; k < kc; k += 4) cmul_add(c[k], V[NS * k + i], re, im);
+        re += dpp_move<DPP_QUAD_XOR1>(re);
+        im += dpp_move<DPP_QUAD_XOR1>(im);
+        re += dpp_move<DPP_QUAD_XOR2>(re);
+        im += dpp_move<DPP_QUAD_XOR2>(im);
+    };
+    auto subtract = [&](int kc, double2* u) {
+        for (int i0 = 0; i0 < n; i0 += SMALL_GROUPS) {
+            const int i = i0 + (tid >> 2);
+            double re, im;
+            expand(kc, i, re, im);
+            if ((tid & 3) == 0 && i < n) {
+                const double2 z = u[i];
+                u[i] = make_double2(z.x - re, z.y - im);
+            }
+        }
+        __syncthreads();
+    };
+    const double beta0 = sqrt(norm2(cur));
+    if (tid == 0) {
+        lz.beta0 = beta0;
+        lz.zero = beta0 == 0.0 ? 1 : 0;
         lz.done = lz.zero;
         lz.m_eff = 0;
         lz.nonherm = nonherm;
     }
-    __syncthreads();
-    if (lz.zero) return;   // x = 0 stays 0
-    {
-        const double inv = 1.0 / lz.beta0;
-        for (int i = threadIdx.x; i < 2 * n; i += blockDim.x) V[i] = w[i] * inv;
+    if (beta0 == 0.0) return;   // x = 0 stays 0
+    double inv = 1.0 / beta0;
+    take(0, cur, inv);
+    // the operator as a matrix: rows row0 and row0 + 1, columns tid % 16 + 16 t
+    const int row0 = 2 * (tid >> 4);
+    double2 mat[2][DENSE ? SMALL_DENSE_COLS : 1];
+    if constexpr (DENSE) {
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int t = 0; t < SMALL_DENSE_COLS; ++t) {
+                const int row = row0 + r, col = (tid & 15) + 16 * t;
+                mat[r][t] = row < n && col < n ? small_entry(op, sidx[row], sidx[col]) : make_double2(0.0, 0.0);
+            }
     }
-    __syncthreads();
+    double bprev = 0.0;
     for (int j = 0; j < m; ++j) {
         const int kc = j + 1;
-        small_matvec(L, nz ? Rr : nullptr, gB ? B : nullptr, gW ? W : nullptr, DL, DR, DP, sL, sR, sidx,
-                     V + 2 * n * j, S, w);
-        small_project(V, kc, w, n, c);
-        if (threadIdx.x == 0) {
-            lz.alpha[j] = c[2 * j];
-            lz.m_eff = j + 1;
-        }
-        if (nonherm && threadIdx.x < 2 * kc) lz.hs[2 * j * KRYLOV_MAX + threadIdx.x] = c[threadIdx.x];
-        if (j == m - 1) break;
-        // w -= V c, second projection, w -= V c' (each thread on its own
-        // element; the second projection reads all of w, behind a barrier)
-        a[0] = 0.0;
-        a[1] = 0.0;
-        for (int pass = 0; pass < 2; ++pass) {
-            if (me_i < n) {
-                const int i = me_i;
-                double wr = w[i], wi = w[n + i];
-#pragma unroll 2
-                for (int k = 0; k < kc; ++k) {
-                    const double vr = V[2 * n * k + i], vi = V[2 * n * k + n + i];
-                    wr -= c[2 * k] * vr - c[2 * k + 1] * vi;
-                    wi -= c[2 * k] * vi + c[2 * k + 1] * vr;
+        if constexpr (DENSE) {
+            if (8 * wave < n) {   // eight rows a wave
+                double re[2] = {0, 0}, im[2] = {0, 0};
+#pragma unroll
+                for (int t = 0; t < SMALL_DENSE_COLS; ++t) {
+                    const int col = (tid & 15) + 16 * t;
+                    const double2 z = col < n ? cur[col] : make_double2(0.0, 0.0);
+                    cmul_add(mat[0][t], z, re[0], im[0]);
+                    cmul_add(mat[1][t], z, re[1], im[1]);
                 }
-                w[i] = wr;
-                w[n + i] = wi;
-                if (pass == 1) a[0] += wr * wr + wi * wi;
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    const double a = row_total(re[r]), b = row_total(im[r]);
+                    if ((tid & 15) == 0 && row0 + r < n) nxt[row0 + r] = make_double2(a * inv, b * inv);
+                }
             }
-            if (pass == 0) {
-                __syncthreads();
-                small_project(V, kc, w, n, c);
-                if (nonherm && threadIdx.x < 2 * kc) lz.hs[2 * j * KRYLOV_MAX + threadIdx.x] += c[threadIdx.x];
-            }
+            __syncthreads();
+        } else
+            small_matvec(op, sidx, cur, inv, S, nxt);
+        project(kc, nxt);
+        if (tid == 0) {
+            lz.alpha[j] = c[j].x;
+            lz.m_eff = kc;
         }
-        tot = block_sum_p<2>(a, sh2);
-        if (threadIdx.x == 0) {
-            const double b = sqrt(tot);
-            const double bprev = j > 0 ? lz.beta[j - 1] : 0.0;
-            const bool stop = !(b > tol * (fabs(lz.alpha[j]) + bprev));
-            if (stop)
-                lz.done = 1;
-            else
-                lz.beta[j] = b;
-            s_stop = stop;
-            s_beta = b;
+        if (nonherm && tid < kc) {
+            lz.hs[2 * (j * KRYLOV_MAX + tid)] = c[tid].x;
+            lz.hs[2 * (j * KRYLOV_MAX + tid) + 1] = c[tid].y;
         }
-        __syncthreads();
-        if (s_stop) break;
-        const double inv = 1.0 / s_beta;
-        for (int i = threadIdx.x; i < 2 * n; i += blockDim.x) V[2 * n * (j + 1) + i] = w[i] * inv;
-        __syncthreads();
+        const double alpha = c[j].x;
+        if (j == m - 1) break;
+        subtract(kc, nxt);
+        project(kc, nxt);
+        if (nonherm && tid < kc) {
+            lz.hs[2 * (j * KRYLOV_MAX + tid)] += c[tid].x;
+            lz.hs[2 * (j * KRYLOV_MAX + tid) + 1] += c[tid].y;
+        }
+        subtract(kc, nxt);
+        const double b = sqrt(norm2(nxt));
+        if (!(b > tol * (fabs(alpha) + bprev))) {   // the same in every wave
+            if (tid == 0) lz.done = 1;
+            break;
+        }
+        if (tid == 0) lz.beta[j] = b;
+        bprev = b;
+        inv = 1.0 / b;
+        take(kc, nxt, inv);
+        double2* const t = cur;
+        cur = nxt;
+        nxt = t;
     }
+    __syncthreads();   // lz and c as the last step left them
     // y = exp(-i tau H_m) e_1, then x = beta0 sum_k y_k v_k
-    lz_expm_hessenberg(&lz, tau, c, st);
-    const int me = lz.m_eff;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        double re = 0, im = 0;
-        for (int k = 0; k < me; ++k) {
-            const double yr = c[2 * k] * lz.beta0, yi = c[2 * k + 1] * lz.beta0;
-            const double vr = V[2 * n * k + i], vi = V[2 * n * k + n + i];
-            re += yr * vr - yi * vi;
-            im += yr * vi + yi * vr;
+    lz_expm_hessenberg(&lz, tau, (double*)c, st);
+    for (int i0 = 0; i0 < n; i0 += SMALL_GROUPS) {
+        const int i = i0 + (tid >> 2);
+        double re, im;
+        expand(lz.m_eff, i, re, im);
+        if ((tid & 3) == 0 && i < n) {
+            x[i] = re * beta0;
+            x[n + i] = im * beta0;
         }
-        x[i] = re;
-        x[n + i] = im;
     }
 }
 
@@ -1196,7 +1313,7 @@ template void lz_iter<float>(double*, int, int, const float*, const float*, cons
 int64_t small_evolve_doubles(int DL, int DR, int DP, int sL, int sR, int m, bool hasB, bool hasW) {
     const int64_t n = (int64_t)DL * DR * DP;
     const int64_t nz = (hasW && sR > 0) ? sR : 0;
-    return 2 * n * (m + 1) + 2 * n + 2 * n * (sL + nz) + 2 * (int64_t)DL * DL * (1 + sL) +
+    return 2 * (int64_t)small_stride((int)n) * m + 4 * n + 2 * n * (sL + nz) + 2 * (int64_t)DL * DL * (1 + sL) +
            (nz ? 2 * (int64_t)DR * DR * (1 + sR) : 0) + (hasB ? 2 * (int64_t)DR * DR * (1 + sL) : 0) +
            (hasW ? 2 * (int64_t)DP * DP * (1 + sL + sR) : 0);
 }
@@ -1205,8 +1322,17 @@ void small_evolve(const double* L, const double* R, const double* B, const doubl
                   int sL, int sR, int m, double tau, double tol, bool nonherm, double* x, StepDev* st,
                   hipStream_t s) {
     if (g_dry_run) return;
-    hipLaunchKernelGGL(k_small_evolve, dim3(1), dim3(SMALL_THREADS), 0, s, L, R, B, W, DL, DR, DP, sL, sR, m, tau,
-                       tol, nonherm ? 1 : 0, x, st);
+#define TTN_L(E, D)                                                                                                \
+    hipLaunchKernelGGL((k_small_evolve<E, D>), dim3(1), dim3(SMALL_THREADS), 0, s, L, R, B, W, DL, DR, DP, sL, sR, \
+                       m, tau, tol, nonherm ? 1 : 0, x, st)
+    const int n = DL * DR * DP;
+    if (n <= SMALL_DENSE_N)
+        TTN_L(2, true);
+    else if (n <= 256)
+        TTN_L(4, false);
+    else
+        TTN_L(16, false);
+#undef TTN_L
 }
 
 void lz_expm_combine(const double* V, int64_t S, int64_t n, double* out, const LanczosDev* lz,
