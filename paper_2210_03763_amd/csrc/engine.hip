@@ -1163,7 +1163,7 @@ void lanczos_expm(ttn_handle* h, const OpDesc& o, double* x, double tau) {
 // with R upper triangular, real positive diagonal; Q overwrites T, R -> Rout.
 // ---------------------------------------------------------------------------
 // With rinvh != nullptr also writes R^{-H} = L2^{-1} L1^{-1} (for the adjoint),
-// keeping L1^{-1} in l1inv (D x D scratch).
+// leaving L1^{-1} in l1inv (D x D scratch).
 void qr_toward(ttn_handle* h, int DL, int DR, int DP, double* Tv, int leg, double* Rout,
                double* rinvh = nullptr, double* l1inv = nullptr) {
     Ctx<double> c{h, nullptr};
@@ -1179,14 +1179,12 @@ void qr_toward(ttn_handle* h, int DL, int DR, int DP, double* Tv, int leg, doubl
     const int64_t Dpad = 16 * (int64_t)((D + 15) / 16);
     chk(h, h->cholwork, D <= 128 ? 2 * Dpad * Dpad : (int64_t)D * (D + 1) + 2 * (int64_t)D * 16, "cholesky work");
     leg_gram(c, leg, Tv, Tv, 0, h->G, 0, DL, DR, DP, 1);
-    chol_inv(h->G, D, h->Linv, h->R1, nullptr, h->cholwork, h->st, h->stream);
-    if (rinvh) {
-        chk(h, l1inv, 2 * (int64_t)D * D, "L1 inverse");
-        copy_d(h->Linv, l1inv, 2 * (int64_t)D * D, nullptr, h->stream);
-    }
-    leg_apply<double>(c, leg, h->Linv, 0, Tv, 0, h->Qtmp, 0, DL, DR, DP, 1, 0, true, false);
+    double* const x1 = rinvh ? l1inv : h->Linv;
+    chk(h, x1, 2 * (int64_t)D * D, "L1 inverse");
+    chol_inv(h->G, D, x1, h->R1, nullptr, h->cholwork, h->st, h->stream);
+    leg_apply<double>(c, leg, x1, 0, Tv, 0, h->Qtmp, 0, DL, DR, DP, 1, 0, true, false);
     leg_gram(c, leg, h->Qtmp, h->Qtmp, 0, h->G, 0, DL, DR, DP, 1);
-    chol_inv(h->G, D, h->Linv, h->R2, nullptr, h->cholwork, h->st, h->stream);
+    chol_inv(h->G, D, h->Linv, h->R2, h->R1, h->cholwork, h->st, h->stream);
     leg_apply<double>(c, leg, h->Linv, 0, h->Qtmp, 0, Tv, 0, DL, DR, DP, 1, 0, true, false);
     if (rinvh) {
         chk(h, rinvh, 2 * (int64_t)D * D, "R^-H");
@@ -1224,8 +1222,6 @@ void qr_toward(ttn_handle* h, int DL, int DR, int DP, double* Tv, int leg, doubl
     g.scm = 1;
     g.scn = D;
     c.run(g);
-    rdiag_min(Rout, D, h->st, h->stream);
-    (void)n;
 }
 
 // T (tensor of node v) <- Op on leg (via a temporary)

@@ -233,14 +233,13 @@ void gather_cols(const double* V, int n, const int* order, int k, double* out, h
 // weight 1 - kept / total in st->max_disc_bits
 void split_finish(const double* w, int n, int k, double* x, int64_t count, StepDev* st, hipStream_t s);
 
-// min over k of Re R[k][k] into st->min_rdiag_bits (R: D x D planar)
-void rdiag_min(const double* R, int D, StepDev* st, hipStream_t s);
 // Cholesky of a Hermitian D x D Gram matrix G (planar, column-major):
-// G = L L^H.  Writes Linv (lower, L^{-1}) and R = L^H (upper), or R = L^H * Rprev
-// when Rprev != nullptr (D > 128 only).  Sets st->bad on a non-positive pivot.
-// work: 2 Dp^2 doubles (Dp = 16 ceil(D / 16)) for D <= 128, else
-// D (D + 1) + 32 D.
-void chol_inv(const double* G, int D, double* Linv, double* R, const double* Rprev, double* work,
+// G = L L^H.  Writes Linv (lower, L^{-1}) and R = L^H (upper).  Rfirst: the R
+// of the gauge move's first factorization when this is its second (G near I);
+// min over k of R[k][k] Rfirst[k][k] then goes into st->min_rdiag_bits.  Sets
+// st->bad on a non-positive pivot.  work: 2 Dp^2 doubles (Dp = 16 ceil(D / 16))
+// for D <= 128, else D (D + 1) + 32 D.
+void chol_inv(const double* G, int D, double* Linv, double* R, const double* Rfirst, double* work,
               StepDev* st, hipStream_t s);
 
 // out[p] = sum_{l,r} a[l] b[r] T[l, r, p] (planar complex vectors); used for
