@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <initializer_list>
 
+#include "lanes.h"
 #include "ttn_internal.h"
 
 namespace ttn {
@@ -190,9 +191,24 @@ struct MfmaT<double> {
 //   WGK > 1: the block is WGK groups of WGM x WGN waves on the same tile; group
 // q takes every WGK-th k-tile from tile q, through LDS buffers of its own,
 // and the groups' sums meet in LDS once, in group order.
-template <typename R, int BM, int BN, int WGM, int WGN, int WGK, int MINB, int BK, bool AK, bool BKF, bool RAG = false>
+//   FUSE (sampling, FP64):
+// MFMA_OUTER: B is an outer product, formed as its tiles are staged:
+// B[k, n] = B1[k_in, n] x.f[k_out, n] (B1 through g's own strides; k_out strides
+// of 1 in f).
+// MFMA_NORMS: also x.norms[n][tm] = sum over the rows m of tile row tm of
+// |C[m, n]|^2 (one split, alpha = 1, beta = 0).
+constexpr int MFMA_PLAIN = 0, MFMA_OUTER = 1, MFMA_NORMS = 2;
+template <typename R>
+struct MfmaExtra {
+    const R* f = nullptr;
+    int64_t f_plane = 0, sfn = 0;
+    R* norms = nullptr;
+};
+template <typename R, int BM, int BN, int WGM, int WGN, int WGK, int MINB, int BK, bool AK, bool BKF,
+          bool RAG = false, int FUSE = MFMA_PLAIN>
 __global__ __launch_bounds__(64 * WGM * WGN * WGK, MINB) void k_cgemm_mfma(Gemm<R> g, int tilesM, int tilesN,
-                                                                          int splits, int kchunk, R* partial) {
+                                                                          int splits, int kchunk, R* partial,
+                                                                          MfmaExtra<R> x) {
     if (g.skip && *g.skip) return;
     constexpr int NT = 64 * WGM * WGN;   // threads of a group
     static_assert(WGK == 1 || !RAG, "K groups are for the aligned form");
@@ -310,8 +326,16 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, MINB) void k_cgemm_mfma(Gemm<
         }
 #pragma unroll
         for (int q = 0; q < QB; ++q) {
-            pb[0][q] = mB[q] * Bb[offB[q]];
-            pb[1][q] = (sb * mB[q]) * Bb[offB[q] + g.b_plane];
+            if constexpr (FUSE == MFMA_OUTER) {
+                const R* f = x.f + kout + x.sfn * (n0 + (mB[q] != R(0) ? (tid + NT * q) / BK : 0));
+                const R ar = mB[q] * Bb[offB[q]], ai = mB[q] * Bb[offB[q] + g.b_plane];
+                const R fr = f[0], fi = f[x.f_plane];
+                pb[0][q] = ar * fr - ai * fi;
+                pb[1][q] = ar * fi + ai * fr;
+            } else {
+                pb[0][q] = mB[q] * Bb[offB[q]];
+                pb[1][q] = (sb * mB[q]) * Bb[offB[q] + g.b_plane];
+            }
         }
     };
     auto stash = [&](int buf) {
@@ -414,6 +438,33 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, MINB) void k_cgemm_mfma(Gemm<
                     dst[REGS * NT] = c3[i][j][r] - c1[i][j][r] - c2[i][j][r];
                 }
         __syncthreads();
+    }
+    if constexpr (FUSE == MFMA_NORMS) {
+        static_assert(WGK == 1 && !RAG, "whole sums in one wave");
+        // rows past M are zero (masked on load): sums over the lanes of a row
+        // (m), then over the waves that share the columns
+        R* sums = lds;   // [WGM][BN]
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                R t = 0;
+#pragma unroll
+                for (int i = 0; i < TI; ++i) {
+                    const R re = c1[i][j][r] - c2[i][j][r], im = c3[i][j][r] - c1[i][j][r] - c2[i][j][r];
+                    t += re * re + im * im;
+                }
+                t = row_total(t);
+                if (lane % 16 == 0) sums[BN * (wave % WGM) + wn0 + 16 * j + MfmaT<R>::row(lane, r)] = t;
+            }
+        __syncthreads();
+        if (tid < BN && n0 + tid < g.N) {
+            R t = sums[tid];
+#pragma unroll
+            for (int w = 1; w < WGM; ++w) t += sums[BN * w + tid];
+            x.norms[(int64_t)(n0 + tid) * tilesM + tm] = t;
+        }
     }
     const int64_t MN = (int64_t)g.M * g.N;
     const int nbatch = g.B1 * g.B2;
@@ -981,7 +1032,7 @@ void launch_ragged(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, bool 
     if (info) *info = CgemmInfo{2, splits};
 #define TTN_RAG_LAUNCH(bt, minb, ak, bk)                                                                       \
     hipLaunchKernelGGL((k_cgemm_mfma<R, bt, bt, 2, 2, 1, minb, 16, ak, bk, true>), grid, dim3(256), 0, s, g, tilesM, \
-                       tilesN, splits, kchunk, part)
+                       tilesN, splits, kchunk, part, MfmaExtra<R>{})
 #define TTN_RAG_LAUNCHES(bt, minb)             \
     do {                                       \
         if (a_k && b_k)                        \
@@ -1014,57 +1065,71 @@ void launch_ragged(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, bool 
 // operators 29.7 / 15.6, 34.2 / 26.5, 51.0 / 46.2; stack of 8 over 64^3 25.8 /
 // 25.1, over 128^3 281 / 268; 96^3 sum over 8 201 / 116; 32 x 32 x 128 node,
 // parent-leg stack of 8 36.5 / 24.7.  FP32, 64^3 sum over 4: 21.7 / 11.4.
+struct AlignedPlan {
+    bool small, big;
+    int groups, splits, kchunk;
+    int64_t blocks;
+};
+
 template <typename R>
-void launch_aligned(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, bool a_k, bool b_k, CgemmInfo* info) {
+AlignedPlan plan_aligned(const Gemm<R>& g, const GemmScratch& ws) {
     const int K = g.Kin * g.Kout, kt = K / 16;
     const int64_t t32 = tile_count(g, 32, 32), t64 = tile_count(g, 64, 64), t128 = tile_count(g, 128, 64);
     // 32 x 32 tiles reach 0.87 of the larger ones' rate (FP32: 0.8) where both fill
     // the chip (128^3: 305 / 268 us)
     const double r32 = sizeof(R) == 8 ? 0.87 : 0.8;
-    // few outputs and a long K, split either way (128 x 128 outputs, K = 16384: 53.7 us
-    // with 32 x 32 tiles, 48.4 with 64 x 64; half the flops: 31.3 / 32.2)
-    const bool deep = t32 < 256 && t64 * (kt / 8) >= 512;
-    const bool small = !deep && (t64 < 256 || padded(g.M, g.N, 32, 32) / r32 < padded(g.M, g.N, 64, 64));
-    const bool big = !small && sizeof(R) == 8 && K >= 512 && t128 >= 256 &&
-                     padded(g.M, g.N, 128, 64) <= padded(g.M, g.N, 64, 64);
-    const int bm = small ? 32 : big ? 128 : 64, bn = small ? 32 : 64;
-    const int64_t tiles = small ? t32 : big ? t128 : t64;
-    int splits = big ? 1 : split_factor(g, ws, tiles, kt, small ? 256 : 512, small || deep ? 8 : 32);
-    const int kchunk = (kt + splits - 1) / splits * 16;
-    splits = (K + kchunk - 1) / kchunk;
-    const int64_t blocks = tiles * splits;
-    const int groups = !small || kchunk < 128 ? 1 : blocks <= 256 ? 4 : blocks <= 512 ? 2 : 1;
-    const int tilesM = (g.M + bm - 1) / bm, tilesN = (g.N + bn - 1) / bn;
-    const dim3 grid((unsigned)blocks);
-    R* part = (R*)ws.partial;
-    if (info) *info = CgemmInfo{2, splits};
-#define TTN_MFMA_LAUNCH(bm, bn, wgm, wgn, wgk, minb, ak, bk)                                                        \
-    hipLaunchKernelGGL((k_cgemm_mfma<R, bm, bn, wgm, wgn, wgk, minb, 16, ak, bk>), grid, dim3(64 * wgm * wgn * wgk), \
-                       0, s, g, tilesM, tilesN, splits, kchunk, part)
-#define TTN_MFMA_LAUNCHES(bm, bn, wgm, wgn, wgk, minb)                        \
-    do {                                                                      \
-        if (a_k && b_k)                                                       \
-            TTN_MFMA_LAUNCH(bm, bn, wgm, wgn, wgk, minb, true, true);         \
-        else if (a_k)                                                         \
-            TTN_MFMA_LAUNCH(bm, bn, wgm, wgn, wgk, minb, true, false);        \
-        else if (b_k)                                                         \
-            TTN_MFMA_LAUNCH(bm, bn, wgm, wgn, wgk, minb, false, true);        \
-        else                                                                  \
-            TTN_MFMA_LAUNCH(bm, bn, wgm, wgn, wgk, minb, false, false);       \
+    // few outputs and a long K: 64 x 64 tiles split to 512 blocks, where the 32 x 32
+    // ones would be split too (128 x 128 outputs, K = 16384: 53.7 us with 32 x 32
+    // tiles, 48.4 with 64 x 64; half the flops: 31.3 / 32.2) or K is so long that
+    // the partial sums weigh little (64 x 8192 outputs, K = 4096: 353 / 268; 64 x 4096,
+    // K = 2048: 84.9 / 77.6; K = 1024: 46.2 / 51)
+    const bool deep = t64 < 256 && t64 * (kt / 8) >= 512 && (t32 < 256 || kt >= 128);
+    AlignedPlan p;
+    p.small = !deep && (t64 < 256 || padded(g.M, g.N, 32, 32) / r32 < padded(g.M, g.N, 64, 64));
+    p.big = !p.small && sizeof(R) == 8 && K >= 512 && t128 >= 256 &&
+            padded(g.M, g.N, 128, 64) <= padded(g.M, g.N, 64, 64);
+    const int64_t tiles = p.small ? t32 : p.big ? t128 : t64;
+    p.splits = p.big ? 1 : split_factor(g, ws, tiles, kt, p.small ? 256 : 512, p.small || deep ? 8 : 32);
+    p.kchunk = (kt + p.splits - 1) / p.splits * 16;
+    p.splits = (K + p.kchunk - 1) / p.kchunk;
+    p.blocks = tiles * p.splits;
+    p.groups = !p.small || p.kchunk < 128 ? 1 : p.blocks <= 256 ? 4 : p.blocks <= 512 ? 2 : 1;
+    return p;
+}
+
+#define TTN_MFMA_LAUNCH(bm, bn, wgm, wgn, wgk, minb, ak, bk, fuse)                                                   \
+    hipLaunchKernelGGL((k_cgemm_mfma<R, bm, bn, wgm, wgn, wgk, minb, 16, ak, bk, false, fuse>),                      \
+                       dim3((unsigned)p.blocks), dim3(64 * wgm * wgn * wgk), 0, s, g, (g.M + bm - 1) / bm,           \
+                       (g.N + bn - 1) / bn, p.splits, p.kchunk, (R*)ws.partial, x)
+
+template <typename R>
+void launch_aligned(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, bool a_k, bool b_k, CgemmInfo* info) {
+    const AlignedPlan p = plan_aligned(g, ws);
+    const MfmaExtra<R> x;
+    if (info) *info = CgemmInfo{2, p.splits};
+#define TTN_MFMA_LAUNCHES(bm, bn, wgm, wgn, wgk, minb)                                \
+    do {                                                                              \
+        if (a_k && b_k)                                                               \
+            TTN_MFMA_LAUNCH(bm, bn, wgm, wgn, wgk, minb, true, true, MFMA_PLAIN);     \
+        else if (a_k)                                                                 \
+            TTN_MFMA_LAUNCH(bm, bn, wgm, wgn, wgk, minb, true, false, MFMA_PLAIN);    \
+        else if (b_k)                                                                 \
+            TTN_MFMA_LAUNCH(bm, bn, wgm, wgn, wgk, minb, false, true, MFMA_PLAIN);    \
+        else                                                                          \
+            TTN_MFMA_LAUNCH(bm, bn, wgm, wgn, wgk, minb, false, false, MFMA_PLAIN);   \
     } while (0)
-    if (groups == 4)
+    if (p.groups == 4)
         TTN_MFMA_LAUNCHES(32, 32, 2, 2, 4, 1);
-    else if (groups == 2)
+    else if (p.groups == 2)
         TTN_MFMA_LAUNCHES(32, 32, 2, 2, 2, 2);
-    else if (small)
+    else if (p.small)
         TTN_MFMA_LAUNCHES(32, 32, 2, 2, 1, 4);
-    else if (!big)
+    else if (!p.big)
         TTN_MFMA_LAUNCHES(64, 64, 2, 4, 1, 2);
     else if constexpr (sizeof(R) == 8)
         TTN_MFMA_LAUNCHES(128, 64, 4, 4, 1, 1);
 #undef TTN_MFMA_LAUNCHES
-#undef TTN_MFMA_LAUNCH
-    if (splits > 1) splitk_reduce(g, splits, (const R*)ws.partial, s);
+    if (p.splits > 1) splitk_reduce(g, p.splits, (const R*)ws.partial, s);
 }
 
 // Launch of k_cgemm_split with bm x bn tiles (128 x 128, 64 x 128, 128 x 64)
@@ -1280,6 +1345,51 @@ bool cgemm(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, char* why, in
     if (ev1) (void)hipEventRecord(ev1, s);
     return true;
 }
+
+// Sampling's contractions with the pass beside them folded in (k_cgemm_mfma's
+// FUSE).  Both take whole k-tiles and the layouts they state; the caller asks
+// cgemm_fusable first and checks g as for cgemm.
+bool cgemm_fusable(const Gemm<double>& g) { return aligned_form(g) && g.B1 * g.B2 == 1; }
+
+// C[m, n] = sum A[m, (kin, kout)] B[kin, n] f[kout, n]; A and B contiguous along
+// k_in, f planar, contiguous along k_out
+void cgemm_outer(const Gemm<double>& g, const double* f, int64_t f_plane, int64_t sfn, const GemmScratch& ws,
+                 hipStream_t s) {
+    typedef double R;
+    if (g_dry_run || g.M <= 0 || g.N <= 0) return;
+    const AlignedPlan p = plan_aligned(g, ws);
+    MfmaExtra<R> x;
+    x.f = f;
+    x.f_plane = f_plane;
+    x.sfn = sfn;
+    if (p.groups == 4)
+        TTN_MFMA_LAUNCH(32, 32, 2, 2, 4, 1, true, true, MFMA_OUTER);
+    else if (p.groups == 2)
+        TTN_MFMA_LAUNCH(32, 32, 2, 2, 2, 2, true, true, MFMA_OUTER);
+    else if (p.small)
+        TTN_MFMA_LAUNCH(32, 32, 2, 2, 1, 4, true, true, MFMA_OUTER);
+    else if (!p.big)
+        TTN_MFMA_LAUNCH(64, 64, 2, 4, 1, 2, true, true, MFMA_OUTER);
+    else
+        TTN_MFMA_LAUNCH(128, 64, 4, 4, 1, 1, true, true, MFMA_OUTER);
+    if (p.splits > 1) splitk_reduce(g, p.splits, (const R*)ws.partial, s);
+}
+
+// C = A B (A contiguous along m, B along k_in) and norms[n][tm] = sum over the
+// 64 rows of tile row tm of |C[m, n]|^2
+void cgemm_norms(const Gemm<double>& g, double* norms, hipStream_t s) {
+    typedef double R;
+    if (g_dry_run || g.M <= 0 || g.N <= 0) return;
+    const GemmScratch ws;
+    AlignedPlan p{};
+    p.splits = 1;
+    p.kchunk = g.Kin * g.Kout;
+    p.blocks = tile_count(g, 64, 64);
+    MfmaExtra<R> x;
+    x.norms = norms;
+    TTN_MFMA_LAUNCH(64, 64, 2, 4, 1, 2, false, true, MFMA_NORMS);
+}
+#undef TTN_MFMA_LAUNCH
 
 template bool cgemm_check<double>(const Gemm<double>&, const GemmScratch&, char*, int);
 template bool cgemm_check<float>(const Gemm<float>&, const GemmScratch&, char*, int);

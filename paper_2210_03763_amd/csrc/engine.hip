@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "../../include/ttn.h"
+#include "lanes.h"
 #include "ttn_internal.h"
 
 using namespace ttn;
@@ -428,6 +429,31 @@ struct Ctx {
         held_flops = 0;
     }
 
+    // whether to record the launch of g, and the events of its window
+    bool window(const Gemm<R>& g, int& idx, hipEvent_t& e0, hipEvent_t& e1) {
+        if (!h->prof || h->dry || g.M <= 0 || g.N <= 0) return false;
+        idx = events();
+        if (idx >= 0) {
+            e0 = h->ev_pool[idx];
+            e1 = h->ev_pool[idx + 1];
+        }
+        return true;
+    }
+    // a contraction with a launch of its own (checked and recorded as run does)
+    template <typename F>
+    void run_fused(const Gemm<R>& g, F launch) {
+        char why[256];
+        flush();
+        if (!cgemm_check<R>(g, h->gs, why, sizeof(why)))
+            throw StatusError{TTN_EINVAL, std::string("launch extent check failed: ") + why};
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        int idx = -1;
+        const bool rec = window(g, idx, e0, e1);
+        if (e0) (void)hipEventRecord(e0, h->stream);
+        launch();
+        if (e1) (void)hipEventRecord(e1, h->stream);
+        if (rec) record(8.0 * g.M * g.N * (double)g.Kin * g.Kout, 1, 2, idx);
+    }
     void run(const Gemm<R>& g) {
         char why[256];
         const double fl = 8.0 * g.M * g.N * (double)g.Kin * g.Kout * (double)g.B1 * g.B2 - flops_less;
@@ -453,15 +479,8 @@ struct Ctx {
         }
         flush();
         hipEvent_t e0 = nullptr, e1 = nullptr;
-        const bool rec = h->prof && !h->dry && g.M > 0 && g.N > 0;
         int idx = -1;
-        if (rec) {
-            idx = events();
-            if (idx >= 0) {
-                e0 = h->ev_pool[idx];
-                e1 = h->ev_pool[idx + 1];
-            }
-        }
+        const bool rec = window(g, idx, e0, e1);
         Gemm<R> gg = g;
         if (sizeof(R) == 4 && h->split_bf16) gg.split = 1;
         CgemmInfo info;

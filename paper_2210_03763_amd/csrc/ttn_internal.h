@@ -72,6 +72,13 @@ bool cgemm(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, char* why, in
 template <typename R>
 bool cgemm_check(const Gemm<R>& g, const GemmScratch& ws, char* why, int whylen);
 
+// Contractions of the sampling walk with the pass beside them folded in (see
+// contract.hip); usable when cgemm_fusable(g).
+bool cgemm_fusable(const Gemm<double>& g);
+void cgemm_outer(const Gemm<double>& g, const double* f, int64_t f_plane, int64_t sfn, const GemmScratch& ws,
+                 hipStream_t s);
+void cgemm_norms(const Gemm<double>& g, double* norms, hipStream_t s);
+
 // Independent short contractions (cgemm_groupable: those that cgemm would give
 // to the wave-sliced kernel without split K) in one launch, for sequences
 // whose cost is their launches.  The caller has checked their extents and that

@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
 TILES = [(48, 50, 50, 0, 7, 1), (64, 64, 80, 0, 3, 1), (48, 100, 90, 1, 2, 0), (100, 48, 90, 1, 2, 1),
          (20, 20, 64, 2, 40, 1), (64, 150, 120, 0, 1, 0), (64, 128, 130, 0, 16, 1), (128, 130, 128, 0, 4, 1),
          (40, 33, 32, 2, 9, 0), (16, 67, 96, 2, 4, 1),
-         (100, 1, 128, 2, 128, 1)]
+         (100, 1, 128, 2, 128, 1), (48, 64, 96, 1, 32, 1)]
 
 
 def _planar(z, dtype):
