@@ -1314,15 +1314,8 @@ void krylov_unchunk(const double* V, int64_t S, int64_t n, int slots, double* ou
 // conversions / copies
 // ---------------------------------------------------------------------------
 namespace {
-__global__ void k_d2f(const double* x, float* y, int64_t c, const int* skip) {
-    if (skip && *skip) return;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < c;
-         i += (int64_t)gridDim.x * blockDim.x)
-        y[i] = (float)x[i];
-}
-
 // several conversions in one launch: the concatenated index space of the
-// arrays, each element converted exactly as by k_d2f
+// arrays
 __global__ void k_d2f_batch(D2FBatch b, int64_t total, const int* skip) {
     if (skip && *skip) return;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
@@ -1336,12 +1329,6 @@ __global__ void k_d2f_batch(D2FBatch b, int64_t total, const int* skip) {
         const int D = b.eye[k];
         b.y[k][off] = D ? ((off < (int64_t)D * D && off % (D + 1) == 0) ? 1.0f : 0.0f) : (float)b.x[k][off];
     }
-}
-__global__ void k_f2d(const float* x, double* y, int64_t c, const int* skip) {
-    if (skip && *skip) return;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < c;
-         i += (int64_t)gridDim.x * blockDim.x)
-        y[i] = (double)x[i];
 }
 __global__ void k_copy(const double* x, double* y, int64_t c, const int* skip) {
     if (skip && *skip) return;
@@ -1403,10 +1390,6 @@ void sum_mats(const double* src, int D, int count, double* dst, hipStream_t s) {
     hipLaunchKernelGGL(k_sum_mats, dim3(grid_for(2 * D2)), dim3(256), 0, s, src, D2, count, dst);
 }
 
-void convert_d2f(const double* x, float* y, int64_t count, const int* skip, hipStream_t s) {
-    if (g_dry_run) return;
-    hipLaunchKernelGGL(k_d2f, dim3(grid_for(count)), dim3(256), 0, s, x, y, count, skip);
-}
 void convert_d2f_many(std::initializer_list<D2FItem> items, const int* skip, hipStream_t s) {
     if (g_dry_run) return;
     D2FBatch b{};
@@ -1426,10 +1409,6 @@ void convert_d2f_many(std::initializer_list<D2FItem> items, const int* skip, hip
         total += it.count;
     }
     if (b.n > 0) hipLaunchKernelGGL(k_d2f_batch, dim3(grid_for(total)), dim3(256), 0, s, b, total, skip);
-}
-void convert_f2d(const float* x, double* y, int64_t count, const int* skip, hipStream_t s) {
-    if (g_dry_run) return;
-    hipLaunchKernelGGL(k_f2d, dim3(grid_for(count)), dim3(256), 0, s, x, y, count, skip);
 }
 void copy_d(const double* x, double* y, int64_t count, const int* skip, hipStream_t s) {
     if (g_dry_run) return;

@@ -194,7 +194,6 @@ void small_evolve(const double* L, const double* R, const double* B, const doubl
                   hipStream_t s);
 
 // conversions and copies
-void convert_d2f(const double* x, float* y, int64_t count, const int* skip, hipStream_t s);
 // several FP64 -> FP32 conversions in one launch (null or empty items
 // skipped); an item with eye = D > 0 writes the planar D x D identity
 // (count 2 D^2) instead of converting x
@@ -213,7 +212,6 @@ struct D2FBatch {
     int n;
 };
 void convert_d2f_many(std::initializer_list<D2FItem> items, const int* skip, hipStream_t s);
-void convert_f2d(const float* x, double* y, int64_t count, const int* skip, hipStream_t s);
 void copy_d(const double* x, double* y, int64_t count, const int* skip, hipStream_t s);
 void transpose_c(const double* x, double* y, int rows, int cols, hipStream_t s);
 void fill_zero_d(double* y, int64_t count, hipStream_t s);
