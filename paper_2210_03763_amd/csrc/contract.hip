@@ -552,9 +552,9 @@ __device__ inline void wave_tile(const Gemm<R>& g, int64_t bid, int tilesM, int 
     const int kb0 = sp * kbper, kb1 = min((K + 15) / 16, kb0 + kbper);
     const int per = (kb1 - kb0 + WK - 1) / WK;
     const int wb0 = kb0 + wave * per, wb1 = min(kb1, wb0 + per);
-    // rows past the edge read row 0 (their outputs are not stored)
-    const R* A = g.A + b1 * g.sab1 + b2 * g.sab2 + (m0 + c16 < g.M ? (int64_t)(m0 + c16) * g.sam : 0);
-    const R* B = g.B + b1 * g.sbb1 + b2 * g.sbb2 + (n0 + c16 < g.N ? (int64_t)(n0 + c16) * g.sbn : 0);
+    // rows past the edge read the tile's first (their outputs are not stored)
+    const R* A = g.A + b1 * g.sab1 + b2 * g.sab2 + (int64_t)(m0 + c16 < g.M ? m0 + c16 : m0) * g.sam;
+    const R* B = g.B + b1 * g.sbb1 + b2 * g.sbb2 + (int64_t)(n0 + c16 < g.N ? n0 + c16 : n0) * g.sbn;
     const R sa = g.conjA ? R(-1) : R(1), sb = g.conjB ? R(-1) : R(1);
     struct Frag {
         R ar[4], ai[4], br[4], bi[4];
@@ -1234,6 +1234,16 @@ template <typename R>
 bool cgemm_groupable(const Gemm<R>& g, const GemmScratch& ws) {
     const bool any = g.M > 0 && g.N > 0 && g.Kin > 0 && g.Kout > 0 && g.B1 > 0 && g.B2 > 0;
     return any && takes_wave(g) && wave_splits(g, ws) == 1;
+}
+
+// A wave-sliced launch whose tiles span all the rows (C over A: columns) of its
+// outputs and do not split K: every workgroup has then read, when it writes
+// (after its last product), all that its own outputs replace, and no other
+// workgroup reads that.  Wider legs belong to large tensors, where the copy
+// weighs little beside the product.
+bool cgemm_in_place(const Gemm<double>& g, const GemmScratch& ws, bool over_a) {
+    if (g.M <= 0 || g.N <= 0 || g.Kin * g.Kout <= 0) return false;
+    return takes_wave(g) && (over_a ? g.N : g.M) <= 16 && wave_splits(g, ws) == 1;
 }
 
 template <typename R>

@@ -92,7 +92,7 @@ struct ttn_handle {
     std::vector<int> leaf_site;
     std::vector<double> V;   // N x N
     // device state
-    std::vector<double*> T, up, dn, vLR, vRL;
+    std::vector<double*> T, up, dn, vLR, vRL, vB;   // vB = diag(1, vRL)
     double* leafblk = nullptr;
     int* d_leaf_site = nullptr;
     // scratch
@@ -268,6 +268,7 @@ void plan(ttn_handle* h, Bump& b) {
     h->dn.assign(nn, nullptr);
     h->vLR.assign(nn, nullptr);
     h->vRL.assign(nn, nullptr);
+    h->vB.assign(nn, nullptr);
     h->nmax = 0;
     h->stack_max = 0;
     h->Dmax = h->d;
@@ -290,6 +291,7 @@ void plan(ttn_handle* h, Bump& b) {
         const int sL = sites_left(h, v);
         h->vLR[v] = b.take<double>(2 * (int64_t)sL * sL);
         h->vRL[v] = b.take<double>(2 * (int64_t)sL * sL);
+        h->vB[v] = b.take<double>(2 * (int64_t)(1 + sL) * (1 + sL));
     }
     // bond stacks (sites below v, size DP^2) are bounded by stack_max as well
     for (int v = 0; v < nn; ++v)
@@ -550,12 +552,11 @@ void sync(ttn_handle* h) {
 // 0 for a shared X) writing nops outputs (stride sy).  trans: use Op^T;
 // conj: use conj(Op).
 template <typename R>
-void leg_apply(Ctx<R>& c, int leg, const R* Op, int64_t so, const R* X, int64_t sx, R* Y, int64_t sy,
-               int DL, int DR, int DP, int nops, int beta, bool conj = false, bool trans = false) {
+Gemm<R> leg_gemm(int leg, const R* Op, int64_t so, const R* X, int64_t sx, R* Y, int64_t sy, int DL, int DR, int DP,
+                 int nops, int beta, bool conj, bool trans) {
     const int64_t n = (int64_t)DL * DR * DP;
     Gemm<R> g;
     g.beta = beta;
-    g.skip = c.skip;
     if (leg == 0) {
         const int D = DL;
         g.M = D;
@@ -626,7 +627,31 @@ void leg_apply(Ctx<R>& c, int leg, const R* Op, int64_t so, const R* X, int64_t 
         g.scb1 = sy;
         g.B1 = nops;
     }
+    return g;
+}
+template <typename R>
+void leg_apply(Ctx<R>& c, int leg, const R* Op, int64_t so, const R* X, int64_t sx, R* Y, int64_t sy,
+               int DL, int DR, int DP, int nops, int beta, bool conj = false, bool trans = false) {
+    Gemm<R> g = leg_gemm<R>(leg, Op, so, X, sx, Y, sy, DL, DR, DP, nops, beta, conj, trans);
+    g.skip = c.skip;
     c.run(g);
+}
+
+// X <- Op X on leg `leg`: in place where the launch lets a workgroup read all
+// that its outputs replace before it writes them, else through tmp
+void leg_apply_inplace(ttn_handle* h, Ctx<double>& c, int leg, const double* Op, double* X, int DL, int DR, int DP,
+                       bool conj, bool trans, double* tmp) {
+    Gemm<double> g = leg_gemm<double>(leg, Op, 0, X, 0, X, 0, DL, DR, DP, 1, 0, conj, trans);
+    g.skip = c.skip;
+    if (cgemm_in_place(g, h->gs, leg != 0)) {
+        c.run(g);
+        return;
+    }
+    const int64_t n = (int64_t)DL * DR * DP;
+    chk(h, tmp, 2 * n, "scratch of a leg product");
+    g.C = tmp;
+    c.run(g);
+    copy_d(tmp, X, 2 * n, c.skip, h->stream);
 }
 
 // Y (+)= sum_{k<cnt} Op_k on leg of X_k (operator slots stride so, tensor slots
@@ -842,11 +867,28 @@ struct OpDesc {
     const Op2* e2 = nullptr;
 };
 
-// Bstk = [H_R, A_1..A_sL] for node v
+// Bstk = [H_R, A_1..A_sL] for node v: the stack [H_R, N_1..N_sR] times diag(1, V),
+// one launch where a copy of H_R beside the sums took two
 void prepare_B(ttn_handle* h, Ctx<double>& c, int v, const double* Rb, int DR, int sL, int sR) {
     const int64_t D2 = (int64_t)DR * DR;
-    copy_d(Rb, h->Bstk, 2 * D2, c.skip, h->stream);
-    vsum_stack(c, Rb, DR, sR, h->vRL[v], sL, h->Bstk + 2 * D2);
+    Gemm<double> g;
+    g.skip = c.skip;
+    g.M = (int)D2;
+    g.N = 1 + sL;
+    g.Kin = 1 + sR;
+    g.A = Rb;
+    g.a_plane = D2;
+    g.sam = 1;
+    g.sak = 2 * D2;
+    g.B = h->vB[v];
+    g.b_plane = (int64_t)(1 + sR) * (1 + sL);
+    g.sbk = 1;
+    g.sbn = 1 + sR;
+    g.C = h->Bstk;
+    g.c_plane = D2;
+    g.scm = 1;
+    g.scn = 2 * D2;
+    c.run(g);
 }
 
 OpDesc node_op(ttn_handle* h, Ctx<double>& c, int v) {
@@ -1243,14 +1285,10 @@ void qr_toward(ttn_handle* h, int DL, int DR, int DP, double* Tv, int leg, doubl
     c.run(g);
 }
 
-// T (tensor of node v) <- Op on leg (via a temporary)
+// T (tensor of node v) <- Op on leg
 void absorb(ttn_handle* h, int v, int leg, const double* Op, bool trans) {
     Ctx<double> c{h, nullptr};
-    const int64_t n = nsize(h, v);
-    chk(h, h->Ttmp, 2 * n, "absorb scratch");
-    leg_apply<double>(c, leg, Op, 0, h->T[v], 0, h->Ttmp, 0, h->DL[v], h->DR[v], h->DP[v], 1, 0, false,
-                      trans);
-    copy_d(h->Ttmp, h->T[v], 2 * n, nullptr, h->stream);
+    leg_apply_inplace(h, c, leg, Op, h->T[v], h->DL[v], h->DR[v], h->DP[v], false, trans, h->Ttmp);
 }
 
 // Up environment of the link above v from its isometry Q: block
@@ -2100,15 +2138,19 @@ void build_couplings(ttn_handle* h, const double* pos) {
     for (int v = 0; v < h->n_nodes; ++v) {
         const int sL = sites_left(h, v), f = h->sfirst[v];
         std::vector<double> lr(2 * (size_t)sL * sL, 0.0), rl(2 * (size_t)sL * sL, 0.0);
+        std::vector<double> vb(2 * (size_t)(1 + sL) * (1 + sL), 0.0);
         for (int i = 0; i < sL; ++i)
             for (int j = 0; j < sL; ++j) {
                 const int si = h->leaf_site[f + i], sj = h->leaf_site[f + sL + j];
                 const double val = h->V[(size_t)si * h->N + sj];
                 lr[i + (size_t)sL * j] = val;   // V[i in L][j in R], column-major i + sL j
                 rl[j + (size_t)sL * i] = val;   // V[j in R][i in L] transposed layout
+                vb[j + 1 + (size_t)(1 + sL) * (i + 1)] = val;
             }
+        vb[0] = 1.0;
         h2d(h, h->vLR[v], lr.data(), lr.size() * sizeof(double));
         h2d(h, h->vRL[v], rl.data(), rl.size() * sizeof(double));
+        h2d(h, h->vB[v], vb.data(), vb.size() * sizeof(double));
         sync(h);
     }
 }

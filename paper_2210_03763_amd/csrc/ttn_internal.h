@@ -72,6 +72,10 @@ bool cgemm(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, char* why, in
 template <typename R>
 bool cgemm_check(const Gemm<R>& g, const GemmScratch& ws, char* why, int whylen);
 
+// Whether cgemm may write C over the operand it replaces: over A (same rows m, C's
+// n on A's k) or over B (same columns n, C's m on B's k), K = N or M.
+bool cgemm_in_place(const Gemm<double>& g, const GemmScratch& ws, bool over_a);
+
 // Contractions of the sampling walk with the pass beside them folded in (see
 // contract.hip); usable when cgemm_fusable(g).
 bool cgemm_fusable(const Gemm<double>& g);
