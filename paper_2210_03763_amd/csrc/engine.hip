@@ -1231,6 +1231,12 @@ void qr_toward(ttn_handle* h, int DL, int DR, int DP, double* Tv, int leg, doubl
     const int D = leg == 0 ? DL : (leg == 1 ? DR : DP);
     const int64_t n = (int64_t)DL * DR * DP;
     chk(h, Tv, 2 * n, "qr tensor");
+    if (qr_small_fits(DL, DR, DP, leg)) {
+        chk(h, Rout, 2 * (int64_t)D * D, "R out");
+        if (rinvh) chk(h, rinvh, 2 * (int64_t)D * D, "R^-H");
+        qr_small(Tv, DL, DR, DP, leg, Rout, rinvh, h->st, h->stream);
+        return;
+    }
     chk(h, h->Qtmp, 2 * n, "qr scratch");
     chk(h, h->G, 2 * (int64_t)D * D, "gram");
     chk(h, h->Linv, 2 * (int64_t)D * D, "Linv");

@@ -2255,7 +2255,157 @@ __global__ __launch_bounds__(CB_THREADS) void k_chol_blk(const double* G, int D,
     if (tid == 0 && s_bad) atomicExch(&st->bad, 1);
 }
 
+// A whole gauge move of a small tensor in one workgroup: Gram matrix, Cholesky
+// factor and inverse, product, twice (CholeskyQR2), and R = R2 R1.  The tensor is
+// D columns of M rows (row index rest = e % s + s (e / (s D)) of element e, column
+// (e / s) % D), D <= 16, M <= QRS_ROWS, held in LDS as X[rest][a]; Gram matrices and
+// products run on the FP64 matrix cores (16 x 16 tiles, D padded), the waves'
+// partial Gram matrices meet in LDS in wave order.
+// Bound by the chain of its passes; as seven launches (two of them the
+// factorizations) it was bound by those.  Measured, us per move (summed launch
+// times / this): 9 x 9 x 16 node 38 / 20, 16 x 16 x 16 node 43 / 25.
+constexpr int QRS_ROWS = 256, QRS_THREADS = 512, QRS_WAVES = QRS_THREADS / 64, QRS_LD = CB + 1;
+__global__ __launch_bounds__(QRS_THREADS) void k_qr_small(double* T, int n, int D, int s, double* Rout, double* rinvh,
+                                                         StepDev* st) {
+    __shared__ double2 X[QRS_ROWS * QRS_LD];
+    __shared__ double2 part[QRS_WAVES * 256];
+    __shared__ double g_re[256], g_im[256];    // Gram matrix, then its factor L
+    __shared__ double l_re[2][256], l_im[2][256];   // L^{-1} of both passes
+    __shared__ double2 fac[2][256];            // R of both passes, [k + 16 a]
+    __shared__ double dinv[CB], cs[8 * CB], sum[QRS_WAVES + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c16 = lane & 15, q4 = lane >> 4;
+    const int M = n / D, Mp = (M + 15) / 16 * 16;
+    // the tensor, with zero rows and columns up to whole tiles
+    if (Mp * D != n || D < CB)
+        for (int e = tid; e < Mp * QRS_LD; e += QRS_THREADS) X[e] = make_double2(0.0, 0.0);
+    __syncthreads();
+    auto place = [&](int e) {
+        const int h = e / s, lo = e - h * s, hi = h / D;
+        return (lo + s * hi) * QRS_LD + (h - hi * D);
+    };
+    for (int e = tid; e < n; e += QRS_THREADS) X[place(e)] = make_double2(T[e], T[n + e]);
+    __syncthreads();
+    int bad = 0;
+    for (int pass = 0; pass < 2; ++pass) {
+        // G = X^H X: wave w takes rows 4 (w + 8 i) ..
+        cb_d4 re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+        for (int k = 4 * wave; k < Mp; k += 4 * QRS_WAVES) {
+            const double2 x = X[(k + q4) * QRS_LD + c16];
+            re = cb_mfma(x.x, x.x, re);
+            im = cb_mfma(x.y, x.x, im);
+            re = cb_mfma(x.y, x.y, re);
+            im = cb_mfma(x.x, -x.y, im);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[256 * wave + 64 * r + lane] = make_double2(re[r], im[r]);
+        __syncthreads();
+        double acc = 0.0;   // |G - 1|_F^2
+        if (tid < 256) {
+            double2 t = part[tid];
+#pragma unroll
+            for (int w = 1; w < QRS_WAVES; ++w) {
+                t.x += part[256 * w + tid].x;
+                t.y += part[256 * w + tid].y;
+            }
+            const int a = tid & 15, b = ((tid & 63) >> 4) + 4 * (tid >> 6);
+            if (a == b && a >= D) t.x = 1.0;
+            g_re[a + CB * b] = t.x;
+            g_im[a + CB * b] = t.y;
+            acc = a > b ? 2.0 * (t.x * t.x + t.y * t.y) : a == b ? (t.x - 1.0) * (t.x - 1.0) : 0.0;
+        }
+        acc = block_sum_all(acc, sum);
+        const int a = tid & 15, b = (tid >> 4) & 15, ab = a + CB * b, ba = b + CB * a;
+        if (pass == 1 && acc <= CHOL_NEAR) {
+            if (tid < 256) {   // L = 1 + E below the diagonal, half of it on it
+                const double dh = 0.5 * (g_re[ab] - 1.0);
+                l_re[1][ab] = a > b ? -g_re[ab] : a == b ? 1.0 - dh : 0.0;
+                l_im[1][ab] = a > b ? -g_im[ab] : 0.0;
+                fac[1][ab] = a < b ? make_double2(g_re[ba], -g_im[ba]) : make_double2(a == b ? 1.0 + dh : 0.0, 0.0);
+            }
+        } else {
+            if (wave == 0) {
+                cb_chol_diag(g_re, g_im, dinv, cs, lane, bad);
+                cb_wave_sync();
+                cb_inv_diag(g_re, g_im, dinv, l_re[pass], l_im[pass], CB, cs, lane);
+            }
+            __syncthreads();
+            if (tid < 256) fac[pass][ab] = a <= b ? make_double2(g_re[ba], -g_im[ba]) : make_double2(0.0, 0.0);
+        }
+        __syncthreads();
+        // X <- X L^{-H}, a 16-row tile a wave
+        const double* lr = l_re[pass];
+        const double* li = l_im[pass];
+        for (int t = wave; t < Mp / 16; t += QRS_WAVES) {
+            double2* row = X + (16 * t + c16) * QRS_LD;
+            cb_d4 yr = {0, 0, 0, 0}, yi = {0, 0, 0, 0};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int k = 4 * j + q4;
+                const double2 x = row[k];
+                const double br = lr[c16 + CB * k], bi = -li[c16 + CB * k];
+                yr = cb_mfma(br, x.x, yr);
+                yi = cb_mfma(bi, x.x, yi);
+                yr = cb_mfma(-bi, x.y, yr);
+                yi = cb_mfma(br, x.y, yi);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) row[q4 + 4 * r] = make_double2(yr[r], yi[r]);
+        }
+        __syncthreads();
+    }
+    for (int e = tid; e < n; e += QRS_THREADS) {
+        const double2 x = X[place(e)];
+        T[e] = x.x;
+        T[n + e] = x.y;
+    }
+    const int a = tid & 15, b = (tid >> 4) & 15, D2 = D * D;
+    if (a < D && b < D) {
+        if (tid < 256) {   // R[a, b]
+            double re = 0, im = 0;
+            for (int j = a; j <= b; ++j) {
+                const double2 x = fac[1][a + CB * j], y = fac[0][j + CB * b];
+                re += x.x * y.x - x.y * y.y;
+                im += x.x * y.y + x.y * y.x;
+            }
+            Rout[a + D * b] = re;
+            Rout[D2 + a + D * b] = im;
+        } else if (rinvh) {   // R^{-H} = L2^{-1} L1^{-1}
+            double re = 0, im = 0;
+            for (int j = b; j <= a; ++j) {
+                const double xr = l_re[1][a + CB * j], xi = l_im[1][a + CB * j];
+                const double yr = l_re[0][j + CB * b], yi = l_im[0][j + CB * b];
+                re += xr * yr - xi * yi;
+                im += xr * yi + xi * yr;
+            }
+            rinvh[a + D * b] = re;
+            rinvh[D2 + a + D * b] = im;
+        }
+    }
+    if (wave == 0) {
+        if (bad && lane == 0) atomicExch(&st->bad, 1);
+        double mn = lane < D ? fac[1][17 * lane].x * fac[0][17 * lane].x : 1e308;
+        mn = mn < 1e308 ? mn : 1e308;
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) {
+            const double t = __shfl_xor(mn, o, 64);
+            mn = t < mn ? t : mn;
+        }
+        if (lane == 0 && mn > 0) atomicMin(&st->min_rdiag_bits, (unsigned long long)__double_as_longlong(mn));
+    }
+}
+
 }  // namespace
+
+bool qr_small_fits(int DL, int DR, int DP, int leg) {
+    const int64_t D = leg == 0 ? DL : leg == 1 ? DR : DP, n = (int64_t)DL * DR * DP;
+    return D <= CB && n / D <= QRS_ROWS;
+}
+void qr_small(double* T, int DL, int DR, int DP, int leg, double* Rout, double* rinvh, StepDev* st, hipStream_t s) {
+    if (g_dry_run) return;
+    const int D = leg == 0 ? DL : leg == 1 ? DR : DP, stride = leg == 0 ? 1 : leg == 1 ? DL : DL * DR;
+    hipLaunchKernelGGL(k_qr_small, dim3(1), dim3(QRS_THREADS), 0, s, T, DL * DR * DP, D, stride, Rout, rinvh, st);
+}
 
 void chol_inv(const double* G, int D, double* Linv, double* R, const double* Rfirst, double* work,
               StepDev* st, hipStream_t s) {

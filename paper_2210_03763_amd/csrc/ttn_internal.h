@@ -242,6 +242,11 @@ void gather_cols(const double* V, int n, const int* order, int k, double* out, h
 // weight 1 - kept / total in st->max_disc_bits
 void split_finish(const double* w, int n, int k, double* x, int64_t count, StepDev* st, hipStream_t s);
 
+// The whole gauge move (CholeskyQR2) of a small tensor on one of its legs in one
+// launch: T <- Q, Rout = R, and (rinvh != nullptr) R^{-H}; usable when
+// qr_small_fits.
+bool qr_small_fits(int DL, int DR, int DP, int leg);
+void qr_small(double* T, int DL, int DR, int DP, int leg, double* Rout, double* rinvh, StepDev* st, hipStream_t s);
 // Cholesky of a Hermitian D x D Gram matrix G (planar, column-major):
 // G = L L^H.  Writes Linv (lower, L^{-1}) and R = L^H (upper).  Rfirst: the R
 // of the gauge move's first factorization when this is its second (G near I);

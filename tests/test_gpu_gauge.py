@@ -21,3 +21,13 @@ def test_conditions(d, chi, eps):
     print(f"[gauge] d={d} chi={chi} eps={eps}", flush=True)
     tol = max(1e-10, 1e-13 / eps)
     compare(w, tol=tol, tolC=tol)
+
+
+@pytest.mark.parametrize("d,chi", [(3, 2), (3, 8), (3, 9), (3, 13), (3, 16), (3, 17), (4, 15), (4, 17)])
+def test_one_workgroup_moves(d, chi):
+    """Bonds on both sides of 16 and tensors on both sides of 256 rows: moves in
+    one workgroup, with rows and columns padded to whole tiles, and beside them
+    the ones that take a launch per product."""
+    w = W.make_random_drive(4, 4, d, chi, 2, 0.01, 2, 3 + chi, plus_sites=tuple(range(16)), eps=5e-2)
+    print(f"[gauge] d={d} chi={chi}", flush=True)
+    compare(w, tol=1e-10, tolC=1e-10)
