@@ -754,7 +754,7 @@ constexpr int SMALL_THREADS = 1024;
 // product instead of images and sums.
 // Measured, m = 12 (us; planar LDS vectors, two passes a product, projections
 // through LDS reductions / this): 3 x 3 x 9 node (n = 81) 95 / 48, 16 x 16
-// bond over five operators (n = 256) 163 / 109.
+// bond over five operators (n = 256) 163 / 86.
 constexpr int SMALL_DENSE_N = 96;
 constexpr int SMALL_DENSE_COLS = SMALL_DENSE_N / 16;   // of each of a thread's two rows
 
@@ -864,18 +864,107 @@ __device__ double2 small_entry(const SmallOp& o, int ir, int ic) {
     return make_double2(re, im);
 }
 
+typedef double cb_d4 __attribute__((ext_vector_type(4)));
+
+__device__ inline cb_d4 cb_mfma(double a, double b, cb_d4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// The structured product on the FP64 matrix cores: every operator of the two
+// stages is a task per 16 x 16 output tile (rows the operator's leg, columns the
+// other two; D padded to 16 in the rows and to 4 in the sum), dealt to the
+// waves; the sums' tasks write a slot of their operator, and one pass adds the
+// slots.  jt: for every leg, the first element of each of its n / D columns.
+struct SmallTasks {
+    int tl, tr, tp;                    // tiles of a product on each leg
+    const int *jl, *jr, *jp;           // column tables
+};
+inline __host__ __device__ int small_tiles(int D, int n) { return (D + 15) / 16 * ((n / D + 15) / 16); }
+inline __host__ __device__ int small_units(int sL, int nz, bool hasB, bool hasW) {
+    return 1 + (hasB ? sL + 1 : 0) + (hasW ? sL + nz + 1 : 0);
+}
+__device__ inline void small_tile(const double2* op, int D, int sq, const int* jt, int cols, int tile,
+                                  const double2* src, double2* dst) {
+    const int lane = threadIdx.x & 63, c16 = lane & 15, q4 = lane >> 4;
+    const int ot = (D + 15) / 16, o = 16 * (tile % ot) + c16, j0 = 16 * (tile / ot);
+    const bool ook = o < D, jok = j0 + c16 < cols;
+    const int jb = jok ? jt[j0 + c16] : 0, oo = ook ? o : 0;
+    cb_d4 re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+    const double2 none = make_double2(0.0, 0.0);
+#pragma unroll 4
+    for (int k = 0; k < D; k += 4) {
+        const int q = k + q4;
+        const double2 a = ook && q < D ? op[oo + D * q] : none;
+        const double2 b = jok && q < D ? src[jb + sq * q] : none;
+        re = cb_mfma(b.x, a.x, re);
+        im = cb_mfma(b.x, a.y, im);
+        re = cb_mfma(-b.y, a.y, re);
+        im = cb_mfma(b.y, a.x, im);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int j = j0 + q4 + 4 * r;
+        if (ook && j < cols) dst[jt[j] + sq * o] = make_double2(re[r], im[r]);
+    }
+}
+__device__ void small_matvec_mfma(const SmallOp& o, const SmallTasks& t, const double2* x, double inv, double2* S,
+                                  double2* slots, double2* y) {
+    constexpr int WAVES = SMALL_THREADS / 64;
+    const int DL = o.DL, DR = o.DR, DP = o.DP, sL = o.sL, nz = o.nz, n = DL * DR * DP;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int e = wave; e < sL * t.tl + nz * t.tr; e += WAVES) {
+        if (e < sL * t.tl) {
+            const int k = e / t.tl;
+            small_tile(o.L + DL * DL * (k + 1), DL, 1, t.jl, n / DL, e - k * t.tl, x, S + n * k);
+        } else {
+            const int f = e - sL * t.tl, k = f / t.tr;
+            small_tile(o.R + DR * DR * (k + 1), DR, DL, t.jr, n / DR, f - k * t.tr, x, S + n * (sL + k));
+        }
+    }
+    __syncthreads();
+    const int nB = o.B ? sL + 1 : 0, nW = o.W ? sL + nz + 1 : 0;
+    for (int e = wave; e < t.tl + nB * t.tr + nW * t.tp; e += WAVES) {
+        if (e < t.tl) {
+            small_tile(o.L, DL, 1, t.jl, n / DL, e, x, slots);
+        } else if (e < t.tl + nB * t.tr) {
+            const int f = e - t.tl, k = f / t.tr;
+            small_tile(o.B + DR * DR * k, DR, DL, t.jr, n / DR, f - k * t.tr, k == 0 ? x : S + n * (k - 1),
+                       slots + n * (1 + k));
+        } else {
+            const int f = e - t.tl - nB * t.tr, k = f / t.tp;
+            small_tile(o.W + DP * DP * k, DP, DL * DR, t.jp, n / DP, f - k * t.tp, k == 0 ? x : S + n * (k - 1),
+                       slots + n * (1 + nB + k));
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += SMALL_THREADS) {
+        double re = 0, im = 0;
+#pragma unroll 4
+        for (int u = 0; u < 1 + nB + nW; ++u) {
+            re += slots[n * u + i].x;
+            im += slots[n * u + i].y;
+        }
+        y[i] = make_double2(re * inv, im * inv);
+    }
+    __syncthreads();
+}
+
 // E: entries of a vector per lane (n <= 64 E); up to 4 of them, a wave keeps its
-// basis vector in registers, else it reads it from LDS.
-template <int E, bool DENSE>
+// basis vector in registers, else it reads it from LDS.  FORM: the product as
+// loops over the stacks, as a dense matrix, or on the matrix cores.
+constexpr int SMALL_LOOPS = 0, SMALL_DENSE = 1, SMALL_MFMA = 2;
+// LDS of the matrix-core form, doubles: the stacks and vectors and the slots
+constexpr int SMALL_MFMA_POOL = 18432;
+template <int E, int FORM>
 __global__ __launch_bounds__(SMALL_THREADS) void k_small_evolve(const double* gL, const double* gR, const double* gB,
                                                              const double* gW, int DL, int DR, int DP, int sL,
                                                              int sR, int m, double tau, double tol, int nonherm,
                                                              double* x, StepDev* st) {
-    __shared__ double2 pool[SMALL_EVOLVE_POOL / 2];
+    __shared__ double2 pool[(FORM == SMALL_MFMA ? SMALL_MFMA_POOL : SMALL_EVOLVE_POOL) / 2];
     __shared__ LanczosDev lz;
     __shared__ int sidx[SMALL_EVOLVE_N];
     __shared__ double2 c[KRYLOV_MAX];
-    constexpr bool KEEP = E <= 4;
+    constexpr bool KEEP = E <= 4, DENSE = FORM == SMALL_DENSE;
     constexpr int UNROLL = KEEP ? E : 4;
     const int n = DL * DR * DP, NS = small_stride(n);
     const int L2 = DL * DL, R2 = DR * DR, P2 = DP * DP;
@@ -902,8 +991,19 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_evolve(const double* gL
     if (gB) stage(gB, B, R2, 1 + sL);
     if (gW) stage(gW, W, P2, 1 + sL + sR);
     const SmallOp op{L, nz ? Rr : nullptr, gB ? B : nullptr, gW ? W : nullptr, DL, DR, DP, sL, nz};
+    double2* slots = W + (gW ? P2 * (1 + sL + sR) : 0);
+    SmallTasks tasks{};
+    if constexpr (FORM == SMALL_MFMA) {
+        int* jl = sidx;
+        int* jr = jl + n / DL;
+        int* jp = jr + n / DR;
+        for (int j = tid; j < n / DL; j += SMALL_THREADS) jl[j] = DL * j;
+        for (int j = tid; j < n / DR; j += SMALL_THREADS) jr[j] = j % DL + DL * DR * (j / DL);
+        for (int j = tid; j < n / DP; j += SMALL_THREADS) jp[j] = j;
+        tasks = SmallTasks{small_tiles(DL, n), small_tiles(DR, n), small_tiles(DP, n), jl, jr, jp};
+    }
     for (int i = tid; i < n; i += SMALL_THREADS) {
-        sidx[i] = (i % DL) | ((i / DL) % DR) << 10 | (i / (DL * DR)) << 20;
+        if constexpr (FORM != SMALL_MFMA) sidx[i] = (i % DL) | ((i / DL) % DR) << 10 | (i / (DL * DR)) << 20;
         cur[i] = make_double2(x[i], x[n + i]);
     }
     __syncthreads();
@@ -1021,7 +1121,9 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_evolve(const double* gL
                 }
             }
             __syncthreads();
-        } else
+        } else if constexpr (FORM == SMALL_MFMA)
+            small_matvec_mfma(op, tasks, cur, inv, S, slots, nxt);
+        else
             small_matvec(op, sidx, cur, inv, S, nxt);
         project(kc, nxt);
         if (tid == 0) {
@@ -1286,13 +1388,20 @@ void small_evolve(const double* L, const double* R, const double* B, const doubl
 #define TTN_L(E, D)                                                                                                \
     hipLaunchKernelGGL((k_small_evolve<E, D>), dim3(1), dim3(SMALL_THREADS), 0, s, L, R, B, W, DL, DR, DP, sL, sR, \
                        m, tau, tol, nonherm ? 1 : 0, x, st)
-    const int n = DL * DR * DP;
+    const int n = DL * DR * DP, nz = W && sR > 0 ? sR : 0;
+    // the matrix-core form where its slots fit beside the rest (16 x 16 bond over
+    // five operators: 86 us, 109 with the loops)
+    const bool mfma = n <= 256 && small_evolve_doubles(DL, DR, DP, sL, sR, m, B != nullptr, W != nullptr) +
+                                          2 * (int64_t)n * small_units(sL, nz, B != nullptr, W != nullptr) <=
+                                      SMALL_MFMA_POOL;
     if (n <= SMALL_DENSE_N)
-        TTN_L(2, true);
+        TTN_L(2, SMALL_DENSE);
+    else if (mfma)
+        TTN_L(4, SMALL_MFMA);
     else if (n <= 256)
-        TTN_L(4, false);
+        TTN_L(4, SMALL_LOOPS);
     else
-        TTN_L(16, false);
+        TTN_L(16, SMALL_LOOPS);
 #undef TTN_L
 }
 
@@ -1781,12 +1890,6 @@ __device__ inline void cb_wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-typedef double cb_d4 __attribute__((ext_vector_type(4)));
-
-__device__ inline cb_d4 cb_mfma(double a, double b, cb_d4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
 // O -= A B^H on a 16 x 16 block by one wave with the FP64 matrix cores.
