@@ -1224,7 +1224,7 @@ void lanczos_expm(ttn_handle* h, const OpDesc& o, double* x, double tau) {
 // with R upper triangular, real positive diagonal; Q overwrites T, R -> Rout.
 // ---------------------------------------------------------------------------
 // With rinvh != nullptr also writes R^{-H} = L2^{-1} L1^{-1} (for the adjoint),
-// leaving L1^{-1} in l1inv (D x D scratch).
+// with l1inv (D x D) as scratch for L1^{-1}.
 void qr_toward(ttn_handle* h, int DL, int DR, int DP, double* Tv, int leg, double* Rout,
                double* rinvh = nullptr, double* l1inv = nullptr) {
     Ctx<double> c{h, nullptr};
