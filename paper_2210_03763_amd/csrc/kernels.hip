@@ -2555,6 +2555,7 @@ constexpr int JAC_SWEEPS2 = 3;       // and after it, before k_herm_jacobi takes
 // State of an iteration phase.
 struct JacState {
     double floor;                    // 4 eps sum |A_ii|
+    int exp;                         // the iteration works on A 2^-exp
     int rot[JAC_SWEEPS + 1];         // rot[s]: sweep s rotated something
     int done;                        // n <= JW: the single launch settled
 };
@@ -2715,24 +2716,38 @@ __device__ inline jf64x4 jac_product(const JacMat& A, const JacMat& B) {
     return acc;
 }
 
-// V = 1, A0 = A, the skip level of the rotations
-__global__ __launch_bounds__(JS_THREADS) void k_jacobi_init(const double* A, int n, double* V, double* A0, JacState* js) {
+// V = 1, A0 = B = A 2^-exp, the skip level of the rotations.  The power of two
+// puts the largest entry into [1/2, 1), so that squares of entries neither
+// underflow nor overflow whatever the scale of A (exact but for entries 2^-1022
+// of the largest); every block finds it for itself.
+__global__ __launch_bounds__(JS_THREADS) void k_jacobi_init(const double* A, int n, double* V, double* A0, double* B,
+                                                           JacState* js) {
     __shared__ double sh[JS_THREADS / 64 + 1];
     const int64_t nn = (int64_t)n * n;
+    double mx = 0.0;
+    for (int64_t e = threadIdx.x; e < 2 * nn; e += blockDim.x) mx = fmax(mx, fabs(A[e]));
+    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+    if (threadIdx.x % 64 == 0) sh[threadIdx.x / 64] = mx;
+    __syncthreads();
+    for (int w = 0; w < JS_THREADS / 64; ++w) mx = fmax(mx, sh[w]);
+    __syncthreads();
+    int ex = 0;
+    if (mx > 0.0 && mx <= 1.7976931348623157e308) (void)frexp(mx, &ex);
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nn; e += (int64_t)gridDim.x * blockDim.x) {
         V[e] = e % n == e / n ? 1.0 : 0.0;
         V[nn + e] = 0.0;
-        A0[e] = A[e];
-        A0[nn + e] = A[nn + e];
+        A0[e] = B[e] = ldexp(A[e], -ex);
+        A0[nn + e] = B[nn + e] = ldexp(A[nn + e], -ex);
     }
     if (blockIdx.x) return;
     double tr = 0.0;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) tr += fabs(A[i + (int64_t)n * i]);
+    for (int i = threadIdx.x; i < n; i += blockDim.x) tr += fabs(ldexp(A[i + (int64_t)n * i], -ex));
     tr = block_sum_all(tr, sh);
     for (int p = 0; p < 2; ++p)
         for (int i = threadIdx.x; i <= JAC_SWEEPS; i += blockDim.x) js[p].rot[i] = 0;
     if (threadIdx.x < 2) {
         js[threadIdx.x].floor = 4.0 * 2.220446049250313e-16 * tr;
+        js[threadIdx.x].exp = ex;
         js[threadIdx.x].done = 0;
     }
 }
@@ -3008,7 +3023,7 @@ __global__ __launch_bounds__(JAC_THREADS) void k_herm_jacobi(double* A, int n, d
             rank += (wj > wi || (wj == wi && j < i)) ? 1 : 0;
         }
         order[rank] = i;
-        w[rank] = wi;
+        w[rank] = ldexp(wi, js->exp);
     }
     if (tid == 0 && !s_done) atomicExch(&st->bad, 1);
 }
@@ -3089,7 +3104,7 @@ void split_finish(const double* w, int n, int k, double* x, int64_t count, StepD
 
 int64_t herm_eig_work(int n) {
     const int64_t np = (n + JW - 1) / JW;
-    return 3 * 2 * (int64_t)n * n + np * 2 * JW * JW + 2 * (int64_t)((sizeof(JacState) + 7) / 8);
+    return 4 * 2 * (int64_t)n * n + np * 2 * JW * JW + 2 * (int64_t)((sizeof(JacState) + 7) / 8);
 }
 
 // The rounds leave A diagonal to the skip level, but V and the eigenvalues
@@ -3099,19 +3114,19 @@ int64_t herm_eig_work(int n) {
 // sweep or two rotate what that turns up (144 x 144, spectrum over six decades:
 // eigenvalues off by 9.9e-14 of their norm before, the leading projector by
 // 1.7e-13).
-void herm_eig(double* A, int n, double* V, double* w, int* order, double* work, StepDev* st, hipStream_t s) {
+void herm_eig(const double* A, int n, double* V, double* w, int* order, double* work, StepDev* st, hipStream_t s) {
     if (g_dry_run) return;
     constexpr double TOL = 1e-15;
     const int64_t n2 = 2 * (int64_t)n * n;
-    double *A0 = work, *T = A0 + n2, *G = T + n2, *U = G + n2;
+    double *A0 = work, *B = A0 + n2, *T = B + n2, *G = T + n2, *U = G + n2;
     const int np = (n + JW - 1) / JW, nb = 2 * np;
     JacState* js = (JacState*)(U + (int64_t)np * 2 * JW * JW);
     auto sweeps = [&](int count, JacState* state) {
         for (int sweep = 0; sweep < count; ++sweep)
             for (int r = 0; r < nb - 1; ++r) {
-                hipLaunchKernelGGL(k_jacobi_solve, dim3(np), dim3(JS_THREADS), 0, s, A, n, nb, r, sweep,
+                hipLaunchKernelGGL(k_jacobi_solve, dim3(np), dim3(JS_THREADS), 0, s, B, n, nb, r, sweep,
                                    nb == 2 ? 60 : 1, TOL, U, state);
-                hipLaunchKernelGGL(k_jacobi_apply, dim3(np * (np - 1) / 2 + np * np), dim3(JA_THREADS), 0, s, A, n, nb,
+                hipLaunchKernelGGL(k_jacobi_apply, dim3(np * (np - 1) / 2 + np * np), dim3(JA_THREADS), 0, s, B, n, nb,
                                    V, r, sweep, (const double*)U, (const JacState*)state);
             }
     };
@@ -3133,16 +3148,16 @@ void herm_eig(double* A, int n, double* V, double* w, int* order, double* work, 
         g.beta = beta;
         cgemm<double>(g, GemmScratch{}, s, nullptr, 0);
     };
-    hipLaunchKernelGGL(k_jacobi_init, dim3((n * n + 1023) / 1024), dim3(JS_THREADS), 0, s, A, n, V, A0, js);
+    hipLaunchKernelGGL(k_jacobi_init, dim3((n * n + 1023) / 1024), dim3(JS_THREADS), 0, s, A, n, V, A0, B, js);
     sweeps(nb == 2 ? 1 : JAC_SWEEPS, js);
     hipLaunchKernelGGL(k_jacobi_scale, dim3((int)((n2 + 1023) / 1024)), dim3(256), 0, s, V, T, n2);
     product(T, true, T, G, 1.0, 0);
     product(T, false, G, V, -0.5, 1);
     product(A0, false, V, G, 1.0, 0);
-    product(V, true, G, A, 1.0, 0);
+    product(V, true, G, B, 1.0, 0);
     const int last = nb == 2 ? 1 : JAC_SWEEPS2;
     sweeps(last, js + 1);
-    hipLaunchKernelGGL(k_herm_jacobi, dim3(1), dim3(JAC_THREADS), 0, s, A, n, V, w, order, last, 60, TOL,
+    hipLaunchKernelGGL(k_herm_jacobi, dim3(1), dim3(JAC_THREADS), 0, s, B, n, V, w, order, last, 60, TOL,
                        (const JacState*)(js + 1), st);
 }
 

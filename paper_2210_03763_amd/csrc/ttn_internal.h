@@ -226,12 +226,12 @@ void herm_f2d(const float* in, double* out, int D, int count, hipStream_t s, boo
 void sum_mats(const double* src, int D, int count, double* dst, hipStream_t s);
 
 // Eigenvalues (descending, w[k]) and eigenvectors (columns order[k] of V) of
-// a Hermitian n x n matrix A (planar, column-major; destroyed), n <= JAC_NMAX,
+// a Hermitian n x n matrix A (planar, column-major) of any scale, n <= JAC_NMAX,
 // by cyclic block Jacobi; st->bad when it does not converge.  work:
 // herm_eig_work(n) doubles.
 constexpr int JAC_NMAX = 256;
 int64_t herm_eig_work(int n);
-void herm_eig(double* A, int n, double* V, double* w, int* order, double* work, StepDev* st, hipStream_t s);
+void herm_eig(const double* A, int n, double* V, double* w, int* order, double* work, StepDev* st, hipStream_t s);
 // dst[c dc + s ds + p dp] = (conj) src[c sc + s ss + p sp], c < K, s < S, p < P
 void copy3(const double* src, int64_t src_plane, int64_t sc, int64_t ss, int64_t sp, double* dst, int64_t dst_plane,
            int64_t dc, int64_t ds, int64_t dp, int K, int S, int P, bool conj, hipStream_t s);
