@@ -686,12 +686,22 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // the nearest bf16 of what the pieces before it leave of x) and a real product
 // as the products of pieces p, q with p + q < NP on v_mfma_f32_32x32x16_bf16
 // with FP32 accumulation; the complex product takes four real ones.
-//   NP = 3 (FP32 mode): 3 x 8 significant bits hold every FP32 number exactly,
-// the three dropped products are below 2^-24 of the whole.  Against 64 bits
+//   NP = 3 (FP32 mode): 3 x 8 significant bits hold an FP32 number exactly if
+// its pieces lie in the range of bf16, the three dropped products are below
+// 2^-24 of the whole.  Against 64 bits
 // the result is closer than that of the FP32 matrix-core kernel it replaced
 // (three FP32 products per complex one, whose Re + Im sums cancel): left-leg
 // stack of a 128^3 node 2.6e-7 (3.9e-7 before), parent-leg sum over 33
 // operators 8.0e-7 (1.17e-6).
+//   Range of NP = 3: the first piece overflows from 3.39e38 on (an infinity turns
+// into NaN), and below 2^-100 the last ones reach the subnormals of bf16.
+// Outputs of operands out of range are taken again in plain FP32 products, with
+// the operands read from memory: by a wave whose outputs are not finite, and by a
+// block whose operands' largest magnitudes split_in_range refuses, which it looks
+// for only if those of its first k-tile are small.  The k loop has no part in it
+// (there, the largest magnitudes cost 1-4 % of a launch); what is left shows where
+// a block has few k-tiles (128^3 left-leg stack of sixteen, eight tiles: 205 us
+// without the checks, 209 with them; sum over 33: 344 / 343).
 //   NP = 2 (BF16x3 mode): hi hi, hi lo, lo hi, relative error 4.4e-6.
 // Loads are FP32; pieces are made while staging.  A wave owns 64 x 32 outputs
 // (two 32 x 32 tiles); tiles of BM x BN outputs and 16 k, two LDS buffers (98 KB
@@ -707,6 +717,15 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // 229 -> 156, 243 -> 209 (33), 256^3 right-leg sum over nine 914 -> 840.
 //   RAG: any inner extent, padded to a whole k-tile for every outer index.
 // ---------------------------------------------------------------------------
+
+// Whether the products of operands with these largest magnitudes are those of
+// exact pieces: no piece of a large entry below the normal numbers (2^-126, 26
+// bits under 2^-100), no product of two of them (26 bits and the sum's growth
+// under 2^-96).
+__device__ inline bool split_in_range(float a, float b) {
+    return a == 0.0f || b == 0.0f || (a >= 0x1p-100f && b >= 0x1p-100f && a * b >= 0x1p-96f);
+}
+
 template <int NP, int BM, int BN, bool AK, bool BKF, bool RAG>
 __global__ __launch_bounds__(64 * (BM / 64) * (BN / 32), 2) void k_cgemm_split(Gemm<float> g, int tilesM, int tilesN,
                                                                               int splits, int kchunk,
@@ -746,21 +765,25 @@ __global__ __launch_bounds__(64 * (BM / 64) * (BN / 32), 2) void k_cgemm_split(G
     auto rowB = [&](int q) { return BKF ? (tid + NT * q) / 4 : (tid + NT * q) % BN; };
     auto quadA = [&](int q) { return AK ? tid % 4 : (tid + NT * q) / BM; };
     auto quadB = [&](int q) { return BKF ? tid % 4 : (tid + NT * q) / BN; };
-    int kin = kb % kinP;
-    const int kout0 = kb / kinP;
+    int kin;
     const float *A[QA], *B[QB];
+    auto rewind = [&]() {
+        kin = kb % kinP;
+        const int kout = kb / kinP;
 #pragma unroll
-    for (int q = 0; q < QA; ++q) {
-        const int r = rowA(q);
-        A[q] = g.A + b1 * g.sab1 + b2 * g.sab2 + (int64_t)m0 * g.sam + kin * g.sak + kout0 * g.sako +
-               (r < g.M - m0 ? r : 0) * g.sam + 4 * quadA(q) * g.sak;
-    }
+        for (int q = 0; q < QA; ++q) {
+            const int r = rowA(q);
+            A[q] = g.A + b1 * g.sab1 + b2 * g.sab2 + (int64_t)m0 * g.sam + kin * g.sak + kout * g.sako +
+                   (r < g.M - m0 ? r : 0) * g.sam + 4 * quadA(q) * g.sak;
+        }
 #pragma unroll
-    for (int q = 0; q < QB; ++q) {
-        const int r = rowB(q);
-        B[q] = g.B + b1 * g.sbb1 + b2 * g.sbb2 + (int64_t)n0 * g.sbn + kin * g.sbk + kout0 * g.sbko +
-               (r < g.N - n0 ? r : 0) * g.sbn + 4 * quadB(q) * g.sbk;
-    }
+        for (int q = 0; q < QB; ++q) {
+            const int r = rowB(q);
+            B[q] = g.B + b1 * g.sbb1 + b2 * g.sbb2 + (int64_t)n0 * g.sbn + kin * g.sbk + kout * g.sbko +
+                   (r < g.N - n0 ? r : 0) * g.sbn + 4 * quadB(q) * g.sbk;
+        }
+    };
+    rewind();
     const int64_t wrapA = g.sako - kinP * g.sak, wrapB = g.sbko - kinP * g.sbk;
     const float sa = g.conjA ? -1.0f : 1.0f, sb = g.conjB ? -1.0f : 1.0f;
     float pa[QA][2][4], pb[QB][2][4];
@@ -839,8 +862,24 @@ __global__ __launch_bounds__(64 * (BM / 64) * (BN / 32), 2) void k_cgemm_split(G
         for (int r = 0; r < 16; ++r) crr[i][r] = cii[i][r] = cim[i][r] = 0.0f;
     const int nt = (ke - kb) / BK;
     const int r32 = lane % 32, kh = lane / 32;
+    float maxA = 0.0f, maxB = 0.0f;   // largest magnitudes of the thread's operands (NaN passed over)
+    auto largest = [&]() {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+#pragma unroll
+            for (int q = 0; q < QA; ++q) maxA = fmaxf(maxA, fabsf(pa[q][j / 4][j % 4]));
+#pragma unroll
+            for (int q = 0; q < QB; ++q) maxB = fmaxf(maxB, fabsf(pb[q][j / 4][j % 4]));
+        }
+    };
+    __shared__ int s_box[NP == 3 ? NT / 64 : 1];   // a wave's first tile holds an entry of 2^-48: 1 of A, 2 of B
     if (nt > 0) {
         fetch(nt > 1);
+        if constexpr (NP == 3) {
+            largest();
+            const int bits = (__any(maxA >= 0x1p-48f) ? 1 : 0) | (__any(maxB >= 0x1p-48f) ? 2 : 0);
+            s_box[wave] = bits;   // by every lane: a branch here would hold the next loads back
+        }
         stash(0);
         fetch(nt > 2);
     }
@@ -885,6 +924,81 @@ __global__ __launch_bounds__(64 * (BM / 64) * (BN / 32), 2) void k_cgemm_split(G
             }
         }
         __syncthreads();
+    }
+    if constexpr (NP == 3) {
+        bool plain = false;
+        int box = 0;
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) box |= s_box[w];
+        if (__builtin_expect(box != 3 && nt > 0, 0)) {   // the same in every wave
+            __shared__ float s_max[2][NT / 64];
+            rewind();
+            for (int t = 0; t < nt; ++t) {
+                fetch(t + 1 < nt);
+                largest();
+            }
+            for (int o = 32; o > 0; o >>= 1) {
+                maxA = fmaxf(maxA, __shfl_xor(maxA, o, 64));
+                maxB = fmaxf(maxB, __shfl_xor(maxB, o, 64));
+            }
+            if (lane == 0) {
+                s_max[0][wave] = maxA;
+                s_max[1][wave] = maxB;
+            }
+            __syncthreads();
+            for (int w = 0; w < NT / 64; ++w) {
+                maxA = fmaxf(maxA, s_max[0][w]);
+                maxB = fmaxf(maxB, s_max[1][w]);
+            }
+            plain = !split_in_range(maxA, maxB);
+        }
+        // an entry out of range makes the imaginary parts of its whole row or column
+        // of outputs not finite: one column and one row of every tile tell; z is NaN then
+        float z[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int i = 1; i < TI; ++i) z[i % 4] = fmaf(cim[i][0], 0.0f, z[i % 4]);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z[r % 4] = fmaf(cim[0][r], 0.0f, z[r % 4]);
+        if (__builtin_expect(plain || __any((z[0] + z[1]) + (z[2] + z[3]) != 0.0f), 0)) {
+            const float* A0 = g.A + b1 * g.sab1 + b2 * g.sab2;
+            const float* B0 = g.B + b1 * g.sbb1 + b2 * g.sbb2;
+            // both tiles along m share the sixteen columns; those past N read the first
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) crr[i][r] = cii[i][r] = cim[i][r] = 0.0f;
+            int ki = kb % kinP, ko = kb / kinP;
+#pragma unroll 1
+            for (int k = kb; k < ke; ++k) {
+                if (ki < g.Kin) {
+                    float ar[TI], ai[TI];
+#pragma unroll
+                    for (int i = 0; i < TI; ++i) {
+                        const int m = m0 + wm0 + 32 * i + r32;
+                        const float* a = A0 + (int64_t)(m < g.M ? m : m0) * g.sam + (int64_t)ki * g.sak +
+                                         (int64_t)ko * g.sako;
+                        ar[i] = a[0];
+                        ai[i] = sa * a[g.a_plane];
+                    }
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int n = n0 + wn0 + 8 * (r / 4) + 4 * kh + r % 4;
+                        const float* b = B0 + (int64_t)(n < g.N ? n : n0) * g.sbn + (int64_t)ki * g.sbk +
+                                         (int64_t)ko * g.sbko;
+                        const float br = b[0], bi = sb * b[g.b_plane];
+#pragma unroll
+                        for (int i = 0; i < TI; ++i) {
+                            crr[i][r] = fmaf(-ai[i], bi, fmaf(ar[i], br, crr[i][r]));
+                            cim[i][r] = fmaf(ai[i], br, fmaf(ar[i], bi, cim[i][r]));
+                        }
+                    }
+                }
+                if (++ki == kinP) {
+                    ki = 0;
+                    ++ko;
+                }
+            }
+        }
     }
     const int64_t MN = (int64_t)g.M * g.N;
     const int nbatch = g.B1 * g.B2;
