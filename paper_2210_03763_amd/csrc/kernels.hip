@@ -773,8 +773,12 @@ static_assert(KRYLOV_MAX <= SMALL_THREADS / 64, "one wave per Krylov vector");
 static_assert(SMALL_DENSE_N * 8 <= SMALL_THREADS && SMALL_DENSE_N % 16 == 0, "16 threads per two rows");
 
 // Row stride of the basis in LDS: 4 (mod 16) entries, so that the four rows a
-// quad reads at one element lie on different banks.
-inline __host__ __device__ int small_stride(int n) { return (n + 11) / 16 * 16 + 4; }
+// quad reads at one element lie on different banks; n where only that fits the
+// pool.
+inline int small_stride(int n, int m, int64_t doubles, int64_t pool) {
+    const int ns = (n + 11) / 16 * 16 + 4;
+    return doubles + 2 * (int64_t)(ns - n) * m <= pool ? ns : n;
+}
 
 __device__ inline void cmul_add(double2 a, double2 b, double& re, double& im) {
     re += a.x * b.x - a.y * b.y;
@@ -958,15 +962,15 @@ constexpr int SMALL_MFMA_POOL = 18432;
 template <int E, int FORM>
 __global__ __launch_bounds__(SMALL_THREADS) void k_small_evolve(const double* gL, const double* gR, const double* gB,
                                                              const double* gW, int DL, int DR, int DP, int sL,
-                                                             int sR, int m, double tau, double tol, int nonherm,
-                                                             double* x, StepDev* st) {
+                                                             int sR, int m, int NS, double tau, double tol,
+                                                             int nonherm, double* x, StepDev* st) {
     __shared__ double2 pool[(FORM == SMALL_MFMA ? SMALL_MFMA_POOL : SMALL_EVOLVE_POOL) / 2];
     __shared__ LanczosDev lz;
     __shared__ int sidx[SMALL_EVOLVE_N];
     __shared__ double2 c[KRYLOV_MAX];
     constexpr bool KEEP = E <= 4, DENSE = FORM == SMALL_DENSE;
     constexpr int UNROLL = KEEP ? E : 4;
-    const int n = DL * DR * DP, NS = small_stride(n);
+    const int n = DL * DR * DP;
     const int L2 = DL * DL, R2 = DR * DR, P2 = DP * DP;
     const int nz = (gW && sR > 0) ? sR : 0;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1376,7 +1380,7 @@ template void lz_iter<float>(double*, int, int, const float*, const float*, cons
 int64_t small_evolve_doubles(int DL, int DR, int DP, int sL, int sR, int m, bool hasB, bool hasW) {
     const int64_t n = (int64_t)DL * DR * DP;
     const int64_t nz = (hasW && sR > 0) ? sR : 0;
-    return 2 * (int64_t)small_stride((int)n) * m + 4 * n + 2 * n * (sL + nz) + 2 * (int64_t)DL * DL * (1 + sL) +
+    return 2 * n * (m + 2) + 2 * n * (sL + nz) + 2 * (int64_t)DL * DL * (1 + sL) +
            (nz ? 2 * (int64_t)DR * DR * (1 + sR) : 0) + (hasB ? 2 * (int64_t)DR * DR * (1 + sL) : 0) +
            (hasW ? 2 * (int64_t)DP * DP * (1 + sL + sR) : 0);
 }
@@ -1387,13 +1391,15 @@ void small_evolve(const double* L, const double* R, const double* B, const doubl
     if (g_dry_run) return;
 #define TTN_L(E, D)                                                                                                \
     hipLaunchKernelGGL((k_small_evolve<E, D>), dim3(1), dim3(SMALL_THREADS), 0, s, L, R, B, W, DL, DR, DP, sL, sR, \
-                       m, tau, tol, nonherm ? 1 : 0, x, st)
+                       m, NS, tau, tol, nonherm ? 1 : 0, x, st)
     const int n = DL * DR * DP, nz = W && sR > 0 ? sR : 0;
     // the matrix-core form where its slots fit beside the rest (16 x 16 bond over
     // five operators: 86 us, 109 with the loops)
-    const bool mfma = n <= 256 && small_evolve_doubles(DL, DR, DP, sL, sR, m, B != nullptr, W != nullptr) +
-                                          2 * (int64_t)n * small_units(sL, nz, B != nullptr, W != nullptr) <=
-                                      SMALL_MFMA_POOL;
+    const int64_t doubles = small_evolve_doubles(DL, DR, DP, sL, sR, m, B != nullptr, W != nullptr);
+    const int64_t slots = 2 * (int64_t)n * small_units(sL, nz, B != nullptr, W != nullptr);
+    const bool mfma = n > SMALL_DENSE_N && n <= 256 && doubles + slots <= SMALL_MFMA_POOL;
+    const int NS = mfma ? small_stride(n, m, doubles + slots, SMALL_MFMA_POOL)
+                        : small_stride(n, m, doubles, SMALL_EVOLVE_POOL);
     if (n <= SMALL_DENSE_N)
         TTN_L(2, SMALL_DENSE);
     else if (mfma)
