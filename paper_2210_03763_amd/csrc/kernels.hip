@@ -2555,10 +2555,9 @@ constexpr int JB = 16;
 constexpr int JW = 2 * JB;           // width of a pair
 constexpr int JS_THREADS = 512;
 constexpr int JA_THREADS = 512;
-constexpr int JAC_SWEEPS = 28;       // block sweeps enqueued before the refinement
-constexpr int JAC_SWEEPS2 = 3;       // and after it, before k_herm_jacobi takes what is left
+constexpr int JAC_SWEEPS = 28;       // block sweeps enqueued before k_herm_jacobi takes what is left
 
-// State of an iteration phase.
+// State of the iteration.
 struct JacState {
     double floor;                    // 4 eps sum |A_ii|
     int exp;                         // the iteration works on A 2^-exp
@@ -2749,21 +2748,11 @@ __global__ __launch_bounds__(JS_THREADS) void k_jacobi_init(const double* A, int
     double tr = 0.0;
     for (int i = threadIdx.x; i < n; i += blockDim.x) tr += fabs(ldexp(A[i + (int64_t)n * i], -ex));
     tr = block_sum_all(tr, sh);
-    for (int p = 0; p < 2; ++p)
-        for (int i = threadIdx.x; i <= JAC_SWEEPS; i += blockDim.x) js[p].rot[i] = 0;
-    if (threadIdx.x < 2) {
-        js[threadIdx.x].floor = 4.0 * 2.220446049250313e-16 * tr;
-        js[threadIdx.x].exp = ex;
-        js[threadIdx.x].done = 0;
-    }
-}
-
-// T = V, V = 1.5 V (the first part of the orthonormalisation V (3 - V^H V) / 2)
-__global__ void k_jacobi_scale(double* V, double* T, int64_t count) {
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < count; e += (int64_t)gridDim.x * blockDim.x) {
-        const double v = V[e];
-        T[e] = v;
-        V[e] = 1.5 * v;
+    for (int i = threadIdx.x; i <= JAC_SWEEPS; i += blockDim.x) js->rot[i] = 0;
+    if (threadIdx.x == 0) {
+        js->floor = 4.0 * 2.220446049250313e-16 * tr;
+        js->exp = ex;
+        js->done = 0;
     }
 }
 
@@ -2871,7 +2860,7 @@ __global__ __launch_bounds__(JA_THREADS) void k_jacobi_apply(double* A, int n, i
     }
 }
 
-// Eigenvalues and eigenvectors of a Hermitian n x n matrix A (planar complex,
+// Diagonalises a Hermitian n x n matrix A (planar complex,
 // column-major; overwritten) by the cyclic Jacobi method with the round-robin
 // ordering: each of the n' - 1 rounds of a sweep (n' = n rounded up to even,
 // the extra index a zero row and column) rotates n' / 2 disjoint index pairs
@@ -2885,12 +2874,11 @@ __global__ __launch_bounds__(JA_THREADS) void k_jacobi_apply(double* A, int n, i
 // matrices) or |b| <= 4 eps sum_i |A_ii| (the rounding level of the matrix,
 // which pairs of numerically zero eigenvalues cannot get below); the
 // iteration stops after a sweep without a rotation, or after max_sweeps
-// (then st->bad is set).  Outputs: w[k] the k-th largest
-// eigenvalue, order[k] its column in V.  Closes the block form: it finds A and V
+// (then st->bad is set).  Closes the block form: it finds A and V
 // as the rounds left them and goes on only if their last sweep still rotated.
-__global__ __launch_bounds__(JAC_THREADS) void k_herm_jacobi(double* A, int n, double* V, double* w, int* order,
-                                                             int block_sweeps, int max_sweeps, double tol,
-                                                             const JacState* js, StepDev* st) {
+__global__ __launch_bounds__(JAC_THREADS) void k_herm_jacobi(double* A, int n, double* V, int block_sweeps,
+                                                             int max_sweeps, double tol, const JacState* js,
+                                                             StepDev* st) {
     __shared__ double rc[JAC_NMAX / 2], rs[JAC_NMAX / 2], rer[JAC_NMAX / 2], rei[JAC_NMAX / 2];
     __shared__ int rp[JAC_NMAX / 2], rq[JAC_NMAX / 2];
     __shared__ int s_rot, s_done;
@@ -3020,18 +3008,177 @@ __global__ __launch_bounds__(JAC_THREADS) void k_herm_jacobi(double* A, int n, d
         }
     }
     __syncthreads();
-    // order[k]: the column of the k-th largest eigenvalue (ties by index)
-    for (int i = tid; i < n; i += JAC_THREADS) {
-        const double wi = A[i + (int64_t)n * i];
+    if (tid == 0 && !s_done) atomicExch(&st->bad, 1);
+}
+
+// ---------------------------------------------------------------------------
+// Refinement of the eigenvectors (Ogita and Aishima 2018, one step).  The
+// rotations leave V = X (1 + O(n eps / gap)) of the exact eigenvectors X, since
+// off-diagonal entries at the rounding level of A are never rotated.  With
+// R = 1 - V^H V and S = V^H A V, lambda_i = S_ii / (1 - R_ii) and V <- V (1 + E),
+// E_ij = (S_ij + lambda_j R_ij) / (lambda_j - lambda_i), is X to second order:
+// E + E^H = R keeps V orthonormal, the first-order rotation between i and j takes
+// out S_ij.  Pairs without a gap (|S_ij| + |lambda R_ij| > 1e-8 |lambda_j -
+// lambda_i|: the square of such a rotation would be visible) take E_ij = R_ij / 2.
+// What S and R hold is the rounding of some thousand rotations, so their own
+// products are summed in pairs of doubles.
+//   Measured, error of the leading projector (a twelfth of the spectrum, over six
+// decades) against extended precision, cyclic Jacobi in one workgroup / the block
+// form with V (3 - V^H V) / 2 and a last sweep / this: 144 x 144 1.2e-13 / 9.6e-14
+// / 1.5e-16, 200 x 200 1.8e-13 / 3.2e-13 / 2.0e-16.  Three launches of 4-17 us
+// where that refinement took 190 (144 x 144 4.01 -> 3.85 ms, 256 x 256 7.24 -> 6.69).
+// ---------------------------------------------------------------------------
+constexpr int ET = 16;   // tile of a refinement product, one output a thread
+
+// s + c += a b, c the rounding errors of s (two-product, two-sum)
+__device__ inline void dd_add(double& s, double& c, double a, double b) {
+#pragma clang fp contract(off)
+    const double p = a * b, e = fma(a, b, -p);
+    const double t = s + p, z = t - s;
+    const double d = (s - (t - z)) + (p - z);
+    s = t;
+    c += d + e;
+}
+
+// Output (m0 + tid % ET, n0 + tid / ET) of op(A) (B + Blo), n x n planar
+// column-major, as high and low parts (re, im) (op: conjugate transpose when HA;
+// Blo may be null).
+struct DD2 {
+    double rh, rl, ih, il;
+};
+template <bool HA>
+__device__ inline DD2 dd_product(const double* A, const double* B, const double* Blo, int n, int m0, int n0) {
+    __shared__ double As[2][ET][ET + 1], Bs[4][ET][ET + 1];
+    const int x = threadIdx.x % ET, y = threadIdx.x / ET;
+    const int64_t nn = (int64_t)n * n;
+    double rs = 0, rc = 0, is = 0, ic = 0;
+    for (int k0 = 0; k0 < n; k0 += ET) {
+        const int ra = HA ? k0 + x : m0 + x, ca = HA ? m0 + y : k0 + y, kb = k0 + x, cb = n0 + y;
+        const bool oka = ra < n && ca < n, okb = kb < n && cb < n;
+        const int64_t oa = oka ? ra + (int64_t)n * ca : 0, ob = okb ? kb + (int64_t)n * cb : 0;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const double a = oka ? A[p * nn + oa] : 0.0;
+            As[p][HA ? x : y][HA ? y : x] = HA && p ? -a : a;
+            Bs[p][x][y] = okb ? B[p * nn + ob] : 0.0;
+            Bs[2 + p][x][y] = okb && Blo ? Blo[p * nn + ob] : 0.0;
+        }
+        __syncthreads();
+#pragma unroll 4
+        for (int k = 0; k < ET; ++k) {
+            const double ar = As[0][k][x], ai = As[1][k][x], br = Bs[0][k][y], bi = Bs[1][k][y];
+            dd_add(rs, rc, ar, br);
+            dd_add(rs, rc, -ai, bi);
+            dd_add(is, ic, ar, bi);
+            dd_add(is, ic, ai, br);
+            if (Blo) {
+                const double lr = Bs[2][k][y], li = Bs[3][k][y];
+                rc += ar * lr - ai * li;
+                ic += ar * li + ai * lr;
+            }
+        }
+        __syncthreads();
+    }
+    DD2 o;
+    o.rh = rs + rc;
+    o.rl = rc - (o.rh - rs);
+    o.ih = is + ic;
+    o.il = ic - (o.ih - is);
+    return o;
+}
+
+// T + Tlo = A V
+__global__ __launch_bounds__(ET* ET) void k_eig_av(const double* A, const double* V, int n, double* T, double* Tlo) {
+    const int m0 = ET * blockIdx.x, n0 = ET * blockIdx.y;
+    const DD2 o = dd_product<false>(A, V, nullptr, n, m0, n0);
+    const int m = m0 + threadIdx.x % ET, c = n0 + threadIdx.x / ET;
+    if (m >= n || c >= n) return;
+    const int64_t nn = (int64_t)n * n, e = m + (int64_t)n * c;
+    T[e] = o.rh;
+    T[nn + e] = o.ih;
+    Tlo[e] = o.rl;
+    Tlo[nn + e] = o.il;
+}
+
+// S = V^H (T + Tlo) (blockIdx.z = 0), R = 1 - V^H V (1)
+__global__ __launch_bounds__(ET* ET) void k_eig_sr(const double* V, const double* T, const double* Tlo, int n,
+                                                  double* S, double* R) {
+    const int m0 = ET * blockIdx.x, n0 = ET * blockIdx.y;
+    const bool first = blockIdx.z == 0;
+    const DD2 o = dd_product<true>(V, first ? T : V, first ? Tlo : nullptr, n, m0, n0);
+    const int m = m0 + threadIdx.x % ET, c = n0 + threadIdx.x / ET;
+    if (m >= n || c >= n) return;
+    const int64_t nn = (int64_t)n * n, e = m + (int64_t)n * c;
+    if (first) {
+        S[e] = o.rh;
+        S[nn + e] = o.ih;
+    } else {
+        R[e] = ((m == c ? 1.0 : 0.0) - o.rh) - o.rl;
+        R[nn + e] = -o.ih - o.il;
+    }
+}
+
+// Vout = V + V E; w[k] the k-th largest eigenvalue of the unscaled matrix,
+// order[k] its column (ties by index, NaN last).
+__global__ __launch_bounds__(ET* ET) void k_eig_update(const double* V, const double* S, const double* R, int n,
+                                                      const JacState* js, double* Vout, double* w, int* order) {
+    __shared__ double lam[JAC_NMAX], Vs[2][ET][ET + 1], Es[2][ET][ET + 1];
+    const int x = threadIdx.x % ET, y = threadIdx.x / ET;
+    const int64_t nn = (int64_t)n * n;
+    for (int i = threadIdx.x; i < n; i += ET * ET) lam[i] = S[i + (int64_t)n * i] / (1.0 - R[i + (int64_t)n * i]);
+    __syncthreads();
+    const int m = ET * blockIdx.x + x, c = ET * blockIdx.y + y;
+    double re = 0, im = 0;
+    for (int k0 = 0; k0 < n; k0 += ET) {
+        const int kv = k0 + y, ke = k0 + x;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) Vs[p][y][x] = m < n && kv < n ? V[p * nn + m + (int64_t)n * kv] : 0.0;
+        double er = 0, ei = 0;
+        if (ke < n && c < n) {
+            const int64_t e = ke + (int64_t)n * c, h = c + (int64_t)n * ke;
+            // the Hermitian parts: E + E^H = R has to hold to rounding over the gap,
+            // whatever A is off Hermitian by
+            const double sr = 0.5 * (S[e] + S[h]), si = 0.5 * (S[nn + e] - S[nn + h]);
+            const double rr = 0.5 * (R[e] + R[h]), ri = 0.5 * (R[nn + e] - R[nn + h]);
+            const double li = lam[ke], lj = lam[c];
+            const double gap = lj - li;
+            const double num = sqrt(sr * sr + si * si) + fmax(fabs(li), fabs(lj)) * sqrt(rr * rr + ri * ri);
+            if (num <= 1e-8 * fabs(gap) && gap != 0.0) {
+                er = (sr + lj * rr) / gap;
+                ei = (si + lj * ri) / gap;
+            } else {
+                er = 0.5 * rr;
+                ei = 0.5 * ri;
+            }
+        }
+        Es[0][x][y] = er;
+        Es[1][x][y] = ei;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < ET; ++k) {
+            const double vr = Vs[0][k][x], vi = Vs[1][k][x], fr = Es[0][k][y], fi = Es[1][k][y];
+            re += vr * fr - vi * fi;
+            im += vr * fi + vi * fr;
+        }
+        __syncthreads();
+    }
+    if (m < n && c < n) {
+        const int64_t e = m + (int64_t)n * c;
+        Vout[e] = V[e] + re;
+        Vout[nn + e] = V[nn + e] + im;
+    }
+    if (blockIdx.x || blockIdx.y) return;
+    auto key = [&](int i) { return lam[i] == lam[i] ? lam[i] : -INFINITY; };
+    for (int i = threadIdx.x; i < n; i += ET * ET) {
+        const double wi = key(i);
         int rank = 0;
         for (int j = 0; j < n; ++j) {
-            const double wj = A[j + (int64_t)n * j];
-            rank += (wj > wi || (wj == wi && j < i)) ? 1 : 0;
+            const double wj = key(j);
+            rank += wj > wi || (wj == wi && j < i) ? 1 : 0;
         }
         order[rank] = i;
-        w[rank] = ldexp(wi, js->exp);
+        w[rank] = ldexp(lam[i], js->exp);
     }
-    if (tid == 0 && !s_done) atomicExch(&st->bad, 1);
 }
 }  // namespace
 
@@ -3110,61 +3257,34 @@ void split_finish(const double* w, int n, int k, double* x, int64_t count, StepD
 
 int64_t herm_eig_work(int n) {
     const int64_t np = (n + JW - 1) / JW;
-    return 4 * 2 * (int64_t)n * n + np * 2 * JW * JW + 2 * (int64_t)((sizeof(JacState) + 7) / 8);
+    return 6 * 2 * (int64_t)n * n + np * 2 * JW * JW + (int64_t)((sizeof(JacState) + 7) / 8);
 }
 
-// The rounds leave A diagonal to the skip level, but V and the eigenvalues
-// carry the rounding of some thousand rotations.  One refinement takes it
-// out: V <- V (3 - V^H V) / 2 is orthonormal to rounding, A <- V^H A0 V holds
-// the eigenvalues as Rayleigh quotients of the original matrix, and a last
-// sweep or two rotate what that turns up (144 x 144, spectrum over six decades:
-// eigenvalues off by 9.9e-14 of their norm before, the leading projector by
-// 1.7e-13).
 void herm_eig(const double* A, int n, double* V, double* w, int* order, double* work, StepDev* st, hipStream_t s) {
     if (g_dry_run) return;
     constexpr double TOL = 1e-15;
     const int64_t n2 = 2 * (int64_t)n * n;
-    double *A0 = work, *B = A0 + n2, *T = B + n2, *G = T + n2, *U = G + n2;
+    double *A0 = work, *B = A0 + n2, *X = B + n2, *T = X + n2, *Tlo = T + n2, *R = Tlo + n2, *U = R + n2;
     const int np = (n + JW - 1) / JW, nb = 2 * np;
     JacState* js = (JacState*)(U + (int64_t)np * 2 * JW * JW);
-    auto sweeps = [&](int count, JacState* state) {
-        for (int sweep = 0; sweep < count; ++sweep)
-            for (int r = 0; r < nb - 1; ++r) {
-                hipLaunchKernelGGL(k_jacobi_solve, dim3(np), dim3(JS_THREADS), 0, s, B, n, nb, r, sweep,
-                                   nb == 2 ? 60 : 1, TOL, U, state);
-                hipLaunchKernelGGL(k_jacobi_apply, dim3(np * (np - 1) / 2 + np * np), dim3(JA_THREADS), 0, s, B, n, nb,
-                                   V, r, sweep, (const double*)U, (const JacState*)state);
-            }
-    };
-    auto product = [&](const double* X, bool hx, const double* Y, double* C, double alpha, int beta) {
-        Gemm<double> g;
-        g.M = g.N = g.Kin = n;
-        g.A = X;
-        g.B = Y;
-        g.C = C;
-        g.a_plane = g.b_plane = g.c_plane = (int64_t)n * n;
-        g.sam = hx ? n : 1;
-        g.sak = hx ? 1 : n;
-        g.conjA = hx;
-        g.sbk = 1;
-        g.sbn = n;
-        g.scm = 1;
-        g.scn = n;
-        g.alpha = alpha;
-        g.beta = beta;
-        cgemm<double>(g, GemmScratch{}, s, nullptr, 0);
-    };
-    hipLaunchKernelGGL(k_jacobi_init, dim3((n * n + 1023) / 1024), dim3(JS_THREADS), 0, s, A, n, V, A0, B, js);
-    sweeps(nb == 2 ? 1 : JAC_SWEEPS, js);
-    hipLaunchKernelGGL(k_jacobi_scale, dim3((int)((n2 + 1023) / 1024)), dim3(256), 0, s, V, T, n2);
-    product(T, true, T, G, 1.0, 0);
-    product(T, false, G, V, -0.5, 1);
-    product(A0, false, V, G, 1.0, 0);
-    product(V, true, G, B, 1.0, 0);
-    const int last = nb == 2 ? 1 : JAC_SWEEPS2;
-    sweeps(last, js + 1);
-    hipLaunchKernelGGL(k_herm_jacobi, dim3(1), dim3(JAC_THREADS), 0, s, B, n, V, w, order, last, 60, TOL,
-                       (const JacState*)(js + 1), st);
+    hipLaunchKernelGGL(k_jacobi_init, dim3((n * n + 1023) / 1024), dim3(JS_THREADS), 0, s, A, n, X, A0, B, js);
+    const int sweeps = nb == 2 ? 1 : JAC_SWEEPS;
+    for (int sweep = 0; sweep < sweeps; ++sweep)
+        for (int r = 0; r < nb - 1; ++r) {
+            hipLaunchKernelGGL(k_jacobi_solve, dim3(np), dim3(JS_THREADS), 0, s, B, n, nb, r, sweep,
+                               nb == 2 ? 60 : 1, TOL, U, js);
+            hipLaunchKernelGGL(k_jacobi_apply, dim3(np * (np - 1) / 2 + np * np), dim3(JA_THREADS), 0, s, B, n, nb, X,
+                               r, sweep, (const double*)U, (const JacState*)js);
+        }
+    hipLaunchKernelGGL(k_herm_jacobi, dim3(1), dim3(JAC_THREADS), 0, s, B, n, X, sweeps, 60, TOL,
+                       (const JacState*)js, st);
+    double* S = B;
+    const int t = (n + ET - 1) / ET;
+    hipLaunchKernelGGL(k_eig_av, dim3(t, t), dim3(ET * ET), 0, s, (const double*)A0, (const double*)X, n, T, Tlo);
+    hipLaunchKernelGGL(k_eig_sr, dim3(t, t, 2), dim3(ET * ET), 0, s, (const double*)X, (const double*)T,
+                       (const double*)Tlo, n, S, R);
+    hipLaunchKernelGGL(k_eig_update, dim3(t, t), dim3(ET * ET), 0, s, (const double*)X, (const double*)S,
+                       (const double*)R, n, (const JacState*)js, V, w, order);
 }
 
 // ---------------------------------------------------------------------------
