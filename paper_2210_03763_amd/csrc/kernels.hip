@@ -2542,6 +2542,13 @@ constexpr int JAC_THREADS = 1024;
 // (the mirror image is written with it) and V <- V U by row blocks, on the FP64
 // matrix cores.  The rotations, and the tests by which a pair is skipped, are
 // those of k_herm_jacobi below.
+//   Matrices of up to JAC_ONE rows are one pair of up to that width, rotated to
+// the end in one launch (k_jacobi_one; 48 rows take 113 KB of LDS, 64 would take
+// 200), where one and two pairs of the block form with their launches were
+// slower than the one workgroup in global memory up to 20 and from 33 to 38 rows.
+// Measured, us a call with the allocation of its work (that workgroup / the block
+// form / this): n = 8 121 / 303 / 73, 16 238 / 365 / 133, 24 480 / 399 / 238, 33
+// 864 / 1231 / 569, 40 1270 / 1360 / 616, 48 1930 / 1370 / 946.
 //   Bound by the serial chain of rotations (0.6-0.9 us per step of JB
 // disjoint rotations in LDS) and its launches: a round takes 13 us in
 // k_jacobi_solve and 7 in k_jacobi_apply, a launch after convergence 1.7.
@@ -2555,6 +2562,7 @@ constexpr int JB = 16;
 constexpr int JW = 2 * JB;           // width of a pair
 constexpr int JS_THREADS = 512;
 constexpr int JA_THREADS = 512;
+constexpr int JAC_ONE = 48;          // widest matrix of k_jacobi_one
 constexpr int JAC_SWEEPS = 28;       // block sweeps enqueued before k_herm_jacobi takes what is left
 
 // State of the iteration.
@@ -2562,7 +2570,6 @@ struct JacState {
     double floor;                    // 4 eps sum |A_ii|
     int exp;                         // the iteration works on A 2^-exp
     int rot[JAC_SWEEPS + 1];         // rot[s]: sweep s rotated something
-    int done;                        // n <= JW: the single launch settled
 };
 
 // Rotation [[c, sigma], [-conj(sigma), c]] of columns (p, q).
@@ -2597,39 +2604,46 @@ __device__ inline JacRot jac_rotation(double a, double d, double br, double bi, 
 }
 
 // The index pair (p, q) that pair i rotates, round after round: the JB pairs
-// between the two blocks, or (ALL) the JW / 2 pairs of the round-robin over the
+// between the two blocks, or (ALL) the W / 2 pairs of the round-robin over the
 // whole width.
-template <bool ALL>
+template <int W, bool ALL>
 struct JacIndex {
+    static_assert(ALL || W == JW, "two blocks");
     int x, y;
-    __device__ explicit JacIndex(int i) : x(i), y(ALL ? JW - 1 - i : JB + i) {}
+    __device__ explicit JacIndex(int i) : x(i), y(ALL ? W - 1 - i : JB + i) {}
     __device__ int p() const { return ALL ? min(x, y) : x; }
     __device__ int q() const { return ALL ? max(x, y) : y; }
     __device__ void next() {
-        if (ALL) {   // slot 0 stays, the others go round 1 .. JW - 1
-            x = x == 0 ? 0 : x == JW - 1 ? 1 : x + 1;
-            y = y == JW - 1 ? 1 : y + 1;
+        if (ALL) {   // slot 0 stays, the others go round 1 .. W - 1
+            x = x == 0 ? 0 : x == W - 1 ? 1 : x + 1;
+            y = y == W - 1 ? 1 : y + 1;
         } else {
             y = JB + ((y + 1) & (JB - 1));
         }
     }
 };
 
-// LDS matrix, re and im, [row][column]: with a stride of 33 doubles sixteen
+// LDS matrix, re and im, [row][column]: with an odd stride of doubles sixteen
 // lanes along a row or along a column meet distinct banks.
-typedef double JacMat[2][JW][JW + 1];
+template <int W>
+using JacMatW = double[2][W][W + 1];
+typedef JacMatW<JW> JacMat;
+
+// Threads of jac_rotate_pair: whole waves for the matrix, the others for u.
+constexpr int jac_mt(int w) { return (w * w / 4 + 63) / 64 * 64; }
+constexpr int jac_threads(int w) { return 2 * jac_mt(w) < 256 ? 256 : 2 * jac_mt(w) < 1024 ? 2 * jac_mt(w) : 1024; }
 
 // One pass of rotations over the pair matrix m[cur], its product gathered in
 // u; returns the buffer that holds the matrix on exit; rot is set if anything
-// rotated.  Threads 0 .. 255 rotate the matrix, thread (i, j) the 2 x 2 block of
-// pairs i and j; reading one buffer and writing the other, a round needs one
-// barrier.  Threads 256 .. 511 apply the rotations of the round before to u.
-template <bool ALL>
-__device__ inline int jac_rotate_pair(JacMat (&m)[2], JacMat& u, JacRot (&rots)[2][JB], int cur, double floor_,
-                                      double tol, int* rot) {
-    const int i = threadIdx.x & 15, j = (threadIdx.x >> 4) & 15;
-    constexpr int rounds = ALL ? JW - 1 : JB;
-    JacIndex<ALL> ii(i), jj(j);
+// rotated.  The first jac_mt(W) threads rotate the matrix, thread (i, j) the 2 x 2
+// block of pairs i and j; reading one buffer and writing the other, a round needs
+// one barrier.  The others apply the rotations of the round before to u.
+template <int W, bool ALL>
+__device__ inline int jac_rotate_pair(JacMatW<W> (&m)[2], JacMatW<W>& u, JacRot (&rots)[2][W / 2], int cur,
+                                      double floor_, double tol, int* rot) {
+    constexpr int P = W / 2, MT = jac_mt(W), UT = jac_threads(W) - MT, ITEMS = (W * P + UT - 1) / UT;
+    constexpr int rounds = ALL ? W - 1 : JB;
+    const int tid = threadIdx.x, i = tid % P, j = tid / P;
     // p <- c p - conj(sigma) q, q <- sigma p + c q on a pair of columns; on rows
     // sigma and its conjugate change places
     auto rotate = [](double c, double sr, double si, double& pr, double& pm, double& qr, double& qm) {
@@ -2639,56 +2653,73 @@ __device__ inline int jac_rotate_pair(JacMat (&m)[2], JacMat& u, JacRot (&rots)[
         pr = tr;
         pm = tm;
     };
-    for (int t = 0; t <= rounds; ++t) {
-        if (threadIdx.x >= 256) {
-            if (t > 0) {
-                const int pj = jj.p(), qj = jj.q();
-                jj.next();
-                const JacRot rj = rots[(t - 1) & 1][j];
+    // matrix: pair i's rotation is worked out by every lane that belongs to it,
+    // pair j's comes from one of them (a wave holds more than P consecutive tids)
+    const int from = (j + P - (tid & ~63) % P) % P;
+    JacIndex<W, ALL> ii(i), jj(j);
+    // u: item a is row[a] of the columns of pair[a]
+    int row[ITEMS], pair[ITEMS], px[ITEMS], py[ITEMS];
 #pragma unroll
-                for (int a = 0; a < 2; ++a) {
-                    const int row = i + JB * a;
-                    double pr = u[0][row][pj], pm = u[1][row][pj], qr = u[0][row][qj], qm = u[1][row][qj];
+    for (int a = 0; a < ITEMS; ++a) {
+        const int e = max(tid - MT, 0) + UT * a;
+        row[a] = e % W;
+        pair[a] = e / W;
+        const JacIndex<W, ALL> first(pair[a]);
+        px[a] = first.x;
+        py[a] = first.y;
+    }
+    for (int t = 0; t <= rounds; ++t) {
+        if (tid >= MT) {
+#pragma unroll
+            for (int a = 0; a < ITEMS; ++a)
+                if (t > 0 && (W * P % UT == 0 || pair[a] < P)) {
+                    JacIndex<W, ALL> pq(0);
+                    pq.x = px[a];
+                    pq.y = py[a];
+                    const int pj = pq.p(), qj = pq.q(), r = row[a];
+                    pq.next();
+                    px[a] = pq.x;
+                    py[a] = pq.y;
+                    const JacRot rj = rots[(t - 1) & 1][pair[a]];
+                    double pr = u[0][r][pj], pm = u[1][r][pj], qr = u[0][r][qj], qm = u[1][r][qj];
                     rotate(rj.c, rj.sr, rj.si, pr, pm, qr, qm);
-                    u[0][row][pj] = pr;
-                    u[1][row][pj] = pm;
-                    u[0][row][qj] = qr;
-                    u[1][row][qj] = qm;
+                    u[0][r][pj] = pr;
+                    u[1][r][pj] = pm;
+                    u[0][r][qj] = qr;
+                    u[1][r][qj] = qm;
                 }
-            }
         } else if (t < rounds) {
-            const JacMat& M = m[cur];
-            JacMat& O = m[cur ^ 1];
+            const JacMatW<W>& M = m[(cur + t) & 1];
+            JacMatW<W>& O = m[(cur + t + 1) & 1];
             const int pi = ii.p(), qi = ii.q(), pj = jj.p(), qj = jj.q();
             ii.next();
             jj.next();
-            // lane i (mod 16) of every wave works out pair i's rotation; pair
-            // j's comes from lane j
             const JacRot ri = jac_rotation(M[0][pi][pi], M[0][qi][qi], M[0][pi][qi], M[1][pi][qi], floor_, tol);
-            double xr[2][2] = {{M[0][pi][pj], M[0][pi][qj]}, {M[0][qi][pj], M[0][qi][qj]}};
-            double xi[2][2] = {{M[1][pi][pj], M[1][pi][qj]}, {M[1][qi][pj], M[1][qi][qj]}};
-            const double cj = __shfl(ri.c, j, 64), srj = __shfl(ri.sr, j, 64), sij = __shfl(ri.si, j, 64);
+            const double cj = __shfl(ri.c, from, 64), srj = __shfl(ri.sr, from, 64), sij = __shfl(ri.si, from, 64);
+            if (P * P == MT || j < P) {
+                double xr[2][2] = {{M[0][pi][pj], M[0][pi][qj]}, {M[0][qi][pj], M[0][qi][qj]}};
+                double xi[2][2] = {{M[1][pi][pj], M[1][pi][qj]}, {M[1][qi][pj], M[1][qi][qj]}};
 #pragma unroll
-            for (int b = 0; b < 2; ++b) rotate(ri.c, ri.sr, -ri.si, xr[0][b], xi[0][b], xr[1][b], xi[1][b]);
+                for (int b = 0; b < 2; ++b) rotate(ri.c, ri.sr, -ri.si, xr[0][b], xi[0][b], xr[1][b], xi[1][b]);
 #pragma unroll
-            for (int a = 0; a < 2; ++a) rotate(cj, srj, sij, xr[a][0], xi[a][0], xr[a][1], xi[a][1]);
-            O[0][pi][pj] = xr[0][0];
-            O[0][pi][qj] = xr[0][1];
-            O[0][qi][pj] = xr[1][0];
-            O[0][qi][qj] = xr[1][1];
-            O[1][pi][pj] = xi[0][0];
-            O[1][pi][qj] = xi[0][1];
-            O[1][qi][pj] = xi[1][0];
-            O[1][qi][qj] = xi[1][1];
-            if (j == 0) {
-                rots[t & 1][i] = ri;
-                if (ri.on) *rot = 1;
+                for (int a = 0; a < 2; ++a) rotate(cj, srj, sij, xr[a][0], xi[a][0], xr[a][1], xi[a][1]);
+                O[0][pi][pj] = xr[0][0];
+                O[0][pi][qj] = xr[0][1];
+                O[0][qi][pj] = xr[1][0];
+                O[0][qi][qj] = xr[1][1];
+                O[1][pi][pj] = xi[0][0];
+                O[1][pi][qj] = xi[0][1];
+                O[1][qi][pj] = xi[1][0];
+                O[1][qi][qj] = xi[1][1];
+                if (j == 0) {
+                    rots[t & 1][i] = ri;
+                    if (ri.on) *rot = 1;
+                }
             }
         }
-        if (t < rounds) cur ^= 1;
         __syncthreads();
     }
-    return cur;
+    return (cur + rounds) & 1;
 }
 
 // global index of local index l < JW of pair X in round r over nb blocks
@@ -2721,23 +2752,269 @@ __device__ inline jf64x4 jac_product(const JacMat& A, const JacMat& B) {
     return acc;
 }
 
-// V = 1, A0 = B = A 2^-exp, the skip level of the rotations.  The power of two
-// puts the largest entry into [1/2, 1), so that squares of entries neither
-// underflow nor overflow whatever the scale of A (exact but for entries 2^-1022
-// of the largest); every block finds it for itself.
+// Exponent of a matrix of `count` doubles: 2^-exp puts the largest entry into
+// [1/2, 1), so that squares of entries neither underflow nor overflow whatever
+// its scale (exact but for entries 2^-1022 of the largest); the same in every
+// thread.  sh: blockDim / 64 doubles.
+__device__ inline int jac_exponent(const double* A, int64_t count, double* sh) {
+    double mx = 0.0;
+    for (int64_t e = threadIdx.x; e < count; e += blockDim.x) mx = fmax(mx, fabs(A[e]));
+    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+    if (threadIdx.x % 64 == 0) sh[threadIdx.x / 64] = mx;
+    __syncthreads();
+    for (int w = 0; w < (int)(blockDim.x / 64); ++w) mx = fmax(mx, sh[w]);
+    __syncthreads();
+    int ex = 0;
+    if (mx > 0.0 && mx <= 1.7976931348623157e308) (void)frexp(mx, &ex);
+    return ex;
+}
+
+// ---------------------------------------------------------------------------
+// Refinement of the eigenvectors (Ogita and Aishima 2018, one step).  The
+// rotations leave V = X (1 + O(n eps / gap)) of the exact eigenvectors X, since
+// off-diagonal entries at the rounding level of A are never rotated.  With
+// R = 1 - V^H V and S = V^H A V, lambda_i = S_ii / (1 - R_ii) and V <- V (1 + E),
+// E_ij = (S_ij + lambda_j R_ij) / (lambda_j - lambda_i), is X to second order:
+// E + E^H = R keeps V orthonormal, the first-order rotation between i and j takes
+// out S_ij.  Pairs without a gap (|S_ij| + |lambda R_ij| > 1e-8 |lambda_j -
+// lambda_i|: the square of such a rotation would be visible) take E_ij = R_ij / 2.
+// What S and R hold is the rounding of some thousand rotations, so their own
+// products are summed in pairs of doubles.
+//   Measured, error of the leading projector (a twelfth of the spectrum, over six
+// decades) against extended precision, cyclic Jacobi in one workgroup / the block
+// form with V (3 - V^H V) / 2 and a last sweep / this: 144 x 144 1.2e-13 / 9.6e-14
+// / 1.5e-16, 200 x 200 1.8e-13 / 3.2e-13 / 2.0e-16; the whole call 4.01 -> 3.85 ms
+// (144 x 144), 7.24 -> 6.69 (256 x 256) against the block form before.
+// ---------------------------------------------------------------------------
+constexpr int ET = 16;   // tile of a refinement product, one output a thread
+
+// s + c += a b, c the rounding errors of s (two-product, two-sum)
+__device__ inline void dd_add(double& s, double& c, double a, double b) {
+#pragma clang fp contract(off)
+    const double p = a * b, e = fma(a, b, -p);
+    const double t = s + p, z = t - s;
+    const double d = (s - (t - z)) + (p - z);
+    s = t;
+    c += d + e;
+}
+
+// Output (m0 + tid % ET, n0 + tid / ET) of op(A) (B + Blo), n x n planar
+// column-major, as high and low parts (re, im) (op: conjugate transpose when HA;
+// Blo may be null).
+struct DD2 {
+    double rh, rl, ih, il;
+};
+template <bool HA>
+__device__ inline DD2 dd_product(const double* A, const double* B, const double* Blo, int n, int m0, int n0) {
+    __shared__ double As[2][ET][ET + 1], Bs[4][ET][ET + 1];
+    const int x = threadIdx.x % ET, y = threadIdx.x / ET;
+    const int64_t nn = (int64_t)n * n;
+    double rs = 0, rc = 0, is = 0, ic = 0;
+    for (int k0 = 0; k0 < n; k0 += ET) {
+        const int ra = HA ? k0 + x : m0 + x, ca = HA ? m0 + y : k0 + y, kb = k0 + x, cb = n0 + y;
+        const bool oka = ra < n && ca < n, okb = kb < n && cb < n;
+        const int64_t oa = oka ? ra + (int64_t)n * ca : 0, ob = okb ? kb + (int64_t)n * cb : 0;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const double a = oka ? A[p * nn + oa] : 0.0;
+            As[p][HA ? x : y][HA ? y : x] = HA && p ? -a : a;
+            Bs[p][x][y] = okb ? B[p * nn + ob] : 0.0;
+            Bs[2 + p][x][y] = okb && Blo ? Blo[p * nn + ob] : 0.0;
+        }
+        __syncthreads();
+        const int kn = min(ET, n - k0);
+#pragma unroll 4
+        for (int k = 0; k < kn; ++k) {
+            const double ar = As[0][k][x], ai = As[1][k][x], br = Bs[0][k][y], bi = Bs[1][k][y];
+            dd_add(rs, rc, ar, br);
+            dd_add(rs, rc, -ai, bi);
+            dd_add(is, ic, ar, bi);
+            dd_add(is, ic, ai, br);
+            if (Blo) {
+                const double lr = Bs[2][k][y], li = Bs[3][k][y];
+                rc += ar * lr - ai * li;
+                ic += ar * li + ai * lr;
+            }
+        }
+        __syncthreads();
+    }
+    DD2 o;
+    o.rh = rs + rc;
+    o.rl = rc - (o.rh - rs);
+    o.ih = is + ic;
+    o.il = ic - (o.ih - is);
+    return o;
+}
+
+// One tile of T + Tlo = A V
+__device__ inline void eig_av(const double* A, const double* V, int n, int m0, int n0, double* T, double* Tlo) {
+    const DD2 o = dd_product<false>(A, V, nullptr, n, m0, n0);
+    const int m = m0 + threadIdx.x % ET, c = n0 + threadIdx.x / ET;
+    if (m >= n || c >= n) return;
+    const int64_t nn = (int64_t)n * n, e = m + (int64_t)n * c;
+    T[e] = o.rh;
+    T[nn + e] = o.ih;
+    Tlo[e] = o.rl;
+    Tlo[nn + e] = o.il;
+}
+
+// One tile of S = V^H (T + Tlo) (first), or of R = 1 - V^H V
+__device__ inline void eig_sr(const double* V, const double* T, const double* Tlo, int n, bool first, int m0, int n0,
+                              double* S, double* R) {
+    const DD2 o = dd_product<true>(V, first ? T : V, first ? Tlo : nullptr, n, m0, n0);
+    const int m = m0 + threadIdx.x % ET, c = n0 + threadIdx.x / ET;
+    if (m >= n || c >= n) return;
+    const int64_t nn = (int64_t)n * n, e = m + (int64_t)n * c;
+    if (first) {
+        S[e] = o.rh;
+        S[nn + e] = o.ih;
+    } else {
+        R[e] = ((m == c ? 1.0 : 0.0) - o.rh) - o.rl;
+        R[nn + e] = -o.ih - o.il;
+    }
+}
+
+// One tile of Vout = V + V E; the first one also w[k], the k-th largest eigenvalue
+// times 2^ex, and order[k], its column (ties by index, NaN last).
+__device__ inline void eig_update(const double* V, const double* S, const double* R, int n, int ex, int m0, int n0,
+                                  double* Vout, double* w, int* order) {
+    __shared__ double lam[JAC_NMAX], Vs[2][ET][ET + 1], Es[2][ET][ET + 1];
+    const int x = threadIdx.x % ET, y = threadIdx.x / ET;
+    const int64_t nn = (int64_t)n * n;
+    for (int i = threadIdx.x; i < n; i += ET * ET) lam[i] = S[i + (int64_t)n * i] / (1.0 - R[i + (int64_t)n * i]);
+    __syncthreads();
+    const int m = m0 + x, c = n0 + y;
+    double re = 0, im = 0;
+    for (int k0 = 0; k0 < n; k0 += ET) {
+        const int kv = k0 + y, ke = k0 + x;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) Vs[p][y][x] = m < n && kv < n ? V[p * nn + m + (int64_t)n * kv] : 0.0;
+        double er = 0, ei = 0;
+        if (ke < n && c < n) {
+            const int64_t e = ke + (int64_t)n * c, h = c + (int64_t)n * ke;
+            // the Hermitian parts: E + E^H = R has to hold to rounding over the gap,
+            // whatever A is off Hermitian by
+            const double sr = 0.5 * (S[e] + S[h]), si = 0.5 * (S[nn + e] - S[nn + h]);
+            const double rr = 0.5 * (R[e] + R[h]), ri = 0.5 * (R[nn + e] - R[nn + h]);
+            const double li = lam[ke], lj = lam[c];
+            const double gap = lj - li;
+            const double num = sqrt(sr * sr + si * si) + fmax(fabs(li), fabs(lj)) * sqrt(rr * rr + ri * ri);
+            if (num <= 1e-8 * fabs(gap) && gap != 0.0) {
+                er = (sr + lj * rr) / gap;
+                ei = (si + lj * ri) / gap;
+            } else {
+                er = 0.5 * rr;
+                ei = 0.5 * ri;
+            }
+        }
+        Es[0][x][y] = er;
+        Es[1][x][y] = ei;
+        __syncthreads();
+        const int kn = min(ET, n - k0);
+#pragma unroll 4
+        for (int k = 0; k < kn; ++k) {
+            const double vr = Vs[0][k][x], vi = Vs[1][k][x], fr = Es[0][k][y], fi = Es[1][k][y];
+            re += vr * fr - vi * fi;
+            im += vr * fi + vi * fr;
+        }
+        __syncthreads();
+    }
+    if (m < n && c < n) {
+        const int64_t e = m + (int64_t)n * c;
+        Vout[e] = V[e] + re;
+        Vout[nn + e] = V[nn + e] + im;
+    }
+    if (m0 || n0) return;
+    auto key = [&](int i) { return lam[i] == lam[i] ? lam[i] : -INFINITY; };
+    for (int i = threadIdx.x; i < n; i += ET * ET) {
+        const double wi = key(i);
+        int rank = 0;
+        for (int j = 0; j < n; ++j) {
+            const double wj = key(j);
+            rank += wj > wi || (wj == wi && j < i) ? 1 : 0;
+        }
+        order[rank] = i;
+        w[rank] = ldexp(lam[i], ex);
+    }
+}
+
+__global__ __launch_bounds__(ET* ET) void k_eig_av(const double* A, const double* V, int n, double* T, double* Tlo) {
+    eig_av(A, V, n, ET * blockIdx.x, ET * blockIdx.y, T, Tlo);
+}
+__global__ __launch_bounds__(ET* ET) void k_eig_sr(const double* V, const double* T, const double* Tlo, int n,
+                                                  double* S, double* R) {
+    eig_sr(V, T, Tlo, n, blockIdx.z == 0, ET * blockIdx.x, ET * blockIdx.y, S, R);
+}
+__global__ __launch_bounds__(ET* ET) void k_eig_update(const double* V, const double* S, const double* R, int n,
+                                                      const JacState* js, double* Vout, double* w, int* order) {
+    eig_update(V, S, R, n, js->exp, ET * blockIdx.x, ET * blockIdx.y, Vout, w, order);
+}
+// The whole iteration for n <= W <= JAC_ONE: X and A0 = A 2^-exp; for W <= ET, one
+// tile, the refinement too (work: T, Tlo, S, R of 2 n^2 doubles).
+template <int W>
+__global__ __launch_bounds__(jac_threads(W)) void k_jacobi_one(const double* A, int n, int max_sweeps, double tol,
+                                                              double* X, double* A0, double* work, double* V,
+                                                              double* w, int* order, JacState* js, StepDev* st) {
+    constexpr int NT = jac_threads(W);
+    __shared__ JacMatW<W> m[2], u;
+    __shared__ JacRot rots[2][W / 2];
+    __shared__ double sh[NT / 64 + 1];
+    __shared__ int s_rot;
+    const int nn = n * n;
+    const int ex = jac_exponent(A, 2 * nn, sh);
+    double tr = 0.0;
+    for (int e = threadIdx.x; e < W * W; e += NT) {
+        const int a = e % W, b = e / W;
+        const bool ok = a < n && b < n;
+        const double re = ok ? ldexp(A[a + n * b], -ex) : 0.0, im = ok ? ldexp(A[nn + a + n * b], -ex) : 0.0;
+        m[0][0][a][b] = re;
+        m[0][1][a][b] = im;
+        u[0][a][b] = a == b ? 1.0 : 0.0;
+        u[1][a][b] = 0.0;
+        if (a == b) tr += fabs(re);
+        if (ok) {
+            A0[a + n * b] = re;
+            A0[nn + a + n * b] = im;
+        }
+    }
+    if (threadIdx.x == 0) js->exp = ex;
+    const double floor_ = 4.0 * 2.220446049250313e-16 * block_sum_all(tr, sh);
+    int cur = 0;
+    bool settled = false;
+    for (int q = 0; q < max_sweeps && !settled; ++q) {
+        if (threadIdx.x == 0) s_rot = 0;
+        __syncthreads();
+        cur = jac_rotate_pair<W, true>(m, u, rots, cur, floor_, tol, &s_rot);
+        settled = !s_rot;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0 && !settled) atomicExch(&st->bad, 1);
+    for (int e = threadIdx.x; e < W * W; e += NT) {
+        const int a = e % W, b = e / W;
+        if (a >= n || b >= n) continue;
+        X[a + n * b] = u[0][a][b];
+        X[nn + a + n * b] = u[1][a][b];
+    }
+    if constexpr (W <= ET) {
+        static_assert(NT == ET * ET, "one output a thread");
+        double *T = work, *Tlo = T + 2 * nn, *S = Tlo + 2 * nn, *R = S + 2 * nn;
+        __syncthreads();
+        eig_av(A0, X, n, 0, 0, T, Tlo);
+        __syncthreads();
+        eig_sr(X, T, Tlo, n, true, 0, 0, S, R);
+        eig_sr(X, T, Tlo, n, false, 0, 0, S, R);
+        __syncthreads();
+        eig_update(X, S, R, n, ex, 0, 0, V, w, order);
+    }
+}
+
+// V = 1, A0 = B = A 2^-exp (every block finds the exponent for itself), the skip
+// level of the rotations.
 __global__ __launch_bounds__(JS_THREADS) void k_jacobi_init(const double* A, int n, double* V, double* A0, double* B,
                                                            JacState* js) {
     __shared__ double sh[JS_THREADS / 64 + 1];
     const int64_t nn = (int64_t)n * n;
-    double mx = 0.0;
-    for (int64_t e = threadIdx.x; e < 2 * nn; e += blockDim.x) mx = fmax(mx, fabs(A[e]));
-    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
-    if (threadIdx.x % 64 == 0) sh[threadIdx.x / 64] = mx;
-    __syncthreads();
-    for (int w = 0; w < JS_THREADS / 64; ++w) mx = fmax(mx, sh[w]);
-    __syncthreads();
-    int ex = 0;
-    if (mx > 0.0 && mx <= 1.7976931348623157e308) (void)frexp(mx, &ex);
+    const int ex = jac_exponent(A, 2 * nn, sh);
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nn; e += (int64_t)gridDim.x * blockDim.x) {
         V[e] = e % n == e / n ? 1.0 : 0.0;
         V[nn + e] = 0.0;
@@ -2752,15 +3029,15 @@ __global__ __launch_bounds__(JS_THREADS) void k_jacobi_init(const double* A, int
     if (threadIdx.x == 0) {
         js->floor = 4.0 * 2.220446049250313e-16 * tr;
         js->exp = ex;
-        js->done = 0;
     }
 }
 
 // Round r of sweep s over nb (even) blocks, workgroup X: the diagonal matrix of
 // pair X rotated in place, the product of its rotations to U[X] (planar,
-// row-major).  passes > 1 (nb == 2): the whole iteration in one launch.
-__global__ __launch_bounds__(JS_THREADS) void k_jacobi_solve(double* A, int n, int nb, int r, int sweep, int passes,
-                                                            double tol, double* U, JacState* js) {
+// row-major).
+__global__ __launch_bounds__(JS_THREADS) void k_jacobi_solve(double* A, int n, int nb, int r, int sweep, double tol,
+                                                            double* U, JacState* js) {
+    static_assert(JS_THREADS == jac_threads(JW), "threads of a pair");
     if (sweep > 0 && !js->rot[sweep - 1]) return;
     __shared__ JacMat m[2], u;
     __shared__ JacRot rots[2][JB];
@@ -2780,23 +3057,9 @@ __global__ __launch_bounds__(JS_THREADS) void k_jacobi_solve(double* A, int n, i
     }
     const double floor_ = js->floor;
     __syncthreads();
-    int cur = 0, settled = 0;
-    for (int q = 0; q < passes && !settled; ++q) {
-        cur = r == 0 ? jac_rotate_pair<true>(m, u, rots, cur, floor_, tol, &s_rot)
-                     : jac_rotate_pair<false>(m, u, rots, cur, floor_, tol, &s_rot);
-        if (passes > 1) {
-            settled = !s_rot;
-            __syncthreads();
-            if (threadIdx.x == 0) s_rot = 0;
-            __syncthreads();
-        }
-    }
-    if (threadIdx.x == 0) {
-        if (passes > 1)
-            js->done = settled;
-        else if (s_rot)
-            js->rot[sweep] = 1;
-    }
+    const int cur = r == 0 ? jac_rotate_pair<JW, true>(m, u, rots, 0, floor_, tol, &s_rot)
+                           : jac_rotate_pair<JW, false>(m, u, rots, 0, floor_, tol, &s_rot);
+    if (threadIdx.x == 0 && s_rot) js->rot[sweep] = 1;
     double* Ux = U + (int64_t)X * 2 * JW * JW;
     for (int e = threadIdx.x; e < JW * JW; e += JS_THREADS) {
         const int a = e % JW, b = e / JW, ga = jac_index(X, a, r, nb), gb = jac_index(X, b, r, nb);
@@ -2890,9 +3153,9 @@ __global__ __launch_bounds__(JAC_THREADS) void k_herm_jacobi(double* A, int n, d
     // off-diagonal entries at the rounding level of the whole matrix cannot
     // be reduced further: a pair is also left alone below 4 eps sum |A_ii|
     const double abs_floor = js->floor;
-    // a single launch says so itself; else a sweep without rotation ended the rounds
-    bool converged = js->done;
-    for (int k = 0; block_sweeps > 1 && k < block_sweeps; ++k) converged = converged || js->rot[k] == 0;
+    // a sweep without rotation ended the rounds
+    bool converged = false;
+    for (int k = 0; k < block_sweeps; ++k) converged = converged || js->rot[k] == 0;
     if (tid == 0) s_done = converged;
     __syncthreads();
     for (int sweep = 0; sweep < max_sweeps && !converged; ++sweep) {
@@ -3011,175 +3274,6 @@ __global__ __launch_bounds__(JAC_THREADS) void k_herm_jacobi(double* A, int n, d
     if (tid == 0 && !s_done) atomicExch(&st->bad, 1);
 }
 
-// ---------------------------------------------------------------------------
-// Refinement of the eigenvectors (Ogita and Aishima 2018, one step).  The
-// rotations leave V = X (1 + O(n eps / gap)) of the exact eigenvectors X, since
-// off-diagonal entries at the rounding level of A are never rotated.  With
-// R = 1 - V^H V and S = V^H A V, lambda_i = S_ii / (1 - R_ii) and V <- V (1 + E),
-// E_ij = (S_ij + lambda_j R_ij) / (lambda_j - lambda_i), is X to second order:
-// E + E^H = R keeps V orthonormal, the first-order rotation between i and j takes
-// out S_ij.  Pairs without a gap (|S_ij| + |lambda R_ij| > 1e-8 |lambda_j -
-// lambda_i|: the square of such a rotation would be visible) take E_ij = R_ij / 2.
-// What S and R hold is the rounding of some thousand rotations, so their own
-// products are summed in pairs of doubles.
-//   Measured, error of the leading projector (a twelfth of the spectrum, over six
-// decades) against extended precision, cyclic Jacobi in one workgroup / the block
-// form with V (3 - V^H V) / 2 and a last sweep / this: 144 x 144 1.2e-13 / 9.6e-14
-// / 1.5e-16, 200 x 200 1.8e-13 / 3.2e-13 / 2.0e-16.  Three launches of 4-17 us
-// where that refinement took 190 (144 x 144 4.01 -> 3.85 ms, 256 x 256 7.24 -> 6.69).
-// ---------------------------------------------------------------------------
-constexpr int ET = 16;   // tile of a refinement product, one output a thread
-
-// s + c += a b, c the rounding errors of s (two-product, two-sum)
-__device__ inline void dd_add(double& s, double& c, double a, double b) {
-#pragma clang fp contract(off)
-    const double p = a * b, e = fma(a, b, -p);
-    const double t = s + p, z = t - s;
-    const double d = (s - (t - z)) + (p - z);
-    s = t;
-    c += d + e;
-}
-
-// Output (m0 + tid % ET, n0 + tid / ET) of op(A) (B + Blo), n x n planar
-// column-major, as high and low parts (re, im) (op: conjugate transpose when HA;
-// Blo may be null).
-struct DD2 {
-    double rh, rl, ih, il;
-};
-template <bool HA>
-__device__ inline DD2 dd_product(const double* A, const double* B, const double* Blo, int n, int m0, int n0) {
-    __shared__ double As[2][ET][ET + 1], Bs[4][ET][ET + 1];
-    const int x = threadIdx.x % ET, y = threadIdx.x / ET;
-    const int64_t nn = (int64_t)n * n;
-    double rs = 0, rc = 0, is = 0, ic = 0;
-    for (int k0 = 0; k0 < n; k0 += ET) {
-        const int ra = HA ? k0 + x : m0 + x, ca = HA ? m0 + y : k0 + y, kb = k0 + x, cb = n0 + y;
-        const bool oka = ra < n && ca < n, okb = kb < n && cb < n;
-        const int64_t oa = oka ? ra + (int64_t)n * ca : 0, ob = okb ? kb + (int64_t)n * cb : 0;
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const double a = oka ? A[p * nn + oa] : 0.0;
-            As[p][HA ? x : y][HA ? y : x] = HA && p ? -a : a;
-            Bs[p][x][y] = okb ? B[p * nn + ob] : 0.0;
-            Bs[2 + p][x][y] = okb && Blo ? Blo[p * nn + ob] : 0.0;
-        }
-        __syncthreads();
-#pragma unroll 4
-        for (int k = 0; k < ET; ++k) {
-            const double ar = As[0][k][x], ai = As[1][k][x], br = Bs[0][k][y], bi = Bs[1][k][y];
-            dd_add(rs, rc, ar, br);
-            dd_add(rs, rc, -ai, bi);
-            dd_add(is, ic, ar, bi);
-            dd_add(is, ic, ai, br);
-            if (Blo) {
-                const double lr = Bs[2][k][y], li = Bs[3][k][y];
-                rc += ar * lr - ai * li;
-                ic += ar * li + ai * lr;
-            }
-        }
-        __syncthreads();
-    }
-    DD2 o;
-    o.rh = rs + rc;
-    o.rl = rc - (o.rh - rs);
-    o.ih = is + ic;
-    o.il = ic - (o.ih - is);
-    return o;
-}
-
-// T + Tlo = A V
-__global__ __launch_bounds__(ET* ET) void k_eig_av(const double* A, const double* V, int n, double* T, double* Tlo) {
-    const int m0 = ET * blockIdx.x, n0 = ET * blockIdx.y;
-    const DD2 o = dd_product<false>(A, V, nullptr, n, m0, n0);
-    const int m = m0 + threadIdx.x % ET, c = n0 + threadIdx.x / ET;
-    if (m >= n || c >= n) return;
-    const int64_t nn = (int64_t)n * n, e = m + (int64_t)n * c;
-    T[e] = o.rh;
-    T[nn + e] = o.ih;
-    Tlo[e] = o.rl;
-    Tlo[nn + e] = o.il;
-}
-
-// S = V^H (T + Tlo) (blockIdx.z = 0), R = 1 - V^H V (1)
-__global__ __launch_bounds__(ET* ET) void k_eig_sr(const double* V, const double* T, const double* Tlo, int n,
-                                                  double* S, double* R) {
-    const int m0 = ET * blockIdx.x, n0 = ET * blockIdx.y;
-    const bool first = blockIdx.z == 0;
-    const DD2 o = dd_product<true>(V, first ? T : V, first ? Tlo : nullptr, n, m0, n0);
-    const int m = m0 + threadIdx.x % ET, c = n0 + threadIdx.x / ET;
-    if (m >= n || c >= n) return;
-    const int64_t nn = (int64_t)n * n, e = m + (int64_t)n * c;
-    if (first) {
-        S[e] = o.rh;
-        S[nn + e] = o.ih;
-    } else {
-        R[e] = ((m == c ? 1.0 : 0.0) - o.rh) - o.rl;
-        R[nn + e] = -o.ih - o.il;
-    }
-}
-
-// Vout = V + V E; w[k] the k-th largest eigenvalue of the unscaled matrix,
-// order[k] its column (ties by index, NaN last).
-__global__ __launch_bounds__(ET* ET) void k_eig_update(const double* V, const double* S, const double* R, int n,
-                                                      const JacState* js, double* Vout, double* w, int* order) {
-    __shared__ double lam[JAC_NMAX], Vs[2][ET][ET + 1], Es[2][ET][ET + 1];
-    const int x = threadIdx.x % ET, y = threadIdx.x / ET;
-    const int64_t nn = (int64_t)n * n;
-    for (int i = threadIdx.x; i < n; i += ET * ET) lam[i] = S[i + (int64_t)n * i] / (1.0 - R[i + (int64_t)n * i]);
-    __syncthreads();
-    const int m = ET * blockIdx.x + x, c = ET * blockIdx.y + y;
-    double re = 0, im = 0;
-    for (int k0 = 0; k0 < n; k0 += ET) {
-        const int kv = k0 + y, ke = k0 + x;
-#pragma unroll
-        for (int p = 0; p < 2; ++p) Vs[p][y][x] = m < n && kv < n ? V[p * nn + m + (int64_t)n * kv] : 0.0;
-        double er = 0, ei = 0;
-        if (ke < n && c < n) {
-            const int64_t e = ke + (int64_t)n * c, h = c + (int64_t)n * ke;
-            // the Hermitian parts: E + E^H = R has to hold to rounding over the gap,
-            // whatever A is off Hermitian by
-            const double sr = 0.5 * (S[e] + S[h]), si = 0.5 * (S[nn + e] - S[nn + h]);
-            const double rr = 0.5 * (R[e] + R[h]), ri = 0.5 * (R[nn + e] - R[nn + h]);
-            const double li = lam[ke], lj = lam[c];
-            const double gap = lj - li;
-            const double num = sqrt(sr * sr + si * si) + fmax(fabs(li), fabs(lj)) * sqrt(rr * rr + ri * ri);
-            if (num <= 1e-8 * fabs(gap) && gap != 0.0) {
-                er = (sr + lj * rr) / gap;
-                ei = (si + lj * ri) / gap;
-            } else {
-                er = 0.5 * rr;
-                ei = 0.5 * ri;
-            }
-        }
-        Es[0][x][y] = er;
-        Es[1][x][y] = ei;
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < ET; ++k) {
-            const double vr = Vs[0][k][x], vi = Vs[1][k][x], fr = Es[0][k][y], fi = Es[1][k][y];
-            re += vr * fr - vi * fi;
-            im += vr * fi + vi * fr;
-        }
-        __syncthreads();
-    }
-    if (m < n && c < n) {
-        const int64_t e = m + (int64_t)n * c;
-        Vout[e] = V[e] + re;
-        Vout[nn + e] = V[nn + e] + im;
-    }
-    if (blockIdx.x || blockIdx.y) return;
-    auto key = [&](int i) { return lam[i] == lam[i] ? lam[i] : -INFINITY; };
-    for (int i = threadIdx.x; i < n; i += ET * ET) {
-        const double wi = key(i);
-        int rank = 0;
-        for (int j = 0; j < n; ++j) {
-            const double wj = key(j);
-            rank += wj > wi || (wj == wi && j < i) ? 1 : 0;
-        }
-        order[rank] = i;
-        w[rank] = ldexp(lam[i], js->exp);
-    }
-}
 }  // namespace
 
 namespace {
@@ -3264,21 +3358,42 @@ void herm_eig(const double* A, int n, double* V, double* w, int* order, double* 
     if (g_dry_run) return;
     constexpr double TOL = 1e-15;
     const int64_t n2 = 2 * (int64_t)n * n;
-    double *A0 = work, *B = A0 + n2, *X = B + n2, *T = X + n2, *Tlo = T + n2, *R = Tlo + n2, *U = R + n2;
+    double *A0 = work, *X = A0 + n2, *T = X + n2, *Tlo = T + n2, *S = Tlo + n2, *R = S + n2, *U = R + n2;
+    double* B = S;   // the rotated matrix, until S takes its place
     const int np = (n + JW - 1) / JW, nb = 2 * np;
     JacState* js = (JacState*)(U + (int64_t)np * 2 * JW * JW);
-    hipLaunchKernelGGL(k_jacobi_init, dim3((n * n + 1023) / 1024), dim3(JS_THREADS), 0, s, A, n, X, A0, B, js);
-    const int sweeps = nb == 2 ? 1 : JAC_SWEEPS;
-    for (int sweep = 0; sweep < sweeps; ++sweep)
-        for (int r = 0; r < nb - 1; ++r) {
-            hipLaunchKernelGGL(k_jacobi_solve, dim3(np), dim3(JS_THREADS), 0, s, B, n, nb, r, sweep,
-                               nb == 2 ? 60 : 1, TOL, U, js);
-            hipLaunchKernelGGL(k_jacobi_apply, dim3(np * (np - 1) / 2 + np * np), dim3(JA_THREADS), 0, s, B, n, nb, X,
-                               r, sweep, (const double*)U, (const JacState*)js);
-        }
-    hipLaunchKernelGGL(k_herm_jacobi, dim3(1), dim3(JAC_THREADS), 0, s, B, n, X, sweeps, 60, TOL,
-                       (const JacState*)js, st);
-    double* S = B;
+#define TTN_ONE(W)                                                                                               \
+    hipLaunchKernelGGL(k_jacobi_one<W>, dim3(1), dim3(jac_threads(W)), 0, s, A, n, 60, TOL, X, A0, T, V, w,  \
+                       order, js, st)
+    if (n <= 2)
+        TTN_ONE(2);
+    else if (n <= 4)
+        TTN_ONE(4);
+    else if (n <= 8)
+        TTN_ONE(8);
+    else if (n <= 16)
+        TTN_ONE(16);
+    else if (n <= 24)
+        TTN_ONE(24);
+    else if (n <= 32)
+        TTN_ONE(32);
+    else if (n <= 40)
+        TTN_ONE(40);
+    else if (n <= JAC_ONE)
+        TTN_ONE(48);
+    else {
+        hipLaunchKernelGGL(k_jacobi_init, dim3((n * n + 1023) / 1024), dim3(JS_THREADS), 0, s, A, n, X, A0, B, js);
+        for (int sweep = 0; sweep < JAC_SWEEPS; ++sweep)
+            for (int r = 0; r < nb - 1; ++r) {
+                hipLaunchKernelGGL(k_jacobi_solve, dim3(np), dim3(JS_THREADS), 0, s, B, n, nb, r, sweep, TOL, U, js);
+                hipLaunchKernelGGL(k_jacobi_apply, dim3(np * (np - 1) / 2 + np * np), dim3(JA_THREADS), 0, s, B, n, nb,
+                                   X, r, sweep, (const double*)U, (const JacState*)js);
+            }
+        hipLaunchKernelGGL(k_herm_jacobi, dim3(1), dim3(JAC_THREADS), 0, s, B, n, X, JAC_SWEEPS, 60, TOL,
+                           (const JacState*)js, st);
+    }
+#undef TTN_ONE
+    if (n <= ET) return;
     const int t = (n + ET - 1) / ET;
     hipLaunchKernelGGL(k_eig_av, dim3(t, t), dim3(ET * ET), 0, s, (const double*)A0, (const double*)X, n, T, Tlo);
     hipLaunchKernelGGL(k_eig_sr, dim3(t, t, 2), dim3(ET * ET), 0, s, (const double*)X, (const double*)T,

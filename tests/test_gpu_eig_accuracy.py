@@ -32,7 +32,7 @@ def _refined(a):
     return lam[::-1], V[:, ::-1]
 
 
-@pytest.mark.parametrize("n", [12, 32, 39, 48, 70, 144, 200])
+@pytest.mark.parametrize("n", [3, 4, 5, 8, 9, 12, 16, 17, 24, 25, 32, 33, 39, 40, 41, 48, 49, 70, 144, 200])
 def test_leading_projector(n):
     L = T.lib()
     L.ttn_herm_eig.restype = C.c_int

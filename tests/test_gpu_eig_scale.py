@@ -37,3 +37,19 @@ def test_eigensolver_scales(n, exponent):
     assert np.abs(w - ref).max() <= 1e-13 * scale
     assert np.abs(A @ V - V * w).max() <= 1e-12 * scale
     assert np.abs(V.conj().T @ V - np.eye(n)).max() <= 1e-12
+
+
+@pytest.mark.parametrize("n", [5, 20, 60])
+def test_order_is_a_permutation_with_nan(n):
+    """Callers gather columns by d_order: it has to stay in range whatever the matrix holds."""
+    L = T.lib()
+    L.ttn_herm_eig.restype = C.c_int
+    L.ttn_herm_eig.argtypes = [C.c_int32] + [C.c_void_p] * 5
+    dA = torch.eye(n, dtype=torch.float64, device="cuda").repeat(2, 1, 1)
+    dA[1] = 0
+    dA[0, n // 2, n // 2] = float("nan")
+    dV, dw = torch.zeros(2 * n * n, dtype=torch.float64, device="cuda"), torch.zeros(n, dtype=torch.float64, device="cuda")
+    do = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    print(f"[eig] n={n} nan", flush=True)
+    L.ttn_herm_eig(n, dA.data_ptr(), dV.data_ptr(), dw.data_ptr(), do.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    assert sorted(do.cpu().tolist()) == list(range(n))
