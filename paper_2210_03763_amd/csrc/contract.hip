@@ -1246,17 +1246,57 @@ void launch_aligned(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, bool
     if (p.splits > 1) splitk_reduce(g, p.splits, (const R*)ws.partial, s);
 }
 
-// Launch of k_cgemm_split with bm x bn tiles (128 x 128, 64 x 128, 128 x 64)
-// and np pieces; grids that leave the chip idle (one 128 x 128 block per CU, two
-// of the others) split K, at least four k-tiles each.
-void launch_split(const Gemm<float>& g, const GemmScratch& ws, hipStream_t s, int np, int bm, int bn, bool a_k,
-                  bool b_k, CgemmInfo* info) {
+// Estimated time (us) of the pass over split K's partial sums.
+template <typename R>
+double reduce_us(const Gemm<R>& g, int splits) {
+    return splits < 2 ? 0.0 : 1.0 + splits * 4.0 * sizeof(R) * g.M * (double)g.N * g.B1 * g.B2 / 7.2e6;
+}
+
+// Tiles and split factor of a k_cgemm_split launch with np pieces: of 128 x 128, 64 x
+// 128 and 128 x 64 tiles and the factors that leave at least four k-tiles to a
+// block, the least of the estimated time: rounds of blocks over the CUs (from the
+// third on, half of what the last one leaves empty is made up for), each 0.116 us per k (two pieces: 0.06) with 34 k of prologue and epilogue, of the half
+// tiles 0.78 alone on a CU and 0.61 beside others, and the pass over the partial
+// sums (within 7 % on average of 1386 launches of 66 shapes, its choice within 1 %
+// of the best one).  Splitting K until a grid covers the chip loses where that
+// pass is long or the last round short (us, split so / this: 64 x 26624 outputs,
+// K = 256, 208 tiles 44 / 31; 128 x 4320 of five, K = 128, 170 tiles 41 / 22; 972 x
+// 144 of seventeen, K = 144 47 / 30).
+struct SplitPlan {
+    int bm, bn, splits;
+};
+inline SplitPlan plan_split(const Gemm<float>& g, const GemmScratch& ws, int np) {
+    const int K = (g.Kin + 15) / 16 * 16 * g.Kout;
+    SplitPlan p{0, 0, 1};
+    double least = 0.0;
+    for (const auto& t : {SplitPlan{128, 128, 1}, SplitPlan{64, 128, 1}, SplitPlan{128, 64, 1}}) {
+        const bool wide = t.bm == t.bn;
+        const int64_t tiles = tile_count(g, t.bm, t.bn);
+        const int most = split_factor(g, ws, tiles, K / 16, 1024, 4);
+        for (int q = 1; q <= most; ++q) {
+            const double x = tiles * q / 256.0, rounds = x <= 2 ? std::ceil(x) : 0.5 * (std::ceil(x) + x);
+            const double full = wide ? rounds : rounds <= 1 ? 0.78 : 0.61 * rounds;
+            const double us = full * (np == 3 ? 0.116 : 0.06) * ((double)K / q + 34) + reduce_us(g, q);
+            if (p.bm == 0 || us < least) {
+                least = us;
+                p = SplitPlan{t.bm, t.bn, q};
+            }
+        }
+    }
+    return p;
+}
+
+// Launch of k_cgemm_split.
+void launch_split(const Gemm<float>& g, const GemmScratch& ws, hipStream_t s, int np, bool a_k, bool b_k,
+                  CgemmInfo* info) {
+    const SplitPlan p = plan_split(g, ws, np);
+    const int bm = p.bm, bn = p.bn;
     const bool rag = g.Kin % 16 != 0;
     const int K = (g.Kin + 15) / 16 * 16 * g.Kout;
     const int tilesM = (g.M + bm - 1) / bm, tilesN = (g.N + bn - 1) / bn;
     const int64_t tiles = (int64_t)tilesM * tilesN * g.B1 * g.B2;
     const bool wide = bm == 128 && bn == 128;
-    int splits = split_factor(g, ws, tiles, K / 16, wide ? 256 : 512, 4);
+    int splits = p.splits;
     const int kchunk = (K / 16 + splits - 1) / splits * 16;
     splits = (K + kchunk - 1) / kchunk;
     const dim3 grid((unsigned)(tiles * splits)), blk(wide ? 512 : 256);
@@ -1451,7 +1491,7 @@ bool cgemm(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, char* why, in
                                        : std::initializer_list<Choice>{{64, 64, 0.40}, {32, 32, 0.36}});
         const double tf = padded(g.M, g.N, f.bm, f.bn) / f.rate, ts = padded(g.M, g.N, t.bm, t.bn) / t.rate;
         if (bf16 || (flops >= SPLIT_MIN_FLOPS && ts < tf)) {
-            launch_split(g, ws, s, bf16 ? 2 : 3, t.bm, t.bn, a_k, b_k, info);
+            launch_split(g, ws, s, bf16 ? 2 : 3, a_k, b_k, info);
             if (ev1) (void)hipEventRecord(ev1, s);
             return true;
         }
