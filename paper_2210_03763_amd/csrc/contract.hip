@@ -1255,13 +1255,14 @@ double reduce_us(const Gemm<R>& g, int splits) {
 // Tiles and split factor of a k_cgemm_split launch with np pieces: of 128 x 128, 64 x
 // 128 and 128 x 64 tiles and the factors that leave at least four k-tiles to a
 // block, the least of the estimated time: rounds of blocks over the CUs (from the
-// third on, half of what the last one leaves empty is made up for), each 0.116 us per k (two pieces: 0.06) with 34 k of prologue and epilogue, of the half
-// tiles 0.78 alone on a CU and 0.61 beside others, and the pass over the partial
-// sums (within 7 % on average of 1386 launches of 66 shapes, its choice within 1 %
-// of the best one).  Splitting K until a grid covers the chip loses where that
-// pass is long or the last round short (us, split so / this: 64 x 26624 outputs,
-// K = 256, 208 tiles 44 / 31; 128 x 4320 of five, K = 128, 170 tiles 41 / 22; 972 x
-// 144 of seventeen, K = 144 47 / 30).
+// third on, half of what the last one leaves empty is made up for), each 0.116 us
+// per k (two pieces: 0.06) with 34 k of prologue and epilogue, of the half tiles
+// 0.78 alone on a CU and 0.61 beside others, and the pass over the partial sums
+// (within 7 % on average of 1386 launches of 66 shapes, its choice within 1 % of
+// the best one).  Splitting K until a grid covers the chip loses where that pass
+// is long or the last round short (us, split so / this: 64 x 26624 outputs, K =
+// 256, 208 tiles 44 / 31; 128 x 4320 of five, K = 128, 170 tiles 41 / 22; 972 x 144 of
+// seventeen, K = 144 47 / 30).
 struct SplitPlan {
     int bm, bn, splits;
 };
@@ -1482,14 +1483,18 @@ bool cgemm(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, char* why, in
         const bool bf16 = g.split && mfma_ok && g.M >= 128 && g.N >= 128 && g.Kin % 32 == 0 &&
                           tiles128 * split_factor(g, ws, tiles128, K / 16, 256, 4) >= 128;
         // FP32 alternatives on the FP32 matrix cores: the aligned tiles (three
-        // products), or the ragged tiles (four); below 1 Gflop their shorter
+        // products), or the ragged tiles (four), which do not pad every outer index
+        // to a whole k-tile as k_cgemm_split does (256 x 256 x 20 node, parent-leg sum
+        // over five 35.9 us split / 30.1 ragged; 20 x 256 x 128, left-leg sum over 33
+        // 102 / 78); below 1 Gflop their shorter
         // prologue wins (64^3 node, right-leg stack of four, 0.54 Gflop: 10.7 us
         // against 13.8; 96^3, left-leg stack of five, 3.4 Gflop: 44.5
         // against 35.7; 208 x 208 x 144, parent-leg sum over three: 305 against
         // 163 with 128 x 64 tiles)
         const Choice f = best(mfma_ok ? std::initializer_list<Choice>{{64, 64, 0.55}, {32, 32, 0.44}}
                                        : std::initializer_list<Choice>{{64, 64, 0.40}, {32, 32, 0.36}});
-        const double tf = padded(g.M, g.N, f.bm, f.bn) / f.rate, ts = padded(g.M, g.N, t.bm, t.bn) / t.rate;
+        const double kpad = (double)((g.Kin + 15) / 16 * 16) / g.Kin;
+        const double tf = padded(g.M, g.N, f.bm, f.bn) / f.rate, ts = padded(g.M, g.N, t.bm, t.bn) / t.rate * kpad;
         if (bf16 || (flops >= SPLIT_MIN_FLOPS && ts < tf)) {
             launch_split(g, ws, s, bf16 ? 2 : 3, a_k, b_k, info);
             if (ev1) (void)hipEventRecord(ev1, s);

@@ -21,7 +21,7 @@ def _contract(prec, case, o, x):
     L.ttn_leg_contract_noalloc.argtypes = [C.c_int32] * 6 + [C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_int32,
                                                             C.c_int32, C.c_void_p]
     d_o, d_x = o.cuda(), x.cuda()
-    d_y = torch.zeros((1 if sm else K, 2, DP, DR, DL), device="cuda")
+    d_y = torch.zeros((1 if sm else K, 2, DP, DR, DL), dtype=x.dtype, device="cuda")
     rc = L.ttn_leg_contract_noalloc(prec, leg, DL, DR, DP, K, d_o.data_ptr(), d_x.data_ptr(), sm, d_y.data_ptr(), sm,
                                     0, torch.cuda.current_stream().cuda_stream)
     assert rc == 0, L.ttn_last_error(None)

@@ -1,0 +1,29 @@
+"""Contractions at the lines between the kernels' ranges, against real float64
+products of the same inputs: FP32 1e-5, FP64 1e-12 of the largest output (the
+bars of the other shapes)."""
+import pytest
+import torch
+
+from paper_2210_03763_amd import ttn as T
+from test_gpu_contract_range import _contract, _inputs
+
+pytestmark = pytest.mark.gpu
+
+# (DL, DR, DP, leg, n_ops, sum)
+# FP32 above 1 Gflop with short inner extents, which the bf16-piece kernel would pad to 16 each
+SHORT_INNER = [(8, 256, 256, 0, 33, 1), (256, 256, 20, 2, 5, 1), (20, 256, 128, 0, 33, 1), (31, 130, 130, 0, 9, 1)]
+
+
+def _check(prec, case):
+    print(f"[routes] {case} prec={prec}", flush=True)
+    dt = torch.float64 if prec == T.PREC_FP64 else torch.float32
+    o, x = (t.to(dt) for t in _inputs(case))
+    got, ref = _contract(prec, case, o, x)
+    err = ((got - ref).abs().max() / ref.abs().max()).item()
+    print(f"[routes] err {err:.2e}", flush=True)
+    assert err <= (1e-12 if prec == T.PREC_FP64 else 1e-5)
+
+
+@pytest.mark.parametrize("case", SHORT_INNER)
+def test_short_inner_extents(case):
+    _check(T.PREC_FP32, case)
