@@ -1053,9 +1053,13 @@ int split_factor(const Gemm<R>& g, const GemmScratch& ws, int64_t tiles, int kti
 // Waves per tile of k_cgemm_wave: one or two k-blocks a wave on short K;
 // sixteen waves on long K, unless there are tiles enough for several blocks
 // per CU (a stack over a 128 x 128 bond: 11.7 us with eight waves, 14.9 with
-// sixteen).
+// sixteen; 288 to 486 tiles, K = 256 to 450: sixteen 8-15 % slower); one wave
+// where the tiles alone are eight waves a CU (FP64, 160 x 36 x 20 node, parent-leg
+// stack of sixteen: 49.0 us with four, 27.2 with one; 64 x 208 x 24, stack of four
+// 30.4 / 17.9; FP32, 21 x 73 x 245, left-leg stack of four 23.7 / 17.9).
 inline int wave_count(int kblocks, int64_t tiles) {
-    return kblocks >= 16 && tiles < 512 ? 16 : kblocks >= 8 ? 8 : kblocks >= 2 ? 4 : 1;
+    if (tiles >= 2048) return 1;
+    return kblocks >= 16 && tiles <= 256 ? 16 : kblocks >= 8 ? 8 : kblocks >= 2 ? 4 : 1;
 }
 
 // Whether k_cgemm_mfma's aligned form takes a Gemm: k-tiles of 16 inside the
@@ -1078,11 +1082,16 @@ int64_t tile_count(const Gemm<R>& g, int bm, int bn) {
 // 32 x 32 tiles cover half the chip, where staging through LDS reads the
 // operands half as often (us, wave-sliced / tiles: 128 tiles with K = 64, FP64
 // 9.9 / 7.8, FP32 8.0 / 6.2; 512 tiles with K = 32, 23.3 / 11.5; below, 64 tiles
-// with K = 64 5.9 / 7.4; K = 192 over 144 tiles, FP32, 8.3 / 9.1).
+// with K = 64 5.9 / 7.4; K = 192 over 144 tiles, FP32, 8.3 / 9.1).  From there on,
+// ragged launches of at most 16 rows or columns, which its tiles do not pad to 32
+// (FP64, 9 x 208 x 624 node, right-leg product 159 us with 32 x 32 tiles, 91 here;
+// FP32, 8 x 256 x 256, left-leg sum over 33 111 / 67), while K is short (K = 4224
+// over 12 x 128 outputs of 36 74.6 / 79.7).
 template <typename R>
 bool takes_wave(const Gemm<R>& g) {
     const int64_t K = (int64_t)g.Kin * g.Kout;
-    if (8.0 * g.M * g.N * (double)K * g.B1 * (double)g.B2 >= WAVE_MAX_FLOPS) return false;
+    if (8.0 * g.M * g.N * (double)K * g.B1 * (double)g.B2 >= WAVE_MAX_FLOPS)
+        return std::min(g.M, g.N) <= 16 && K <= 1024 && !aligned_form(g);
     return !(aligned_form(g) && g.M >= 32 && g.N >= 32 && tile_count(g, 32, 32) >= (K > 128 ? 256 : 128));
 }
 
@@ -1469,7 +1478,14 @@ bool cgemm(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, char* why, in
     };
     if (ev0) (void)hipEventRecord(ev0, s);
     if (K == 0 || takes_wave(g)) {
-        launch_wave(g, ws, s, info);
+        // where it would split K over the grid (K >= 1024 over few tiles) and B lies
+        // along k, its reads of B are not contiguous: ragged tiles, staged through
+        // LDS (FP64, 85 x 117 outputs, K = 1360 21.8 us wave-sliced, 14.2 ragged; FP32,
+        // 64 x 96, K = 1088 14.4 / 10.3)
+        if (K > 0 && b_k && g.M >= 32 && g.N >= 32 && wave_splits(g, ws) > 1)
+            launch_ragged(g, ws, s, true, a_k, b_k, info);
+        else
+            launch_wave(g, ws, s, info);
         if (ev1) (void)hipEventRecord(ev1, s);
         return true;
     }

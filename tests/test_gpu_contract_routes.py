@@ -27,3 +27,14 @@ def _check(prec, case):
 @pytest.mark.parametrize("case", SHORT_INNER)
 def test_short_inner_extents(case):
     _check(T.PREC_FP32, case)
+
+
+# tiles enough for one wave each, thin outputs beside long ones, and a long K over few tiles
+WAVES = [(160, 36, 20, 2, 16, 0), (21, 73, 245, 0, 4, 0), (27, 64, 129, 0, 4, 0), (9, 208, 156, 1, 2, 0),
+         (8, 256, 256, 0, 17, 1), (16, 33, 700, 1, 5, 1), (13, 200, 90, 1, 33, 1), (85, 9, 13, 0, 16, 1), (64, 8, 12, 0, 17, 1)]
+
+
+@pytest.mark.parametrize("prec", [T.PREC_FP64, T.PREC_FP32])
+@pytest.mark.parametrize("case", WAVES)
+def test_wave_counts(case, prec):
+    _check(prec, case)
