@@ -1176,6 +1176,12 @@ void launch_ragged(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, bool 
     if (splits > 1) splitk_reduce(g, splits, (const R*)ws.partial, s);
 }
 
+// Estimated time (us) of the pass over split K's partial sums.
+template <typename R>
+double reduce_us(const Gemm<R>& g, int splits) {
+    return splits < 2 ? 0.0 : 1.0 + splits * 4.0 * sizeof(R) * g.M * (double)g.N * g.B1 * g.B2 / 7.2e6;
+}
+
 // Launch of the aligned form of k_cgemm_mfma.  64 x 64 tiles (8 waves, two blocks
 // per CU) where they cover every CU; 32 x 32 tiles (4 waves) where those do not
 // or pad less, with two or four groups of waves on a tile when there are few
@@ -1198,21 +1204,47 @@ template <typename R>
 AlignedPlan plan_aligned(const Gemm<R>& g, const GemmScratch& ws) {
     const int K = g.Kin * g.Kout, kt = K / 16;
     const int64_t t32 = tile_count(g, 32, 32), t64 = tile_count(g, 64, 64), t128 = tile_count(g, 128, 64);
-    // 32 x 32 tiles reach 0.87 of the larger ones' rate (FP32: 0.8) where both fill
-    // the chip (128^3: 305 / 268 us)
-    const double r32 = sizeof(R) == 8 ? 0.87 : 0.8;
+    // us per k of a 32 x 32 tile on every CU; 32 x 32 tiles reach 0.87 of the larger
+    // ones' rate (FP32: 0.8) where both fill the chip (128^3: 305 / 268 us)
+    const double ck = sizeof(R) == 8 ? 0.041 : 0.0263, r32 = sizeof(R) == 8 ? 0.87 : 0.8;
+    // time in rounds of tiles over the CUs: with a short K, 64 x 64 tiles a little
+    // over one to a CU leave most of the second round empty (FP64, 1944 x 48 outputs of nine
+    // operators, 279 tiles: 17.8 us, 1098 of 32 x 32 14.9; FP32, 2560 x 64 of nine,
+    // 360: 14.8 / 13.7; but 221 of them 11.5, 884 of 32 x 32 12.7; K = 1024, 10368 x 128
+    // outputs, 324 tiles 197, 1296 of 32 x 32 222)
+    auto rounds = [&](int64_t blocks) {
+        return blocks <= 256 ? 1.0 : K <= 256 ? (double)((blocks + 255) / 256) : blocks / 256.0;
+    };
+    const double us64 = rounds(t64) * 4 * r32 * ck * K;
+    // 32 x 32 tiles that leave CUs without a block split K, into whole rounds where
+    // it pays (FP64, 192 x 288 outputs, K = 1536, 54 tiles: 33.7 us with 270 blocks,
+    // 25.4 with 216; 1152 x 112, K = 1904, 144 tiles: 77 with one split, 63 with four;
+    // FP32, 160 x 96 of twelve, K = 480, 180 tiles: 18.7 with two, 14.6 with one)
+    const int64_t per = 2 * (int64_t)g.M * g.N * g.B1 * g.B2 * (int64_t)sizeof(R);
+    int s32 = 1;
+    double us32 = rounds(t32) * ck * K;
+    if (t32 < 256 && (int64_t)g.M * g.N < (1LL << 31))
+        for (int q = 2; q <= std::min<int64_t>(std::min(16, kt / 8), ws.bytes / per); ++q) {
+            const double u = std::ceil(t32 * q / 256.0) / q * ck * K + reduce_us(g, q);
+            if (u < us32) {
+                us32 = u;
+                s32 = q;
+            }
+        }
     // few outputs and a long K: 64 x 64 tiles split to 512 blocks, where the 32 x 32
     // ones would be split too (128 x 128 outputs, K = 16384: 53.7 us with 32 x 32
     // tiles, 48.4 with 64 x 64; half the flops: 31.3 / 32.2) or K is so long that
     // the partial sums weigh little (64 x 8192 outputs, K = 4096: 353 / 268; 64 x 4096,
     // K = 2048: 84.9 / 77.6; K = 1024: 46.2 / 51)
-    const bool deep = t64 < 256 && t64 * (kt / 8) >= 512 && (t32 < 256 || kt >= 128);
+    // and little padding (24 x 64 outputs of 80, K = 1088: 44.0 / 31.9)
+    const bool deep = t64 < 256 && t64 * (kt / 8) >= 512 && (t32 < 256 || kt >= 128) &&
+                      3 * padded(g.M, g.N, 64, 64) <= 4 * padded(g.M, g.N, 32, 32);
     AlignedPlan p;
-    p.small = !deep && (t64 < 256 || padded(g.M, g.N, 32, 32) / r32 < padded(g.M, g.N, 64, 64));
+    p.small = !deep && us32 < us64;
     p.big = !p.small && sizeof(R) == 8 && K >= 512 && t128 >= 256 &&
             padded(g.M, g.N, 128, 64) <= padded(g.M, g.N, 64, 64);
     const int64_t tiles = p.small ? t32 : p.big ? t128 : t64;
-    p.splits = p.big ? 1 : split_factor(g, ws, tiles, kt, p.small ? 256 : 512, p.small || deep ? 8 : 32);
+    p.splits = p.big ? 1 : p.small ? s32 : split_factor(g, ws, tiles, kt, 512, deep ? 8 : 32);
     p.kchunk = (kt + p.splits - 1) / p.splits * 16;
     p.splits = (K + p.kchunk - 1) / p.kchunk;
     p.blocks = tiles * p.splits;
@@ -1253,12 +1285,6 @@ void launch_aligned(const Gemm<R>& g, const GemmScratch& ws, hipStream_t s, bool
         TTN_MFMA_LAUNCHES(128, 64, 4, 4, 1, 1);
 #undef TTN_MFMA_LAUNCHES
     if (p.splits > 1) splitk_reduce(g, p.splits, (const R*)ws.partial, s);
-}
-
-// Estimated time (us) of the pass over split K's partial sums.
-template <typename R>
-double reduce_us(const Gemm<R>& g, int splits) {
-    return splits < 2 ? 0.0 : 1.0 + splits * 4.0 * sizeof(R) * g.M * (double)g.N * g.B1 * g.B2 / 7.2e6;
 }
 
 // Tiles and split factor of a k_cgemm_split launch with np pieces: of 128 x 128, 64 x

@@ -38,3 +38,14 @@ WAVES = [(160, 36, 20, 2, 16, 0), (21, 73, 245, 0, 4, 0), (27, 64, 129, 0, 4, 0)
 @pytest.mark.parametrize("case", WAVES)
 def test_wave_counts(case, prec):
     _check(prec, case)
+
+
+# aligned tiles: 32 x 32 ones split into whole rounds, 64 x 64 ones around one round, a padded long K
+ALIGNED = [(192, 16, 18, 0, 8, 1), (16, 72, 112, 2, 17, 1), (160, 12, 8, 0, 5, 1), (112, 27, 12, 0, 33, 1),
+           (128, 48, 48, 2, 4, 0), (48, 64, 221, 0, 1, 0), (54, 36, 48, 2, 9, 0), (80, 32, 64, 2, 9, 0), (24, 64, 80, 1, 17, 1)]
+
+
+@pytest.mark.parametrize("prec", [T.PREC_FP64, T.PREC_FP32])
+@pytest.mark.parametrize("case", ALIGNED)
+def test_aligned_plans(case, prec):
+    _check(prec, case)
