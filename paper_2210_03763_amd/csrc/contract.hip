@@ -1564,10 +1564,10 @@ bool cgemm_fusable(const Gemm<double>& g) { return aligned_form(g) && g.B1 * g.B
 
 // C[m, n] = sum A[m, (kin, kout)] B[kin, n] f[kout, n]; A and B contiguous along
 // k_in, f planar, contiguous along k_out
-void cgemm_outer(const Gemm<double>& g, const double* f, int64_t f_plane, int64_t sfn, const GemmScratch& ws,
-                 hipStream_t s) {
+int cgemm_outer(const Gemm<double>& g, const double* f, int64_t f_plane, int64_t sfn, const GemmScratch& ws,
+                hipStream_t s) {
     typedef double R;
-    if (g_dry_run || g.M <= 0 || g.N <= 0) return;
+    if (g_dry_run || g.M <= 0 || g.N <= 0) return 1;
     const AlignedPlan p = plan_aligned(g, ws);
     MfmaExtra<R> x;
     x.f = f;
@@ -1584,13 +1584,14 @@ void cgemm_outer(const Gemm<double>& g, const double* f, int64_t f_plane, int64_
     else
         TTN_MFMA_LAUNCH(128, 64, 4, 4, 1, 1, true, true, MFMA_OUTER);
     if (p.splits > 1) splitk_reduce(g, p.splits, (const R*)ws.partial, s);
+    return p.splits;
 }
 
 // C = A B (A contiguous along m, B along k_in) and norms[n][tm] = sum over the
 // 64 rows of tile row tm of |C[m, n]|^2
-void cgemm_norms(const Gemm<double>& g, double* norms, hipStream_t s) {
+int cgemm_norms(const Gemm<double>& g, double* norms, hipStream_t s) {
     typedef double R;
-    if (g_dry_run || g.M <= 0 || g.N <= 0) return;
+    if (g_dry_run || g.M <= 0 || g.N <= 0) return 1;
     const GemmScratch ws;
     AlignedPlan p{};
     p.splits = 1;
@@ -1599,6 +1600,7 @@ void cgemm_norms(const Gemm<double>& g, double* norms, hipStream_t s) {
     MfmaExtra<R> x;
     x.norms = norms;
     TTN_MFMA_LAUNCH(64, 64, 2, 4, 1, 2, false, true, MFMA_NORMS);
+    return 1;
 }
 #undef TTN_MFMA_LAUNCH
 

@@ -441,7 +441,8 @@ struct Ctx {
         }
         return true;
     }
-    // a contraction with a launch of its own (checked and recorded as run does)
+    // a contraction with a launch of its own (checked and recorded as run does);
+    // launch returns the split-K factor it took
     template <typename F>
     void run_fused(const Gemm<R>& g, F launch) {
         char why[256];
@@ -452,9 +453,9 @@ struct Ctx {
         int idx = -1;
         const bool rec = window(g, idx, e0, e1);
         if (e0) (void)hipEventRecord(e0, h->stream);
-        launch();
+        const int splits = launch();
         if (e1) (void)hipEventRecord(e1, h->stream);
-        if (rec) record(8.0 * g.M * g.N * (double)g.Kin * g.Kout, 1, 2, idx);
+        if (rec) record(8.0 * g.M * g.N * (double)g.Kin * g.Kout, splits, 2, idx);
     }
     void run(const Gemm<R>& g) {
         char why[256];

@@ -77,11 +77,11 @@ bool cgemm_check(const Gemm<R>& g, const GemmScratch& ws, char* why, int whylen)
 bool cgemm_in_place(const Gemm<double>& g, const GemmScratch& ws, bool over_a);
 
 // Contractions of the sampling walk with the pass beside them folded in (see
-// contract.hip); usable when cgemm_fusable(g).
+// contract.hip); usable when cgemm_fusable(g).  They return the split-K factor.
 bool cgemm_fusable(const Gemm<double>& g);
-void cgemm_outer(const Gemm<double>& g, const double* f, int64_t f_plane, int64_t sfn, const GemmScratch& ws,
-                 hipStream_t s);
-void cgemm_norms(const Gemm<double>& g, double* norms, hipStream_t s);
+int cgemm_outer(const Gemm<double>& g, const double* f, int64_t f_plane, int64_t sfn, const GemmScratch& ws,
+                hipStream_t s);
+int cgemm_norms(const Gemm<double>& g, double* norms, hipStream_t s);
 
 // Independent short contractions (cgemm_groupable: those that cgemm would give
 // to the wave-sliced kernel without split K) in one launch, for sequences
