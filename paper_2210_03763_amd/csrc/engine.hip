@@ -393,7 +393,8 @@ int take_events(ttn_handle* h, int k) {
 // short ones are held back and leave as one launch; a contraction that reads or
 // writes what a held one writes, or writes what one reads, sends them off
 // first, so the sequence means what it says.  Only contractions may be issued
-// inside a Group.
+// inside a Group, and between the first held one and the flush nothing else is
+// recorded.
 template <typename R>
 struct Ctx {
     ttn_handle* h;
@@ -402,7 +403,7 @@ struct Ctx {
     struct Span {
         uintptr_t lo, hi;
     };
-    int depth = 0, held = 0;
+    int depth = 0, held = 0, held_idx = -1;
     Gemm<R> hold[GROUP_MAX];
     Span rd[GROUP_MAX][2], wr[GROUP_MAX];
     double held_flops = 0;
@@ -418,12 +419,21 @@ struct Ctx {
     // pair around all its launches), the others one by one
     int events() { return h->prof_timed && !h->in_heff ? take_events(h, 2) : -1; }
 
-    void flush() {
+    // Events and room for the records of the contractions to be held: what of a
+    // profiling window can fail, before flush, which ~Group calls, needs it.
+    void reserve_window() {
+        held_idx = -1;
+        if (!h->prof || h->dry) return;
+        const size_t need = h->prof_recs.size() + GROUP_MAX;
+        if (h->prof_recs.capacity() < need) h->prof_recs.reserve(2 * need);
+        held_idx = events();
+    }
+    void flush() noexcept {
         if (held == 0) return;
         const int cnt = held;
         held = 0;
         const bool rec = h->prof && !h->dry;
-        const int idx = rec ? events() : -1;
+        const int idx = held_idx;
         if (idx >= 0) (void)hipEventRecord(h->ev_pool[idx], h->stream);
         const int launches = cgemm_group<R>(hold, cnt, h->gs, h->stream);
         if (idx >= 0) (void)hipEventRecord(h->ev_pool[idx + 1], h->stream);
@@ -472,6 +482,7 @@ struct Ctx {
                     flush();
                     break;
                 }
+            if (held == 0) reserve_window();
             hold[held] = g;
             rd[held][0] = a;
             rd[held][1] = b;
@@ -1056,6 +1067,7 @@ struct HeffMark {
     explicit HeffMark(ttn_handle* hh) : h(hh) {
         if (h->prof) h->prof_matvecs += 1;
         if (h->prof && h->prof_timed && !h->dry) {
+            if (h->mv_recs.size() == h->mv_recs.capacity()) h->mv_recs.reserve(2 * h->mv_recs.size() + 64);
             idx = take_events(h, 2);
             first = h->prof_recs.size();
             (void)hipEventRecord(h->ev_pool[idx], h->stream);
