@@ -283,12 +283,13 @@ int ttn_leg_contract_noalloc(int32_t precision, int32_t leg, int32_t DL, int32_t
 
 /* The eigensolver of the two-site split on caller memory (kernel unit
  * tests): eigenvalues and eigenvectors of the Hermitian n x n matrix d_a
- * (planar complex FP64, column-major; destroyed), 1 <= n <= 256, by the
- * cyclic Jacobi method with round-robin pair ordering in one workgroup.
+ * (planar complex FP64, column-major; may be destroyed), 1 <= n <= 256, of
+ * any scale, by cyclic Jacobi rotations (in one workgroup up to 48 rows, by
+ * blocks above) and one step of iterative refinement.
  * d_w[k] receives the k-th largest eigenvalue, d_order[k] (int32) the
  * column of d_v (n x n planar) holding its eigenvector.  Synchronises
  * hip_stream; TTN_ENUMERIC if the iteration does not converge, TTN_EINVAL
- * for bad arguments.  Allocates a small status block. */
+ * for bad arguments.  Allocates its work (up to 6.1 MiB). */
 int ttn_herm_eig(int32_t n, void* d_a, void* d_v, void* d_w, void* d_order, void* hip_stream);
 
 /* Device time of the contraction kernels inside a profiling window. */
@@ -339,7 +340,8 @@ typedef struct {
     double flops;     /* algorithmic real flops (8 M N K)                     */
     double ms;        /* event time of the main kernel and its reduction; -1
                          for H_eff / K_eff launches (timed per matvec) and in
-                         untimed windows                                      */
+                         untimed windows; of short contractions issued together
+                         as several launches the first has all flops and time */
 } ttn_launch_rec;
 
 /* Opens a profiling window: from now on contraction launches are recorded

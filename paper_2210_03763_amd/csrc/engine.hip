@@ -150,13 +150,14 @@ struct ttn_handle {
     };
     std::vector<MatvecRec> mv_recs;
     struct ProfRec {
-        int ev;          // begin event (end: ev + 1), -1 when timed per matvec
+        int ev;          // begin event (end: ev + 1), -1 when timed per matvec, -2 with the record before
         int prec;        // 0 fp64, 1 fp32
         double flops;    // algorithmic real flops (8 per complex multiply-add)
         bool heff;
         int kernel = 0;  // CgemmInfo::kernel
         int splits = 0;
         int matvec = -1;
+        double ms = -1.0;   // device time, read once when the window closes
     };
     std::vector<ProfRec> prof_recs;
     std::vector<ttn_launch_rec> prof_last;   // launches of the last closed window
@@ -437,7 +438,7 @@ struct Ctx {
         if (idx >= 0) (void)hipEventRecord(h->ev_pool[idx], h->stream);
         const int launches = cgemm_group<R>(hold, cnt, h->gs, h->stream);
         if (idx >= 0) (void)hipEventRecord(h->ev_pool[idx + 1], h->stream);
-        for (int i = 0; rec && i < launches; ++i) record(i == 0 ? held_flops : 0.0, 1, 2, i == 0 ? idx : -1);
+        for (int i = 0; rec && i < launches; ++i) record(i == 0 ? held_flops : 0.0, 1, 2, i == 0 || idx < 0 ? idx : -2);
         held_flops = 0;
     }
 
@@ -1765,9 +1766,11 @@ void step_body(ttn_handle* h, double tau) {
 }
 
 // Device time of one individually timed contraction launch (its main kernel
-// and split-K reduction between two events); -1 for launches timed per matvec.
+// and split-K reduction between two events); -1 for launches timed per matvec,
+// 0 for one whose time the record before it holds.  Two readings of the same
+// events differ by a tick now and then, so every launch is read once.
 double launch_ms(const ttn_handle::ProfRec& r, const std::vector<hipEvent_t>& pool) {
-    if (r.ev < 0) return -1.0;
+    if (r.ev < 0) return r.ev == -2 ? 0.0 : -1.0;
     float a = 0.f;
     HIPCHECK(hipEventElapsedTime(&a, pool[r.ev], pool[r.ev + 1]));
     return (double)a;
@@ -1776,9 +1779,10 @@ double launch_ms(const ttn_handle::ProfRec& r, const std::vector<hipEvent_t>& po
 // Adds the launches, flops and device times of a window to `out`: launches
 // outside H_eff / K_eff matvecs carry their own event time; the matvec
 // launches are timed together, per matvec.
-void accumulate_prof(const ttn_handle* h, ttn_profile* out) {
-    for (const auto& r : h->prof_recs) {
-        const double ms = r.ev >= 0 ? launch_ms(r, h->ev_pool) : 0.0;
+void accumulate_prof(ttn_handle* h, ttn_profile* out) {
+    for (auto& r : h->prof_recs) {
+        r.ms = launch_ms(r, h->ev_pool);
+        const double ms = std::max(0.0, r.ms);
         ttn_kernel_prof& k = r.prec ? out->gemm_f32 : out->gemm_f64;
         k.launches += 1;
         k.ms += ms;
@@ -2749,7 +2753,7 @@ int ttn_profile_end(ttn_handle* h, ttn_profile* out) {
         h->prof_last.clear();
         for (const auto& r : h->prof_recs)
             h->prof_last.push_back(ttn_launch_rec{r.kernel, r.prec, r.heff ? 1 : 0, r.splits, r.matvec, 0, r.flops,
-                                                  launch_ms(r, h->ev_pool)});
+                                                  r.ms});
         for (const auto& r : h->vec_recs) {
             float ms = 0.f;
             HIPCHECK(hipEventElapsedTime(&ms, h->ev_pool[r.ev], h->ev_pool[r.ev + 1]));

@@ -1,11 +1,13 @@
-"""A profiling window that runs out of events: ttn_tdvp_step has to return its
-error, wherever in a sequence of held-back contractions the event was wanted
-(an exception out of a destructor would end the process).  The library's host
-code runs on the CPU against a HIP runtime made of the C library: device memory
-is host memory, launches do nothing."""
+"""Profiling windows against a HIP runtime made of the C library (the library's
+host code runs on the CPU, device memory is host memory, launches do nothing).
+A window that runs out of events: ttn_tdvp_step has to return its error, wherever
+in a sequence of held-back contractions the event was wanted (an exception out
+of a destructor would end the process).  A window whose events read otherwise
+at every call: its launch records and its sums have to come from one reading."""
+import os
+import pathlib
 import subprocess
 import sys
-import textwrap
 
 import pytest
 
@@ -21,7 +23,8 @@ int hipEventCreate(void **e) {
     return 0;
 }
 int hipEventDestroy(void *e) { free(e); return 0; }
-int hipEventElapsedTime(float *t, void *a, void *b) { *t = 0.0f; return 0; }
+static int g_reads;
+int hipEventElapsedTime(float *t, void *a, void *b) { *t = 1.0f + 0.0078125f * (g_reads++ % 64); return 0; }
 int hipEventRecord(void *e, void *s) { return 0; }
 int hipFree(void *p) { free(p); return 0; }
 int hipGetDevice(int *d) { *d = 0; return 0; }
@@ -61,6 +64,9 @@ buf = (C.c_char * (n.value + 4096))()
 e = np.ascontiguousarray(w.seg_edges, dtype=np.float64)
 om, de = (np.ascontiguousarray(a, dtype=np.float64) for a in (w.omega, w.delta))
 z = np.zeros(2, np.int32)
+"""
+
+OUT_OF_EVENTS = r"""
 failed = 0
 for events in list(range(0, 64, 2)) + [100000]:          # the pool grows by pairs, in a handle of its own
     stub.stub_events(-1)
@@ -78,16 +84,32 @@ print("out of events", failed, flush=True)
 assert failed == 32
 """
 
+ONE_READING = r"""
+h = C.c_void_p()
+assert L.ttn_init(C.byref(cfg), (C.addressof(buf) + 4095) // 4096 * 4096, n, None, C.byref(h)) == 0
+assert L.ttn_set_pulses(h, om.shape[1], T._dptr(e), T._dptr(om), T._dptr(de), 0, T._iptr(z), T._iptr(z), T._dptr(np.zeros(2))) == 0
+assert L.ttn_profile_begin(h) == 0 and L.ttn_tdvp_step(h, 0.01, 1, None) == 0
+p = T.Profile()
+assert L.ttn_profile_end(h, C.byref(p)) == 0
+recs = (T.LaunchRec * L.ttn_profile_launches(h, None, 0))()
+L.ttn_profile_launches(h, recs, len(recs))
+single = sum(r.ms for r in recs if r.ms >= 0)
+print("launches", len(recs), single + p.heff.ms, p.gemm_f32.ms + p.gemm_f64.ms, flush=True)
+assert len(recs) == p.gemm_f32.launches + p.gemm_f64.launches
+assert all((r.ms < 0) == (r.heff == 1) for r in recs)
+assert abs(single + p.heff.ms - (p.gemm_f32.ms + p.gemm_f64.ms)) < 1e-9 * len(recs)
+"""
+
 
 @pytest.mark.parametrize("precision", [0, 1])
-def test_running_out_of_events_is_an_error(tmp_path, precision):
-    src, so = tmp_path / "hip_stub.c", tmp_path / "libhip_stub.so"
+@pytest.mark.parametrize("body", [OUT_OF_EVENTS, ONE_READING], ids=["out-of-events", "one-reading"])
+def test_window(tmp_path, body, precision):
+    src, so, drv = tmp_path / "hip_stub.c", tmp_path / "libhip_stub.so", tmp_path / "driver.py"
     src.write_text(STUB)
     subprocess.run(["gcc", "-shared", "-fPIC", "-w", "-o", str(so), str(src)], check=True)
-    drv = tmp_path / "driver.py"
-    drv.write_text(textwrap.dedent(DRIVER))
+    drv.write_text(DRIVER + body)
+    root = str(pathlib.Path(__file__).parents[1])
     r = subprocess.run([sys.executable, str(drv), str(so), str(precision)], capture_output=True, text=True, timeout=120,
-                       cwd=str(__import__("pathlib").Path(__file__).parents[1]),
-                       env=dict(__import__("os").environ, PYTHONPATH=str(__import__("pathlib").Path(__file__).parents[1])))
+                       cwd=root, env=dict(os.environ, PYTHONPATH=root))
     print(r.stdout[-500:], r.stderr[-1500:], flush=True)
     assert r.returncode == 0, f"exit {r.returncode}"
