@@ -49,8 +49,8 @@ __device__ inline double block_sum_all(double v, double* sh) {
 
 // Sums P values (P a power of two, 2 <= P <= 32) over the block with one
 // barrier: a butterfly inside each wave leaves value (l >> 1) & (P - 1),
-// summed over the wave, in lane l; the waves' results meet in sh (P per wave,
-// at most four waves).  Returns the block total of value threadIdx.x in
+// summed over the wave, in lane l; the waves' results meet in sh (P per wave).
+// Returns the block total of value threadIdx.x in
 // threads 0 .. P-1.
 template <int H, int P>
 __device__ inline void butterfly_step(double (&a)[P], int lane) {
@@ -85,8 +85,6 @@ __device__ inline double block_sum_p(double (&a)[P], double* sh) {
         for (int w2 = 0; w2 < (int)(blockDim.x >> 6); ++w2) r += sh[P * w2 + threadIdx.x];
     return r;
 }
-
-__device__ inline double block_sum32(double (&a)[32], double* sh) { return block_sum_p<32>(a, sh); }
 
 // smallest power of two >= 2 kc
 constexpr int pow2_pairs(int kc) {
