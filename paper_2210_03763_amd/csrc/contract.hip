@@ -688,11 +688,10 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // with FP32 accumulation; the complex product takes four real ones.
 //   NP = 3 (FP32 mode): 3 x 8 significant bits hold an FP32 number exactly if
 // its pieces lie in the range of bf16, the three dropped products are below
-// 2^-24 of the whole.  Against 64 bits
-// the result is closer than that of the FP32 matrix-core kernel it replaced
-// (three FP32 products per complex one, whose Re + Im sums cancel): left-leg
-// stack of a 128^3 node 2.6e-7 (3.9e-7 before), parent-leg sum over 33
-// operators 8.0e-7 (1.17e-6).
+// 2^-24 of the whole.  Against 64 bits the result is closer than that of the
+// FP32 matrix-core kernel it replaced (three FP32 products per complex one,
+// whose Re + Im sums cancel): left-leg stack of a 128^3 node 2.6e-7 (3.9e-7
+// before), parent-leg sum over 33 operators 8.0e-7 (1.17e-6).
 //   Range of NP = 3: the first piece overflows from 3.39e38 on (an infinity turns
 // into NaN), and below 2^-100 the last ones reach the subnormals of bf16.
 // Outputs of operands out of range are taken again in plain FP32 products, with
@@ -711,10 +710,10 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // 71 % of the cycles, but at 1.7 GHz -- 1.2 PFLOP/s of bf16 products is the
 // chip's power limit (a library bf16 product of 8192^3 reaches 1.13).
 // Measured, us, FP32 matrix cores -> here: 128^3 node, stacks of 17 on the left
-// leg 331 -> 223 and of 16 on the right leg 292 -> 198, right-leg sum over 17
-// 257 -> 183, parent-leg sum over 33 477 -> 337, 256^3 sum over five 1145 ->
-// 804.  BF16x3, kernel with 16x16x32 products and 32-wide k-tiles -> here:
-// 229 -> 156, 243 -> 209 (33), 256^3 right-leg sum over nine 914 -> 840.
+// leg 337 -> 219 and of 16 on the right leg 292 -> 199, right-leg sum over 17
+// 257 -> 184, parent-leg sum over 33 480 -> 345, 256^3 sum over five 1151 ->
+// 823.  BF16x3, kernel with 16x16x32 products and 32-wide k-tiles -> here:
+// 226 -> 148, 237 -> 216 (33), 256^3 right-leg sum over nine 953 -> 853.
 //   RAG: any inner extent, padded to a whole k-tile for every outer index.
 // ---------------------------------------------------------------------------
 
@@ -1183,17 +1182,16 @@ double reduce_us(const Gemm<R>& g, int splits) {
 }
 
 // Launch of the aligned form of k_cgemm_mfma.  64 x 64 tiles (8 waves, two blocks
-// per CU) where they cover every CU; 32 x 32 tiles (4 waves) where those do not
-// or pad less, with two or four groups of waves on a tile when there are few
-// of them, so that a CU always has 8 to 16 waves and no split's partial sums
-// pass through memory; FP64 launches with a long K take 128 x 64 tiles (16
-// waves).  K is split over the grid only where the 32 x 32 tiles leave CUs
-// without a block, or where a long K meets one 64 x 64 tile per CU.
+// per CU) or 32 x 32 ones (4 waves), whichever the estimate below puts first, with
+// two or four groups of waves on a 32 x 32 tile when there are few of them, so
+// that a CU has 8 to 16 waves; FP64 launches with a long K take 128 x 64 tiles
+// (16 waves).  K is split over the grid only where the 32 x 32 tiles leave CUs
+// without a block, or where a long K meets few 64 x 64 tiles.
 // Measured, FP64, us (128 x 64 tiles or 64 x 64 ones of four waves with K split
 // over the grid / the rule here): right-leg sum of a 64^3 node over 4, 8, 16
-// operators 29.7 / 15.6, 34.2 / 26.5, 51.0 / 46.2; stack of 8 over 64^3 25.8 /
-// 25.1, over 128^3 281 / 268; 96^3 sum over 8 201 / 116; 32 x 32 x 128 node,
-// parent-leg stack of 8 36.5 / 24.7.  FP32, 64^3 sum over 4: 21.7 / 11.4.
+// operators 28.9 / 14.6, 33.7 / 24.8, 48.9 / 44.1; stack of 8 over 64^3 23.8 /
+// 24.2, over 128^3 292 / 267; 96^3 sum over 8 191 / 110; 32 x 32 x 128 node,
+// parent-leg stack of 8 34.7 / 23.3.  FP32, 64^3 sum over 4: 23.7 / 10.2.
 struct AlignedPlan {
     bool small, big;
     int groups, splits, kchunk;
@@ -1208,10 +1206,10 @@ AlignedPlan plan_aligned(const Gemm<R>& g, const GemmScratch& ws) {
     // ones' rate (FP32: 0.8) where both fill the chip (128^3: 305 / 268 us)
     const double ck = sizeof(R) == 8 ? 0.041 : 0.0263, r32 = sizeof(R) == 8 ? 0.87 : 0.8;
     // time in rounds of tiles over the CUs: with a short K, 64 x 64 tiles a little
-    // over one to a CU leave most of the second round empty (FP64, 1944 x 48 outputs of nine
-    // operators, 279 tiles: 17.8 us, 1098 of 32 x 32 14.9; FP32, 2560 x 64 of nine,
-    // 360: 14.8 / 13.7; but 221 of them 11.5, 884 of 32 x 32 12.7; K = 1024, 10368 x 128
-    // outputs, 324 tiles 197, 1296 of 32 x 32 222)
+    // over one to a CU leave most of the second round empty (FP64, 1944 x 48 outputs
+    // of nine operators, 279 tiles: 17.8 us, 1098 of 32 x 32 14.9; FP32, 2560 x 64 of
+    // nine, 360: 14.8 / 13.7; but 221 of them 11.5, 884 of 32 x 32 12.7; K = 1024,
+    // 10368 x 128 outputs, 324 tiles 197, 1296 of 32 x 32 222)
     auto rounds = [&](int64_t blocks) {
         return blocks <= 256 ? 1.0 : K <= 256 ? (double)((blocks + 255) / 256) : blocks / 256.0;
     };
@@ -1234,9 +1232,9 @@ AlignedPlan plan_aligned(const Gemm<R>& g, const GemmScratch& ws) {
     // few outputs and a long K: 64 x 64 tiles split to 512 blocks, where the 32 x 32
     // ones would be split too (128 x 128 outputs, K = 16384: 53.7 us with 32 x 32
     // tiles, 48.4 with 64 x 64; half the flops: 31.3 / 32.2) or K is so long that
-    // the partial sums weigh little (64 x 8192 outputs, K = 4096: 353 / 268; 64 x 4096,
-    // K = 2048: 84.9 / 77.6; K = 1024: 46.2 / 51)
-    // and little padding (24 x 64 outputs of 80, K = 1088: 44.0 / 31.9)
+    // the partial sums weigh little (64 x 8192 outputs, K = 4096: 353 / 268; 64 x
+    // 4096, K = 2048: 84.9 / 77.6; K = 1024: 46.2 / 51), and only with little
+    // padding (24 x 64 outputs of 80, K = 1088: 44.0 with 64 x 64, 31.9 with 32 x 32)
     const bool deep = t64 < 256 && t64 * (kt / 8) >= 512 && (t32 < 256 || kt >= 128) &&
                       3 * padded(g.M, g.N, 64, 64) <= 4 * padded(g.M, g.N, 32, 32);
     AlignedPlan p;

@@ -50,8 +50,7 @@ __device__ inline double block_sum_all(double v, double* sh) {
 // Sums P values (P a power of two, 2 <= P <= 32) over the block with one
 // barrier: a butterfly inside each wave leaves value (l >> 1) & (P - 1),
 // summed over the wave, in lane l; the waves' results meet in sh (P per wave).
-// Returns the block total of value threadIdx.x in
-// threads 0 .. P-1.
+// Returns the block total of value threadIdx.x in threads 0 .. P-1.
 template <int H, int P>
 __device__ inline void butterfly_step(double (&a)[P], int lane) {
     // lanes that differ in bit 2H exchange one half of their first 2H values
