@@ -696,13 +696,13 @@ def summarize_profile(profdir, calib_mib=256, out_dir=None):
             "window), from the one after the calibration kernel (name containing `neg_kernel`) to the",
             "window's last contraction launch.",
             "",
-            "Command (R = repository root on the GPU box), then the summary:",
+            "Command (R = repository root), then the summary:",
             "",
             "```",
             f"cd /tmp && export TMPDIR=/tmp && rocprofv3 --kernel-trace --stats --output-format csv "
-            f"-d $R/gpurun_out/prof/trace -o run -- python3 $R/bench.py {base} "
-            f"--launch-log $R/gpurun_out/prof/trace/launches.json",
-            "python bench.py --summarize-profile gpurun_out/prof",
+            f"-d $R/out/prof/trace -o run -- python3 $R/bench.py {base} "
+            f"--launch-log $R/out/prof/trace/launches.json",
+            "python bench.py --summarize-profile out/prof",
             "```",
             "",
             "Kernel-name filter of the contraction launches: main kernels `k_cgemm_mfma<...>`,",
@@ -758,17 +758,17 @@ def summarize_profile(profdir, calib_mib=256, out_dir=None):
         sha = hashlib.sha256(open(CONTRACT_SRC, "rb").read()).hexdigest()
         L = json.load(open(os.path.join(fdir, "launches.json")))
         cmd = ("cd /tmp && export TMPDIR=/tmp && timeout -s KILL 420 rocprofv3 --pmc {c} --kernel-include-regex "
-               "\"k_cgemm|k_splitk_reduce|neg_kernel\" --output-format csv -d $R/gpurun_out/prof/{d} -o run -- "
-               "python3 $R/bench.py {b} --no-graphs --untimed-window --launch-log $R/gpurun_out/prof/{d}/launches.json")
+               "\"k_cgemm|k_splitk_reduce|neg_kernel\" --output-format csv -d $R/out/prof/{d} -o run -- "
+               "python3 $R/bench.py {b} --no-graphs --untimed-window --launch-log $R/out/prof/{d}/launches.json")
         lines = [
             "# HBM traffic of the H_eff/K_eff contraction launches, 8x8, d=4, chi=128 (mixed)",
             "",
-            "Two counter passes, one counter each (R = repository root on the GPU box), then the summary:",
+            "Two counter passes, one counter each (R = repository root), then the summary:",
             "",
             "```",
             cmd.format(c="FETCH_SIZE", d="fetch", b=base),
             cmd.format(c="WRITE_SIZE", d="write", b=base),
-            "python bench.py --summarize-profile gpurun_out/prof",
+            "python bench.py --summarize-profile out/prof",
             "```",
             "",
             "Kernel-name filter: the counter passes record only dispatches matching",

@@ -2550,8 +2550,8 @@ constexpr int JAC_THREADS = 1024;
 // disjoint rotations in LDS) and its launches: a round takes 13 us in
 // k_jacobi_solve and 7 in k_jacobi_apply, a launch after convergence 1.7.
 // 144 x 144, spectrum over six decades, 16 sweeps: 44.4 ms in one workgroup
-// with the matrix in global memory (31 us per step of 72 rotations) -> 4.1;
-// 256 x 256: about 150 -> 7.1.  Measured and dropped: every workgroup rotating
+// with the matrix in global memory (31 us per step of 72 rotations) -> 3.8;
+// 256 x 256: 264 -> 6.7.  Measured and dropped: every workgroup rotating
 // its own copy of P and Q (one launch per round, 28 us), LDS rows of 36 and 48
 // doubles (conflicts along columns, 19 us), the products of U formed by the
 // threads that rotate the matrix (17 us).
