@@ -700,7 +700,9 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // for only if those of its first k-tile are small.  The k loop has no part in it
 // (there, the largest magnitudes cost 1-4 % of a launch); what is left shows where
 // a block has few k-tiles (128^3 left-leg stack of sixteen, eight tiles: 205 us
-// without the checks, 209 with them; sum over 33: 344 / 343).
+// without the checks, 209 with them; sum over 33: 344 / 343).  Sums of finite
+// operands that overflow are not looked for: they are infinite or NaN, from 2^-8
+// below the largest FP32 number on (the three-product form: from a quarter of it).
 //   NP = 2 (BF16x3 mode): hi hi, hi lo, lo hi, relative error 4.4e-6.
 // Loads are FP32; pieces are made while staging.  A wave owns 64 x 32 outputs
 // (two 32 x 32 tiles); tiles of BM x BN outputs and 16 k, two LDS buffers (98 KB
